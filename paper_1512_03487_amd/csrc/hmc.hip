@@ -29,12 +29,6 @@ __device__ __forceinline__ void load_link(const double2 *__restrict__ U, size_t 
     }
 }
 
-__device__ __forceinline__ void store_link(double2 *__restrict__ U, size_t link, const M3 u) {
-    double2 *q = U + link * 9;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) q[k] = make_double2(u[k / 3][k % 3].r, u[k / 3][k % 3].i);
-}
-
 // c = a b (A: a^dagger when DA, B: b^dagger when DB)
 template <bool DA, bool DB>
 __device__ __forceinline__ void mm(const M3 a, const M3 b, M3 c) {
@@ -53,9 +47,88 @@ __device__ __forceinline__ void mm(const M3 a, const M3 b, M3 c) {
         }
 }
 
-__device__ __forceinline__ void madd(M3 a, const M3 b) {
+// c += a b (B: b^dagger when DB)
+template <bool DB>
+__device__ __forceinline__ void mm_acc(const M3 a, const M3 b, M3 c) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) a[k / 3][k % 3] = cadd(a[k / 3][k % 3], b[k / 3][k % 3]);
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            Cx<double> s = c[i][j];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) s = cmac(s, a[i][k], DB ? cconj(b[j][k]) : b[k][j]);
+            c[i][j] = s;
+        }
+}
+
+// Links through LDS. A link is nine consecutive 16-byte chunks, so lanes that load their own link
+// touch 64 cache lines with every load instruction, and the vector L1 looks the lines up one after
+// another: the gauge force spent its time there (74.8 us at 16^4 against 12 us of arithmetic). A
+// wavefront's 64 links are therefore fetched chunk by chunk, consecutive lanes on consecutive
+// chunks (7 links per instruction), and pass through a linear LDS area; reading a link back at the
+// nine-chunk pitch is free of bank conflicts (36 dwords: eight lanes cover the 32 banks once).
+constexpr int kLkChunks = 9;
+constexpr int kLkArea = 64 * kLkChunks;   // chunks of one wavefront's area
+
+struct LinkFetch {
+    chunk_t w[kLkChunks];
+};
+
+// Chunks of the links named by the wavefront's lanes (lane r: link index idx).
+__device__ __forceinline__ void link_fetch(const void *__restrict__ U, int idx, LinkFetch &f) {
+    const int lane = threadIdx.x & 63;
+    const chunk_t *src = static_cast<const chunk_t *>(U);
+#pragma unroll
+    for (int k = 0; k < kLkChunks; ++k) {
+        const int c = k * 64 + lane, r = c / kLkChunks;
+        f.w[k] = src[static_cast<size_t>(__shfl(idx, r, 64)) * kLkChunks + (c - r * kLkChunks)];
+    }
+}
+
+// Chunks of the wavefront's 64 consecutive links starting at link l0 (the last ones past n clamped).
+__device__ __forceinline__ void link_fetch_run(const void *__restrict__ U, long l0, long n, LinkFetch &f) {
+    const int lane = threadIdx.x & 63;
+    const chunk_t *src = static_cast<const chunk_t *>(U);
+    const long last = n * kLkChunks - 1;
+#pragma unroll
+    for (int k = 0; k < kLkChunks; ++k) {
+        const long c = l0 * kLkChunks + k * 64 + lane;
+        f.w[k] = src[c < last ? c : last];
+    }
+}
+
+__device__ __forceinline__ void link_put(const LinkFetch &f, chunk_t *area) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < kLkChunks; ++k) area[k * 64 + lane] = f.w[k];
+    wave_sync();
+}
+
+// The link in slot r of an area.
+__device__ __forceinline__ void link_get(const chunk_t *area, int r, M3 u) {
+#pragma unroll
+    for (int k = 0; k < kLkChunks; ++k) {
+        double2 v;
+        __builtin_memcpy(&v, &area[r * kLkChunks + k], 16);
+        u[k / 3][k % 3] = {v.x, v.y};
+    }
+}
+
+__device__ __forceinline__ void link_take(const LinkFetch &f, chunk_t *area, M3 u) {
+    link_put(f, area);
+    link_get(area, threadIdx.x & 63, u);
+    wave_sync();   // every lane has its link before the area is reused
+}
+
+// This lane's matrix into its slot of an area.
+__device__ __forceinline__ void link_leave(const M3 u, chunk_t *area) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < kLkChunks; ++k) {
+        const double2 v = make_double2(u[k / 3][k % 3].r, u[k / 3][k % 3].i);
+        __builtin_memcpy(&area[lane * kLkChunks + k], &v, 16);
+    }
+    wave_sync();
 }
 
 __device__ __forceinline__ int nbr(const GeomDev &g, int x4, int mu, int dir) {
@@ -66,63 +139,116 @@ __device__ __forceinline__ int nbr(const GeomDev &g, int x4, int mu, int dir) {
     return c == 0 ? x4 + (g.L[mu] - 1) * stride : x4 - stride;
 }
 
-// F_mu(x) = scale * (beta / 3) TA(U_mu(x) A_mu(x)); one thread per link.
-__global__ void __launch_bounds__(256)
-k_gauge_force(const double2 *__restrict__ U, double2 *__restrict__ F, GeomDev g, double beta, double scale, int accumulate) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= g.vol * 4) return;
-    const int mu = t & 3, x4 = t >> 2;
-    const int xpm = nbr(g, x4, mu, +1);
-    M3 A, u1, u2, u3, w, v;
+// F_mu(x) = scale * (beta / 3) TA(U_mu(x) A_mu(x)), added to F with ACC; one lane per link, a quad
+// of lanes per site. Fifteen fetches per lane in place of 19 per-lane link loads: the site's own
+// four links and its four U_nu(x - nu) are fetched once per quad and read by the other lanes from
+// LDS. Bound by load latency at two wavefronts per SIMD: the matrices take 247 registers and the
+// two areas 18 KB per wavefront. 16^4: 74.8 us with per-lane loads, 58.8 through LDS, 53.0 with
+// an XCD's blocks on one run of sites (both with F read and added to, which took another 17.9 us
+// in a pass of its own); the next staple's links fetched during the products 62 us (registers
+// spill).
+template <bool ACC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_gauge_force(const void *__restrict__ U, void *F, GeomDev g, double beta, double scale) {
+    __shared__ chunk_t sm[4][2 * kLkArea];
+    chunk_t *own = sm[threadIdx.x >> 6], *tmp = own + kLkArea;
+    const int lane = threadIdx.x & 63, mu = lane & 3;
+    const long nlinks = static_cast<long>(g.vol) * 4;
+    // the wavefront's first link (an XCD's blocks cover one run of sites, whose links its L2 holds)
+    const long l0 = static_cast<long>(xcd_block(blockIdx.x, gridDim.x)) * 256 + (threadIdx.x & ~63);
+    if (l0 >= nlinks) return;
+    const int x4 = static_cast<int>(l0 + lane < nlinks ? (l0 + lane) >> 2 : g.vol - 1);
+    // the lane's own direction: steps of the site index to x + mu and x - mu; other directions' from
+    // the quad's lanes
+    const int dp = nbr(g, x4, mu, +1) - x4, dm = nbr(g, x4, mu, -1) - x4;
+    const int quad = lane & ~3;
+    M3 A, u1, u2, w;
 #pragma unroll
     for (int k = 0; k < 9; ++k) A[k / 3][k % 3] = {0.0, 0.0};
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
+    LinkFetch f, f2;
+    link_fetch_run(U, l0, nlinks, f);
+    link_put(f, own);
+#pragma unroll 1
+    for (int j = 1; j < 4; ++j) {
         // upper staple U_nu(x+mu) U_mu(x+nu)^dagger U_nu(x)^dagger
-        const int xpn = nbr(g, x4, nu, +1);
-        load_link(U, static_cast<size_t>(xpm) * 4 + nu, u1);
-        load_link(U, static_cast<size_t>(xpn) * 4 + mu, u2);
-        load_link(U, static_cast<size_t>(x4) * 4 + nu, u3);
+        const int nu = (mu + j) & 3;
+        const int dpn = __shfl(dp, quad + nu, 64);
+        link_fetch(U, (x4 + dp) * 4 + nu, f);
+        link_fetch(U, (x4 + dpn) * 4 + mu, f2);
+        link_take(f, tmp, u1);
+        link_take(f2, tmp, u2);
         mm<false, true>(u1, u2, w);
-        mm<false, true>(w, u3, v);
-        madd(A, v);
-        // lower staple U_nu(x+mu-nu)^dagger U_mu(x-nu)^dagger U_nu(x-nu)
-        const int xmn = nbr(g, x4, nu, -1);
-        const int xpmmn = nbr(g, xpm, nu, -1);
-        load_link(U, static_cast<size_t>(xpmmn) * 4 + nu, u1);
-        load_link(U, static_cast<size_t>(xmn) * 4 + mu, u2);
-        load_link(U, static_cast<size_t>(xmn) * 4 + nu, u3);
-        mm<true, true>(u1, u2, w);
-        mm<false, false>(w, u3, v);
-        madd(A, v);
+        link_get(own, quad + nu, u1);
+        mm_acc<true>(w, u1, A);
     }
-    load_link(U, static_cast<size_t>(t), u1);
+    wave_sync();
+    link_fetch(U, (x4 + dm) * 4 + mu, f);   // U_mu(x - mu), read by the quad's other lanes
+    link_put(f, own);
+#pragma unroll 1
+    for (int j = 1; j < 4; ++j) {
+        // lower staple U_nu(x+mu-nu)^dagger U_mu(x-nu)^dagger U_nu(x-nu)
+        const int nu = (mu + j) & 3;
+        const int dmn = __shfl(dm, quad + nu, 64);
+        link_fetch(U, (x4 + dp + dmn) * 4 + nu, f);
+        link_fetch(U, (x4 + dmn) * 4 + mu, f2);
+        link_take(f, tmp, u1);
+        link_take(f2, tmp, u2);
+        mm<true, true>(u1, u2, w);
+        link_get(own, quad + nu, u1);
+        mm_acc<false>(w, u1, A);
+    }
+    link_fetch_run(U, l0, nlinks, f);
+    link_take(f, tmp, u1);
+    if (ACC) link_fetch_run(F, l0, nlinks, f);   // the field this force is added to, chunk by chunk
     mm<false, false>(u1, A, w);
     // TA(w) = (w - w^dagger)/2 - tr(w - w^dagger)/6
     const double imtr = w[0][0].i + w[1][1].i + w[2][2].i;
     const double c = scale * beta / 3.0;
-    M3 f;
-    if (accumulate) load_link(F, static_cast<size_t>(t), f);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             Cx<double> x = {0.5 * (w[a][b].r - w[b][a].r), 0.5 * (w[a][b].i + w[b][a].i)};
             if (a == b) x.i -= imtr / 3.0;
-            x = {c * x.r, c * x.i};
-            f[a][b] = accumulate ? cadd(f[a][b], x) : x;
+            u1[a][b] = {c * x.r, c * x.i};
         }
-    store_link(F, static_cast<size_t>(t), f);
+    link_leave(u1, tmp);
+    chunk_t *out = static_cast<chunk_t *>(F);
+#pragma unroll
+    for (int k = 0; k < kLkChunks; ++k) {
+        const long q = l0 * kLkChunks + k * 64 + lane;
+        double2 x;
+        __builtin_memcpy(&x, &tmp[k * 64 + lane], 16);
+        if (ACC) {
+            double2 y;
+            __builtin_memcpy(&y, &f.w[k], 16);
+            x = make_double2(y.x + x.x, y.y + x.y);
+        }
+        chunk_t o;
+        __builtin_memcpy(&o, &x, 16);
+        if (q < nlinks * kLkChunks) out[q] = o;
+    }
 }
 
-// U <- exp(eps P) U per link: Taylor series to order 16 of X / 2^k with |X| / 2^k < 1/2
-// (Frobenius norm), then k squarings (scaling and squaring).
+// U <- exp(eps P) U per link: the Taylor polynomial of order 16 of X / 2^k with |X| / 2^k < 1/2
+// (Frobenius norm), then k squarings (scaling and squaring). By Cayley-Hamilton, X^3 = t X^2 - s X +
+// d with t = tr X, s = (t^2 - tr X^2) / 2, d = det X, so Horner's scheme runs on the three scalar
+// coefficients of I, X and X^2 (three complex products a step in place of a matrix product) and the
+// matrices enter once, as X^2 and e0 + e1 X + e2 X^2. Links and momenta pass through LDS (above).
+// Bound by memory: 16^4 31.1 us with matrix products and per-lane loads, 18.9 us so (6.0 TB/s of
+// its 113 MB).
 __global__ void __launch_bounds__(256)
-k_link_exp(double2 *__restrict__ U, const double2 *__restrict__ P, double eps, long nlinks) {
-    const long l = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;
-    if (l >= nlinks) return;
-    M3 X, E, T, u, r;
-    load_link(P, l, X);
+k_link_exp(void *U, const void *__restrict__ P, double eps, long nlinks) {
+    __shared__ chunk_t sm[4][kLkArea];
+    chunk_t *tmp = sm[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63;
+    const long l0 = static_cast<long>(blockIdx.x) * 256 + (threadIdx.x & ~63);
+    if (l0 >= nlinks) return;
+    M3 X, E, T, u;
+    LinkFetch f, fu;
+    link_fetch_run(P, l0, nlinks, f);
+    link_fetch_run(U, l0, nlinks, fu);
+    link_take(f, tmp, X);
     double n2 = 0.0;
 #pragma unroll
     for (int k = 0; k < 9; ++k) n2 += X[k / 3][k % 3].r * X[k / 3][k % 3].r + X[k / 3][k % 3].i * X[k / 3][k % 3].i;
@@ -135,24 +261,50 @@ k_link_exp(double2 *__restrict__ U, const double2 *__restrict__ P, double eps, l
     const double sc = eps * ldexp(1.0, -sq);
 #pragma unroll
     for (int k = 0; k < 9; ++k) X[k / 3][k % 3] = cscale(sc, X[k / 3][k % 3]);
-    // Horner: E = I + X (I + X/2 (I + X/3 (... (I + X/16))))
-#pragma unroll
-    for (int k = 0; k < 9; ++k) E[k / 3][k % 3] = {k % 4 == 0 ? 1.0 : 0.0, 0.0};
-    for (int n = 16; n >= 1; --n) {
-        mm<false, false>(X, E, T);
+    mm<false, false>(X, X, T);
+    const Cx<double> t = cadd(cadd(X[0][0], X[1][1]), X[2][2]), t2 = cadd(cadd(T[0][0], T[1][1]), T[2][2]);
+    const Cx<double> s = cscale(0.5, csub(cmul(t, t), t2));
+    Cx<double> d = cmul(X[0][0], csub(cmul(X[1][1], X[2][2]), cmul(X[1][2], X[2][1])));
+    d = cmac(d, X[0][1], csub(cmul(X[1][2], X[2][0]), cmul(X[1][0], X[2][2])));
+    d = cmac(d, X[0][2], csub(cmul(X[1][0], X[2][1]), cmul(X[1][1], X[2][0])));
+    Cx<double> e0 = {1.0, 0.0}, e1 = {0.0, 0.0}, e2 = {0.0, 0.0};
+    for (int n = 16; n >= 2; --n) {
         const double inv = 1.0 / n;
+        const Cx<double> a0 = cmul(d, e2), a1 = csub(e0, cmul(s, e2)), a2 = cmac(e1, t, e2);
+        e0 = {1.0 + inv * a0.r, inv * a0.i};
+        e1 = cscale(inv, a1);
+        e2 = cscale(inv, a2);
+    }
+    {
+        // n = 1, with e0 - 1 in e0: the unit is added last, to the small rest of the diagonal
+        const Cx<double> a0 = cmul(d, e2), a1 = csub(e0, cmul(s, e2)), a2 = cmac(e1, t, e2);
+        e0 = a0;
+        e1 = a1;
+        e2 = a2;
+    }
 #pragma unroll
-        for (int k = 0; k < 9; ++k) E[k / 3][k % 3] = {(k % 4 == 0 ? 1.0 : 0.0) + inv * T[k / 3][k % 3].r,
-                                                       inv * T[k / 3][k % 3].i};
+    for (int k = 0; k < 9; ++k) {
+        Cx<double> x = cmac(cmul(e1, X[k / 3][k % 3]), e2, T[k / 3][k % 3]);
+        if (k % 4 == 0) {
+            x = cadd(x, e0);
+            x.r += 1.0;
+        }
+        E[k / 3][k % 3] = x;
     }
     for (int k = 0; k < sq; ++k) {
         mm<false, false>(E, E, T);
 #pragma unroll
         for (int j = 0; j < 9; ++j) E[j / 3][j % 3] = T[j / 3][j % 3];
     }
-    load_link(U, l, u);
-    mm<false, false>(E, u, r);
-    store_link(U, l, r);
+    link_take(fu, tmp, u);
+    mm<false, false>(E, u, T);
+    link_leave(T, tmp);
+    chunk_t *out = static_cast<chunk_t *>(U);
+#pragma unroll
+    for (int k = 0; k < kLkChunks; ++k) {
+        const long q = l0 * kLkChunks + k * 64 + lane;
+        if (q < nlinks * kLkChunks) out[q] = tmp[k * 64 + lane];
+    }
 }
 
 // y += a x over n doubles.
@@ -238,15 +390,18 @@ static hipError_t reduce_to_host(double *part, int np, hipStream_t st, double *r
 hipError_t launch_gauge_force(const void *U, void *F, const GeomDev &g, double beta, double scale, int accumulate,
                               hipStream_t st) {
     if (g.vol == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gauge_force, dim3((g.vol * 4 + 255) / 256), dim3(256), 0, st, static_cast<const double2 *>(U),
-                       static_cast<double2 *>(F), g, beta, scale, accumulate);
+    const dim3 grid((g.vol * 4 + 255) / 256), block(256);
+    if (accumulate)
+        hipLaunchKernelGGL(k_gauge_force<true>, grid, block, 0, st, U, F, g, beta, scale);
+    else
+        hipLaunchKernelGGL(k_gauge_force<false>, grid, block, 0, st, U, F, g, beta, scale);
     return hipGetLastError();
 }
 
 hipError_t launch_link_exp(void *U, const void *P, double eps, long nlinks, hipStream_t st) {
     if (nlinks == 0) return hipSuccess;
     hipLaunchKernelGGL(k_link_exp, dim3(static_cast<unsigned>((nlinks + 255) / 256)), dim3(256), 0, st,
-                       static_cast<double2 *>(U), static_cast<const double2 *>(P), eps, nlinks);
+                       U, P, eps, nlinks);
     return hipGetLastError();
 }
 
@@ -359,6 +514,14 @@ static hipError_t total_force(MdRun &r) {
     return daxpy(r.ws + r.L.F, r.ws + r.L.Ff, 1.0, static_cast<long>(r.g.vol) * 4 * 18, r.st);
 }
 
+// P -= c (gauge force + fermion force): the gauge force is added to P by its own kernel.
+static hipError_t kick(MdRun &r, void *P, double c) {
+    HMCCHK(launch_gauge_force(r.U, P, r.g, r.p.beta, -c, 1, r.st));
+    if (!r.phi) return hipSuccess;
+    HMCCHK(fermion_force(r));
+    return daxpy(P, r.ws + r.L.Ff, -c, static_cast<long>(r.g.vol) * 4 * 18, r.st);
+}
+
 hipError_t run_md_leapfrog(void *U, void *P, const void *phi, const GeomDev &g, const grid_md_params &p, void *ws,
                            hipStream_t st, grid_md_stats *stats) {
     const auto t0 = std::chrono::steady_clock::now();
@@ -387,12 +550,10 @@ hipError_t run_md_leapfrog(void *U, void *P, const void *phi, const GeomDev &g, 
         const long nl = static_cast<long>(g.vol) * 4;
         auto gauge_integrate = [&](double tau) -> hipError_t {
             const double h = tau / p.n_inner;
-            HMCCHK(launch_gauge_force(U, r.ws + r.L.F, g, p.beta, 1.0, 0, st));
-            HMCCHK(daxpy(P, r.ws + r.L.F, -0.25 * h, nd, st));
+            HMCCHK(launch_gauge_force(U, P, g, p.beta, -0.25 * h, 1, st));
             for (int j = 0; j < p.n_inner; ++j) {
                 HMCCHK(launch_link_exp(U, P, h, nl, st));
-                HMCCHK(launch_gauge_force(U, r.ws + r.L.F, g, p.beta, 1.0, 0, st));
-                HMCCHK(daxpy(P, r.ws + r.L.F, (j == p.n_inner - 1 ? -0.25 : -0.5) * h, nd, st));
+                HMCCHK(launch_gauge_force(U, P, g, p.beta, (j == p.n_inner - 1 ? -0.25 : -0.5) * h, 1, st));
             }
             return hipSuccess;
         };
@@ -443,21 +604,18 @@ hipError_t run_md_leapfrog(void *U, void *P, const void *phi, const GeomDev &g, 
         // force evaluations
         const long nl = static_cast<long>(g.vol) * 4;
         void *Ud = r.ws + r.L.Ud;
-        HMCCHK(total_force(r));
-        HMCCHK(daxpy(P, r.ws + r.L.F, -0.5 * p.eps / 6.0, nd, st));
+        HMCCHK(kick(r, P, 0.5 * p.eps / 6.0));
         for (int i = 0; i < p.n_steps; ++i) {
             HMCCHK(launch_link_exp(U, P, 0.5 * p.eps, nl, st));
             HMCCHK(total_force(r));
             HMCCHK(hipMemcpyAsync(Ud, U, static_cast<size_t>(nl) * 144, hipMemcpyDeviceToDevice, st));
             HMCCHK(launch_link_exp(Ud, r.ws + r.L.F, -0.5 * p.eps * p.eps / 24.0, nl, st));
             r.U = Ud;   // the force at the displaced links
-            const hipError_t e = total_force(r);
+            const hipError_t e = kick(r, P, 0.5 * 2.0 * p.eps / 3.0);
             r.U = U;
             HMCCHK(e);
-            HMCCHK(daxpy(P, r.ws + r.L.F, -0.5 * 2.0 * p.eps / 3.0, nd, st));
             HMCCHK(launch_link_exp(U, P, 0.5 * p.eps, nl, st));
-            HMCCHK(total_force(r));
-            HMCCHK(daxpy(P, r.ws + r.L.F, -0.5 * (i == p.n_steps - 1 ? 1.0 : 2.0) * p.eps / 6.0, nd, st));
+            HMCCHK(kick(r, P, 0.5 * (i == p.n_steps - 1 ? 1.0 : 2.0) * p.eps / 6.0));
         }
         HMCCHK(hipStreamSynchronize(st));
         stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -468,27 +626,22 @@ hipError_t run_md_leapfrog(void *U, void *P, const void *phi, const GeomDev &g, 
         // merged: 2 n + 1 force evaluations
         constexpr double lam = 0.1931833275037836;
         const long nl = static_cast<long>(g.vol) * 4;
-        HMCCHK(total_force(r));
-        HMCCHK(daxpy(P, r.ws + r.L.F, -0.5 * lam * p.eps, nd, st));
+        HMCCHK(kick(r, P, 0.5 * lam * p.eps));
         for (int i = 0; i < p.n_steps; ++i) {
             HMCCHK(launch_link_exp(U, P, 0.5 * p.eps, nl, st));
-            HMCCHK(total_force(r));
-            HMCCHK(daxpy(P, r.ws + r.L.F, -0.5 * (1.0 - 2.0 * lam) * p.eps, nd, st));
+            HMCCHK(kick(r, P, 0.5 * (1.0 - 2.0 * lam) * p.eps));
             HMCCHK(launch_link_exp(U, P, 0.5 * p.eps, nl, st));
-            HMCCHK(total_force(r));
-            HMCCHK(daxpy(P, r.ws + r.L.F, -0.5 * (i == p.n_steps - 1 ? lam : 2.0 * lam) * p.eps, nd, st));
+            HMCCHK(kick(r, P, 0.5 * (i == p.n_steps - 1 ? lam : 2.0 * lam) * p.eps));
         }
         HMCCHK(hipStreamSynchronize(st));
         stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         return hipSuccess;
     }
     // P -= (eps / 2) F / 2
-    HMCCHK(total_force(r));
-    HMCCHK(daxpy(P, r.ws + r.L.F, -0.25 * p.eps, nd, st));
+    HMCCHK(kick(r, P, 0.25 * p.eps));
     for (int i = 0; i < p.n_steps; ++i) {
         HMCCHK(launch_link_exp(U, P, p.eps, static_cast<long>(g.vol) * 4, st));
-        HMCCHK(total_force(r));
-        HMCCHK(daxpy(P, r.ws + r.L.F, (i == p.n_steps - 1 ? -0.25 : -0.5) * p.eps, nd, st));
+        HMCCHK(kick(r, P, (i == p.n_steps - 1 ? 0.25 : 0.5) * p.eps));
     }
     HMCCHK(hipStreamSynchronize(st));
     stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
