@@ -858,6 +858,212 @@ __device__ __forceinline__ void column_m5inv(chunk_t *lds, Cx<typename SP::C> v[
     for (int j = 0; j < 12; ++j) v[j / 3][j % 3] = x[j / 3][j % 3];
 }
 
+// ------------------------------------------------------------------------------------------
+// Records and links of the plane walk (plane.hip)
+// ------------------------------------------------------------------------------------------
+
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float half_lo(uint32_t w) { return static_cast<float>(__builtin_bit_cast(half2_t, w).x); }
+__device__ __forceinline__ float half_hi(uint32_t w) { return static_cast<float>(__builtin_bit_cast(half2_t, w).y); }
+
+// A spinor record as loaded. FP16 storage keeps the codes: the projection adds two codes (exactly,
+// in FP32) with one v_fma_mix_f32 each and the record's scale multiplies in the FMA that adds the
+// transported half-spinor, so no code is converted or scaled by itself. A projected half-spinor is
+// the true one divided by scale().
+template <class SP>
+struct Rec;
+
+template <>
+struct Rec<SpF32> {
+    using C = float;
+    Cx<float> p[4][3];
+    __device__ __forceinline__ void set(const uint4 *w, float) { SpF32::unpack(w, 1.0f, p); }
+    __device__ __forceinline__ float scale() const { return 1.0f; }
+    template <int MU, int E>
+    __device__ __forceinline__ void proj(Cx<C> h[2][3]) const {
+        project<MU, E>(p, h);
+    }
+    // acc += a psi
+    __device__ __forceinline__ void axpy(Cx<C> acc[4][3], C a) const {
+#pragma unroll
+        for (int j = 0; j < 12; ++j) {
+            Cx<C> &o = acc[j / 3][j % 3];
+            o = {o.r + a * p[j / 3][j % 3].r, o.i + a * p[j / 3][j % 3].i};
+        }
+    }
+};
+
+template <>
+struct Rec<SpF16S> {
+    using C = float;
+    uint32_t w[12];
+    float s;
+    __device__ __forceinline__ void set(const uint4 *v, float sc) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            w[4 * j] = v[j].x;
+            w[4 * j + 1] = v[j].y;
+            w[4 * j + 2] = v[j].z;
+            w[4 * j + 3] = v[j].w;
+        }
+        s = sc;
+    }
+    __device__ __forceinline__ float scale() const { return s; }
+    // code (a, c) + EE code (b, c), or + EE i code (b, c) with IM. The factor 1 is hidden from the
+    // compiler, which would otherwise turn the FMA into two conversions and an addition.
+    template <int EE, bool IM>
+    __device__ __forceinline__ Cx<C> comb(int a, int b, int c) const {
+        float one = 1.0f;
+        __asm__("" : "+s"(one));
+        const uint32_t u = w[a * 3 + c], v = w[b * 3 + c];
+        if (IM)
+            return {__builtin_fmaf(EE > 0 ? -half_hi(v) : half_hi(v), one, half_lo(u)),
+                    __builtin_fmaf(EE > 0 ? half_lo(v) : -half_lo(v), one, half_hi(u))};
+        return {__builtin_fmaf(EE > 0 ? half_lo(v) : -half_lo(v), one, half_lo(u)),
+                __builtin_fmaf(EE > 0 ? half_hi(v) : -half_hi(v), one, half_hi(u))};
+    }
+    template <int MU, int E>
+    __device__ __forceinline__ void proj(Cx<C> h[2][3]) const {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {   // the four cases of project()
+            if (MU == 0) {
+                h[0][c] = comb<-E, true>(0, 3, c);
+                h[1][c] = comb<-E, true>(1, 2, c);
+            } else if (MU == 1) {
+                h[0][c] = comb<-E, false>(0, 3, c);
+                h[1][c] = comb<E, false>(1, 2, c);
+            } else if (MU == 2) {
+                h[0][c] = comb<-E, true>(0, 2, c);
+                h[1][c] = comb<E, true>(1, 3, c);
+            } else {
+                h[0][c] = comb<E, false>(0, 2, c);
+                h[1][c] = comb<E, false>(1, 3, c);
+            }
+        }
+    }
+    __device__ __forceinline__ void axpy(Cx<C> acc[4][3], C a) const {
+        const C as = a * s;
+#pragma unroll
+        for (int j = 0; j < 12; ++j) {
+            Cx<C> &o = acc[j / 3][j % 3];
+            o = {__builtin_fmaf(half_lo(w[j]), as, o.r), __builtin_fmaf(half_hi(w[j]), as, o.i)};
+        }
+    }
+};
+
+// acc += s [chi; E A_MU^dagger chi] (reconstruct_add with the record's scale; s = 1 unless SCALED)
+template <int MU, int E, bool SCALED, typename C>
+__device__ __forceinline__ void reconstruct_fma(Cx<C> acc[4][3], const Cx<C> chi[2][3], C s) {
+    if constexpr (!SCALED) {
+        reconstruct_add<MU, E>(acc, chi);
+    } else {
+        const C e = E > 0 ? s : -s;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const Cx<C> c0 = chi[0][a], c1 = chi[1][a];
+            acc[0][a] = {acc[0][a].r + s * c0.r, acc[0][a].i + s * c0.i};
+            acc[1][a] = {acc[1][a].r + s * c1.r, acc[1][a].i + s * c1.i};
+            if (MU == 0) {
+                acc[2][a] = {acc[2][a].r - e * c1.i, acc[2][a].i + e * c1.r};
+                acc[3][a] = {acc[3][a].r - e * c0.i, acc[3][a].i + e * c0.r};
+            } else if (MU == 1) {
+                acc[2][a] = {acc[2][a].r + e * c1.r, acc[2][a].i + e * c1.i};
+                acc[3][a] = {acc[3][a].r - e * c0.r, acc[3][a].i - e * c0.i};
+            } else if (MU == 2) {
+                acc[2][a] = {acc[2][a].r - e * c0.i, acc[2][a].i + e * c0.r};
+                acc[3][a] = {acc[3][a].r + e * c1.i, acc[3][a].i - e * c1.r};
+            } else {
+                acc[2][a] = {acc[2][a].r + e * c0.r, acc[2][a].i + e * c0.i};
+                acc[3][a] = {acc[3][a].r + e * c1.r, acc[3][a].i + e * c1.i};
+            }
+        }
+    }
+}
+
+// acc (spins 2 hf, 2 hf + 1) += f * that half of a record at rec (LDS or global), scale *sc
+template <class SP>
+__device__ __forceinline__ void half_axpy(Cx<float> acc[4][3], const void *rec, const float *sc, int hf, float f) {
+    if constexpr (SP::kScaled) {
+        const uint2 *q = static_cast<const uint2 *>(rec) + hf * 3;
+        const float fs = f * *sc;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const uint2 v = q[k];
+            Cx<float> &a = acc[2 * hf + (2 * k) / 3][(2 * k) % 3], &b = acc[2 * hf + (2 * k + 1) / 3][(2 * k + 1) % 3];
+            a = {__builtin_fmaf(half_lo(v.x), fs, a.r), __builtin_fmaf(half_hi(v.x), fs, a.i)};
+            b = {__builtin_fmaf(half_lo(v.y), fs, b.r), __builtin_fmaf(half_hi(v.y), fs, b.i)};
+        }
+    } else {
+        Cx<float> q[2][3];
+        SP::load_half(rec, nullptr, 0, hf, q);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            Cx<float> &o = acc[2 * hf + j / 3][j % 3];
+            o = {o.r + f * q[j / 3][j % 3].r, o.i + f * q[j / 3][j % 3].i};
+        }
+    }
+}
+
+// A link as the A operand of v_mfma_f32_4x4x1 (16 blocks): the four lanes of a block are four s of
+// one 4D site, lane i holds row i of the 3x3 matrix V (V = U or U^dagger; lane 3 repeats row 2, its
+// row of the result is not read), lane j's vector is column j of the B operand, and the block's
+// product leaves lane j with V times its own vector, row a in the a-th of four result registers.
+struct MatRow {
+    float r[3], i[3];
+};
+typedef float mfma_acc_t __attribute__((ext_vector_type(4)));
+
+template <bool ADJ>
+__device__ __forceinline__ void mat_row(const float2 *link, MatRow &m) {
+    const int i = min(static_cast<int>(threadIdx.x & 3), 2);
+    const float2 *q = link + (ADJ ? i : 3 * i);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float2 v = q[ADJ ? 3 * k : k];
+        m.r[k] = v.x;
+        m.i[k] = v.y;   // of U; su3_mfma conjugates for the adjoint
+    }
+}
+
+// chi_k = V h_k: real and imaginary parts of the complex product, K = 1 per instruction, each an
+// FP32 multiply-add chain as su3_mul's; all lanes of the wavefront take part.
+template <bool ADJ>
+__device__ __forceinline__ void su3_mfma(const MatRow &m, const Cx<float> h[2][3], Cx<float> chi[2][3]) {
+    const mfma_acc_t z = {0.f, 0.f, 0.f, 0.f};
+    mfma_acc_t cr[2], ci[2];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            cr[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(m.r[k], h[s][k].r, k ? cr[s] : z, 0, 0, 0);
+            ci[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(m.r[k], h[s][k].i, k ? ci[s] : z, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            cr[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(ADJ ? m.i[k] : -m.i[k], h[s][k].i, cr[s], 0, 0, 0);
+            ci[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(ADJ ? -m.i[k] : m.i[k], h[s][k].r, ci[s], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) chi[s][a] = {cr[s][a], ci[s][a]};
+}
+
+// acc += (1 + E gamma_MU) V psi, one direction at a time as hop_term
+template <int MU, int E, bool ADJ, class SP>
+__device__ __forceinline__ void hop_mfma(Cx<float> acc[4][3], const Rec<SP> &r, const MatRow &m) {
+    Cx<float> h[2][3], chi[2][3];
+    r.template proj<MU, E>(h);
+    su3_mfma<ADJ>(m, h, chi);
+    reconstruct_fma<MU, E, SP::kScaled>(acc, chi, r.scale());
+    pin(acc);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Hardware dispatches workgroup b to XCD b % 8. Renumber so that each XCD receives one
 // contiguous range of logical blocks: neighbouring lattice sites then share an L2.
 __device__ __forceinline__ int xcd_block(int b, int nblocks) {

@@ -1218,8 +1218,9 @@ static hipError_t launch_walk_cb(const DhopArgs &a) {
     return hipGetLastError();
 }
 
-// Schedules: column walk for FP16 storage and 5D FP32 fields (full lattice, or checkerboard
-// fields in the even-odd form), direction-parallel otherwise (measured faster there). The
+// Schedules: the plane walk (plane.hip) for the plain operators on 5D FP32 and FP16-storage fields
+// its tiles divide, column walks for the other FP16-storage and 5D FP32 fields (full lattice, or
+// checkerboard fields in the even-odd form), direction-parallel otherwise (measured faster there). The
 // full-lattice walk also takes the custom form with a separate y and beta = -1/2 (the Moebius
 // operator's hopping pass).
 static bool walk_prec(const DhopArgs &a) { return a.prec == GRID_F16S || (a.prec == GRID_F32 && a.g.Ls > 1); }
@@ -1234,13 +1235,19 @@ static hipError_t launch_sched(const DhopArgs &a) {
     if ((a.kind == kMobHop || a.kind == kMobDiag || a.kind == kHopInv || a.kind == kMobHopInv) && !use_walk_cb(a))
         return hipErrorInvalidValue;
     if (tile_applies(a)) return launch_tile(a);
-    if (use_walk(a)) return launch_walk<SP, LK>(a);
-    if (use_walk_cb(a)) return launch_walk_cb<SP, LK>(a);
-    return launch_dir<SP, LK>(a);
+    if (plane_applies(a)) return launch_plane(a);
+    // the walks serve FP32 and FP16 storage, the direction-parallel kernel FP64 and FP32 (walk_prec)
+    if constexpr (sizeof(typename SP::C) == 4) {
+        if (use_walk(a)) return launch_walk<SP, LK>(a);
+        if (use_walk_cb(a)) return launch_walk_cb<SP, LK>(a);
+    }
+    if constexpr (!SP::kScaled) return launch_dir<SP, LK>(a);
+    return hipErrorInvalidValue;
 }
 
 long dhop_blocks(const DhopArgs &a) {
     if (tile_applies(a)) return tile_blocks(a);
+    if (plane_applies(a)) return plane_blocks(a);
     if (use_walk(a)) {
         const long nbc = (static_cast<long>(a.g.L[0]) * a.g.L[1] * a.g.L[2] * a.g.Ls + 255) / 256;
         return nbc * (a.g.L[3] / choose_steps(a.g));

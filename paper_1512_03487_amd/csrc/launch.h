@@ -82,6 +82,10 @@ bool walk_mobius_applies(const DhopArgs &a);
 bool tile_applies(const DhopArgs &a);
 long tile_blocks(const DhopArgs &a);
 hipError_t launch_tile(const DhopArgs &a);
+// Plane walk (plane.hip): full-lattice 5D FP32 / FP16-storage fields, the plain operators H and M.
+bool plane_applies(const DhopArgs &a);
+long plane_blocks(const DhopArgs &a);
+hipError_t launch_plane(const DhopArgs &a);
 // Number of blocks (= partial sums written by a fused epilogue) launch_dhop uses for `a`.
 long dhop_blocks(const DhopArgs &a);
 // Upper bound of dhop_blocks over all schedules for a field of n5 sites and time extent Lt.

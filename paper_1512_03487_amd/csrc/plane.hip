@@ -1,0 +1,412 @@
+// Plane walk of the hopping operator on 5D fields (FP32 and FP16 storage, gfx950).
+//
+// A block owns a TX x TY tile of (x, y) columns at one z with all their s (one thread per 5D
+// column, s fastest, TX TY Ls <= 256 threads) and walks T time slices. Per slice its own records,
+// the tile's four faces and every link the slice's hops use go through LDS, so the four x and y
+// hops, the fifth-dimension hop and the diagonal read LDS; the two z neighbours are read straight
+// from memory; psi(x, t + 1) is the next slice's own record and the backward t-hop is carried in
+// registers, as in the column walks.
+//
+// Why. A CU keeps about 56 vector-L1 misses in flight (requests x latency / time, the same in every
+// schedule measured, a plain copy included), so the time goes with the number of 128-byte lines a
+// site requests times their latency: 6.9 lines in the same-step column walk, which fetches a record
+// for each of its uses, and 4.0 here (FP32, 24^4 x 12; FP16 storage 3.9 and 2.4). Same-step walk
+// against this kernel: 24^4 x 12 FP32 376 -> 335 us, FP16 storage 218 -> 193 us; 16^4 x 16 105 -> 80 us
+// and 59 -> 48 us. What remains is the latency of the lines that miss the L2: at this size a step of
+// the blocks an XCD holds moves as much as its L2, so the z neighbours are mostly fetched again.
+// Tried and not kept: the next slice's loads in registers during the hops (345 against 325 us in
+// FP32, registers spill), streaming stores (580 us), tiles ordered over 2 x 2 x 2 XCD domains (+- 2 %).
+//
+// The SU(3) products run on the matrix cores: the four lanes of a v_mfma_f32_4x4x1 block are four s
+// of one 4D site and share its link (su3_mfma), which needs Ls to be a multiple of four. A lane then
+// holds one row of a link, 24 bytes from LDS in place of 72, and the kernel fits more wavefronts.
+#include <type_traits>
+
+#include "device.h"
+#include "launch.h"
+
+namespace gridmi {
+
+struct PlaneDev {
+    int tx, ty;          // tile extents (powers of two)
+    int ltx, lty;        // their logarithms
+    int T;               // time slices per block
+};
+
+// Halo columns of a tile: the -x, +x faces (ty each), then -y, +y (tx each).
+// Link slots of a slice: the tile's own columns' four links (4 c + mu), U_z(x - z) of every column,
+// U_x(x - x) at the -x face and U_y(x - y) at the -y face.
+
+static size_t plane_lds_bytes(const PlaneDev &d, int Ls, int chunks, bool scaled) {
+    const size_t nc = static_cast<size_t>(d.tx) * d.ty, nh = 2 * (d.tx + d.ty);
+    const size_t slots = 5 * nc + d.tx + d.ty;
+    return (nc + nh) * Ls * (chunks * 16 + (scaled ? 4 : 0)) + ((slots * 72 + 15) & ~size_t(15));
+}
+
+template <class SP, class LK, bool DAG, int KIND, int FUSE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const float *__restrict__ psi_scale, void *out,
+             float *out_scale, GeomDev g, PlaneDev pd, double diag, double mf, FuseDev fz) {
+    static_assert(KIND == GRID_HOP || KIND == GRID_DWF, "plain operators only");
+    constexpr bool SC = SP::kScaled;
+    constexpr int CH = SP::kChunks;
+    constexpr int KH = CH;   // halo chunks per thread (no more halo columns than own ones)
+    extern __shared__ chunk_t plane_lds[];
+    const int Ls = g.Ls, TX = pd.tx, TY = pd.ty, NC = TX * TY, NH = 2 * (TX + TY), NT = NC * Ls;
+    const int NS = 5 * NC + TX + TY;
+    chunk_t *rec = plane_lds;                                             // own records, then the halo's
+    float2 *lks = reinterpret_cast<float2 *>(rec + (NC + NH) * Ls * CH);  // links, FP32, nine to a slot
+    float *rsc = reinterpret_cast<float *>(rec + (NC + NH) * Ls * CH + (NS * 72 + 15) / 16);   // scales
+    const int tid = threadIdx.x;
+    const bool act = tid < NT;
+    const int td = act ? tid : 0;   // idle lanes take part in the matrix products
+    const int Lx = g.L[0], Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
+    const int ntx = Lx >> pd.ltx, nty = Ly >> pd.lty, ntile = ntx * nty * Lz;
+    const int lb = xcd_block(blockIdx.x, gridDim.x);
+    const int seg = lb / ntile, tile = lb - seg * ntile;
+    const int x0 = (tile % ntx) << pd.ltx, y0 = ((tile / ntx) % nty) << pd.lty, z = tile / (ntx * nty);
+    const int c = td / Ls, s = td - c * Ls, cx = c & (TX - 1), cy = c >> pd.ltx;
+    const int V3 = Lx * Ly * Lz, nq = V3 * Ls, plane = Lx * Ly;
+    const int col = z * plane + (y0 + cy) * Lx + x0 + cx;
+    const int zpo = (z == Lz - 1 ? 1 - Lz : 1) * plane * Ls, zmo = (z == 0 ? Lz - 1 : -1) * plane * Ls;
+    const int q = col * Ls + s;
+    const int t0 = seg * pd.T;
+    constexpr int EF = DAG ? +1 : -1;
+    // out = beta (H psi + (diag psi - S psi) / beta), beta = 1 for H and -1/2 for M
+    const float bt = KIND == GRID_HOP ? 1.0f : -0.5f;
+    const float dgb = static_cast<float>(diag) / bt;
+    const float fpb = -((s == Ls - 1) ? static_cast<float>(-mf) : 1.0f) / bt;
+    const float fmb = -((s == 0) ? static_cast<float>(-mf) : 1.0f) / bt;
+
+    // Byte offsets, within a time slice, of this thread's loads: own chunks j NT + tid, halo chunks
+    // j NT + tid, halo scales, one link.
+    unsigned og[CH], hg[KH], hso = 0, ug;
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+        const int cc = j * NT + td, row = cc / (TX * Ls * CH), off = cc - row * (TX * Ls * CH);
+        og[j] = (((z * Ly + y0 + row) * Lx + x0) * Ls * CH + off) * 16u;
+    }
+    auto halo_col = [&](int hc) -> int {   // first record of a halo column
+        int hx, hy;
+        if (hc < 2 * TY) {
+            hx = hc < TY ? (x0 == 0 ? Lx - 1 : x0 - 1) : (x0 + TX == Lx ? 0 : x0 + TX);
+            hy = y0 + (hc & (TY - 1));
+        } else {
+            hy = hc < 2 * TY + TX ? (y0 == 0 ? Ly - 1 : y0 - 1) : (y0 + TY == Ly ? 0 : y0 + TY);
+            hx = x0 + ((hc - 2 * TY) & (TX - 1));
+        }
+        return ((z * Ly + hy) * Lx + hx) * Ls;
+    };
+    const int nhc = NH * Ls * CH;
+#pragma unroll
+    for (int j = 0; j < KH; ++j) {
+        const int h = j * NT + td, hc = h / (Ls * CH), off = h - hc * (Ls * CH);
+        hg[j] = h < nhc ? (halo_col(hc) * CH + off) * 16u : og[0];
+    }
+    if constexpr (SC) {
+        const int hc = td / Ls;
+        hso = td < NH * Ls ? (halo_col(hc) + (td - hc * Ls)) * 4u : q * 4u;
+    }
+    {
+        int lx = x0, ly = y0, lz = z, mu = 0;
+        const int cc = td < 4 * NC ? td >> 2 : td - 4 * NC;
+        if (td < 5 * NC) {
+            mu = td < 4 * NC ? td & 3 : 2;
+            lx = x0 + (cc & (TX - 1));
+            ly = y0 + (cc >> pd.ltx);
+            if (td >= 4 * NC) lz = z == 0 ? Lz - 1 : z - 1;
+        } else if (td < 5 * NC + TY) {
+            lx = x0 == 0 ? Lx - 1 : x0 - 1;
+            ly = y0 + td - 5 * NC;
+        } else if (td < NS) {
+            mu = 1;
+            ly = y0 == 0 ? Ly - 1 : y0 - 1;
+            lx = x0 + td - 5 * NC - TY;
+        }
+        ug = ((lz * Ly + ly) * Lx + lx) * 4 + mu;
+    }
+    // LDS slots of the neighbours: records, and the backward hops' links
+    const int nxp = cx < TX - 1 ? td + Ls : (NC + TY + cy) * Ls + s;
+    const int nxm = cx > 0 ? td - Ls : (NC + cy) * Ls + s;
+    const int nyp = cy < TY - 1 ? td + TX * Ls : (NC + 2 * TY + TX + cx) * Ls + s;
+    const int nym = cy > 0 ? td - TX * Ls : (NC + 2 * TY + cx) * Ls + s;
+    const int lxm = cx > 0 ? (c - 1) * 4 : 5 * NC + cy;
+    const int lym = cy > 0 ? (c - TX) * 4 + 1 : 5 * NC + TY + cx;
+    const int rsp = s == Ls - 1 ? td - (Ls - 1) : td + 1, rsm = s == 0 ? td + Ls - 1 : td - 1;
+
+    // The slice index and the offsets are hidden from the loop optimiser at each use (empty asm, no
+    // instruction): it would otherwise keep a 64-bit address per load across the loop instead of
+    // forming the scalar-base, 32-bit-offset loads.
+    auto slice = [](int tt) {
+        __asm__("" : "+s"(tt));
+        return tt;
+    };
+    auto load16 = [](const char *b, unsigned off) {
+        __asm__("" : "+v"(off));
+        return *reinterpret_cast<const chunk_t *>(b + off);
+    };
+    Cx<float> A[4][3], hb[2][3];
+    float hs;
+    Rec<SP> p;
+    MatRow u, utf, utb;
+    // record q + dq of a slice, straight from memory
+    auto direct = [&](int tt, int dq, Rec<SP> &r) {
+        const char *b = static_cast<const char *>(psi) + static_cast<size_t>(slice(tt)) * nq * (CH * 16);
+        unsigned o = static_cast<unsigned>(q + dq) * (CH * 16u);
+        __asm__("" : "+v"(o));
+        uint4 w[CH];
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const chunk_t v = *reinterpret_cast<const chunk_t *>(b + o + j * 16);
+            w[j] = make_uint4(v.x, v.y, v.z, v.w);
+        }
+        r.set(w, SC ? (psi_scale + static_cast<size_t>(slice(tt)) * nq)[static_cast<unsigned>(q + dq)] : 1.0f);
+    };
+    auto staged = [&](int r) {
+        uint4 w[CH];
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            const chunk_t v = rec[r * CH + k];
+            w[k] = make_uint4(v.x, v.y, v.z, v.w);
+        }
+        p.set(w, SC ? rsc[r] : 1.0f);
+    };
+    [[maybe_unused]] double n2 = 0.0;   // fused epilogue: this thread's |out|^2
+    // out(tt) from the finished sum
+    auto finish = [&](int tt) {
+#pragma unroll
+        for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {bt * A[j / 3][j % 3].r, bt * A[j / 3][j % 3].i};
+        const size_t o = static_cast<size_t>(tt) * nq + q;
+        if constexpr (FUSE == kFuseAxpy) {
+            // r - alpha op psi; r may alias out: the thread reads its record before storing it
+            Cx<float> rv[4][3];
+            SP::load(fz.r, fz.r_scale, o, rv);
+            const float al = static_cast<float>(fz.scal[fz.num] / fz.scal[fz.den]);
+#pragma unroll
+            for (int j = 0; j < 12; ++j) {
+                const Cx<float> a = A[j / 3][j % 3], b = rv[j / 3][j % 3];
+                A[j / 3][j % 3] = {b.r - al * a.r, b.i - al * a.i};
+            }
+        }
+        if (act) {
+            if constexpr (FUSE == kFuseNone)
+                SP::store(out, out_scale, o, A);
+            else
+                n2 += SP::store_n2(out, out_scale, o, A);
+        }
+    };
+    {
+        // the backward t-hop of slice t0: U_t(x, t0 - 1) and h(psi(x, t0 - 1))
+        const int tm = t0 == 0 ? Lt - 1 : t0 - 1;
+        direct(tm, 0, p);
+        p.template proj<3, -EF>(hb);
+        hs = p.scale();
+        Cx<float> w[3][3];
+        LK::load(U, (static_cast<size_t>(tm) * V3 + col) * 4 + 3, w);
+        const int i = min(tid & 3, 2);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const Cx<float> e = i == 0 ? w[k][0] : i == 1 ? w[k][1] : w[k][2];
+            utb.r[k] = e.r;
+            utb.i[k] = e.i;
+        }
+        utf = utb;
+    }
+#pragma unroll 1
+    for (int k = 0; k < pd.T; ++k) {
+        const int tt = t0 + k;
+        {
+            const char *b = static_cast<const char *>(psi) + static_cast<size_t>(slice(tt)) * nq * (CH * 16);
+            const char *lk = static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes);
+            chunk_t wo[CH], wh[KH];
+            Cx<float> wu[3][3];
+            float so = 1.f, sh = 1.f;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) wo[j] = load16(b, og[j]);
+#pragma unroll
+            for (int j = 0; j < KH; ++j) wh[j] = load16(b, hg[j]);
+            LK::load(lk, ug, wu);
+            if constexpr (SC) {
+                const char *sb = reinterpret_cast<const char *>(psi_scale) + static_cast<size_t>(slice(tt)) * nq * 4;
+                so = *reinterpret_cast<const float *>(sb + static_cast<unsigned>(q) * 4u);
+                sh = *reinterpret_cast<const float *>(sb + hso);
+            }
+            if (act) {
+#pragma unroll
+                for (int j = 0; j < CH; ++j) rec[j * NT + td] = wo[j];
+#pragma unroll
+                for (int j = 0; j < KH; ++j)
+                    if (j * NT + td < nhc) rec[(CH + j) * NT + td] = wh[j];
+                if (td < NS) {
+                    float2 *d = lks + td * 9;
+#pragma unroll
+                    for (int e = 0; e < 9; ++e) d[e] = make_float2(wu[e / 3][e % 3].r, wu[e / 3][e % 3].i);
+                }
+                if constexpr (SC) {
+                    rsc[td] = so;
+                    if (td < NH * Ls) rsc[NT + td] = sh;
+                }
+            }
+        }
+        __syncthreads();
+        staged(td);
+        if (k > 0) {
+            hop_mfma<3, EF, false, SP>(A, p, utf);   // the forward t-hop finishes out(tt - 1)
+            finish(tt - 1);
+        }
+        Cx<float> chi[2][3];
+        su3_mfma<true>(utb, hb, chi);
+#pragma unroll
+        for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {0.f, 0.f};
+        reconstruct_fma<3, -EF, SC>(A, chi, hs);
+        p.template proj<3, -EF>(hb);
+        hs = p.scale();
+        if constexpr (KIND != GRID_HOP) p.axpy(A, dgb);
+        Rec<SP> pz;
+        direct(tt, zpo, pz);   // in flight during the x hops
+        if constexpr (KIND == GRID_DWF) {
+            // - P_- psi~_{s+1} - P_+ psi~_{s-1} (M; P_+ and P_- exchanged for M^dagger)
+            constexpr int hup = DAG ? 0 : 1;
+            half_axpy<SP>(A, rec + rsp * CH, rsc + rsp, hup, fpb);
+            half_axpy<SP>(A, rec + rsm * CH, rsc + rsm, 1 - hup, fmb);
+        }
+        staged(nxp);
+        mat_row<false>(lks + (c * 4) * 9, u);
+        hop_mfma<0, EF, false, SP>(A, p, u);
+        staged(nxm);
+        mat_row<true>(lks + lxm * 9, u);
+        hop_mfma<0, -EF, true, SP>(A, p, u);
+        mat_row<false>(lks + (c * 4 + 2) * 9, u);
+        hop_mfma<2, EF, false, SP>(A, pz, u);
+        direct(tt, zmo, pz);   // in flight during the y hops
+        staged(nyp);
+        mat_row<false>(lks + (c * 4 + 1) * 9, u);
+        hop_mfma<1, EF, false, SP>(A, p, u);
+        staged(nym);
+        mat_row<true>(lks + lym * 9, u);
+        hop_mfma<1, -EF, true, SP>(A, p, u);
+        mat_row<true>(lks + (4 * NC + c) * 9, u);
+        hop_mfma<2, -EF, true, SP>(A, pz, u);
+        // U_t(x, tt): the forward t-hop of out(tt) and the backward one of out(tt + 1)
+        mat_row<false>(lks + (c * 4 + 3) * 9, utf);
+        mat_row<true>(lks + (c * 4 + 3) * 9, utb);
+        __syncthreads();   // the next slice overwrites what was read here
+    }
+    {
+        const int tl = t0 + pd.T - 1;
+        direct(tl == Lt - 1 ? 0 : tl + 1, 0, p);
+        hop_mfma<3, EF, false, SP>(A, p, utf);
+        finish(tl);
+    }
+    if constexpr (FUSE != kFuseNone) {
+        n2 = wave_sum64(n2);
+        __shared__ double fred[4];
+        if ((tid & 63) == 0) fred[tid >> 6] = n2;
+        __syncthreads();
+        if (tid == 0) {
+            double v = 0.0;
+            for (int w = 0; w < static_cast<int>(blockDim.x >> 6); ++w) v += fred[w];
+            fz.part[blockIdx.x] = v;
+        }
+    }
+}
+
+// Tile: 4 x 4 columns for Ls = 12 and 16, 8 x 4 (or 4 x 8) for Ls = 8, so that a block has 192 or
+// 256 threads, the halo no more columns than the tile and a slice's links no more than the threads.
+static bool plane_tile(const GeomDev &g, PlaneDev *d) {
+    if (g.Ls == 12 || g.Ls == 16) {
+        d->ltx = d->lty = 2;
+    } else if (g.Ls == 8) {
+        d->ltx = g.L[0] % 8 == 0 ? 3 : 2;
+        d->lty = 5 - d->ltx;
+    } else {
+        return false;
+    }
+    d->tx = 1 << d->ltx;
+    d->ty = 1 << d->lty;
+    return g.L[0] % d->tx == 0 && g.L[1] % d->ty == 0;
+}
+
+// Slices per block: the divisor T <= 8 of Lt with the least of (T + 1.5) x the sum over rounds of
+// (1.5 + blocks of the round on a CU). A walk's start and end cost about one and a half slices, and a
+// slice of one block takes, with m blocks on its CU, about as long as 1.5 + m (latency, then
+// throughput). Measured, T = 2 / 3 / 4 / 6 / 8 / 12 / 24: 24^4 x 12 FP16 storage 226 / 205 / 198 / 193 / 198 /
+// 197 / 201 us, FP32 371 / 339 / 339 / 336 / 348 / 340 / 371 us, 24^4 x 8 FP32 248 / 229 / 227 / 221 / 236 / 237 /
+// 239 us; T = 2 / 4 / 8 / 16: 16^4 x 16 FP32 93 / 85 / 80 / 89 us, 16^4 x 12 FP16 storage 45 / 39 / 45 / 58 us;
+// T = 1 / 2 / 3 / 4 / 6: 12^4 x 16 FP32 38 / 34 / 29 / 34 / 34 us.
+static PlaneDev plane_dev(const GeomDev &g, int prec) {
+    PlaneDev d{};
+    if (!plane_tile(g, &d)) return d;
+    const int waves = (d.tx * d.ty * g.Ls + 63) / 64;
+    const bool scaled = prec == GRID_F16S;
+    const long granules = (static_cast<long>(plane_lds_bytes(d, g.Ls, scaled ? 3 : 6, scaled)) + 1279) / 1280;
+    const long by_lds = 128 / granules;   // 160 KB in granules of 1280 bytes
+    const long per_cu = by_lds < 12 / waves ? by_lds : 12 / waves;   // three wavefronts per SIMD
+    const long tiles = static_cast<long>(g.vol / g.L[3]) / (d.tx * d.ty);
+    double best = 0.0;
+    for (int T = 1; T <= 8 && T <= g.L[3]; ++T) {
+        if (g.L[3] % T) continue;
+        const long m = (tiles * (g.L[3] / T) + 255) / 256, rem = m % per_cu;
+        const double cost = (T + 1.5) * ((m / per_cu) * (1.5 + per_cu) + (rem ? 1.5 + rem : 0.0));
+        if (d.T == 0 || cost < best) {
+            best = cost;
+            d.T = T;
+        }
+    }
+    return d;
+}
+
+// Below these sizes the column walk is faster (its wavefronts wait for nothing but their own loads):
+// FP32 8^3 x 32 x 8 (131072 sites) 14.8 against 16.1 us here, 12^3 x 8 x 16 (221184) 25.7 against 21.7;
+// FP16 storage 12^4 x 12 (248832) 17.9 against 20.6 us, 12^4 x 16 (331776) 23.2 against 21.8.
+bool plane_applies(const DhopArgs &a) {
+    PlaneDev d;
+    const int least = a.prec == GRID_F16S ? 300000 : 160000;
+    return !a.custom && (a.kind == GRID_HOP || a.kind == GRID_DWF) && (a.prec == GRID_F32 || a.prec == GRID_F16S) &&
+           a.g.n5 >= least && plane_tile(a.g, &d);
+}
+
+long plane_blocks(const DhopArgs &a) {
+    const PlaneDev d = plane_dev(a.g, a.prec);
+    return static_cast<long>(a.g.vol / a.g.L[3]) / (d.tx * d.ty) * (a.g.L[3] / d.T);
+}
+
+template <class SP, class LK>
+static hipError_t launch_plane_t(const DhopArgs &a) {
+    const PlaneDev d = plane_dev(a.g, a.prec);
+    const dim3 grid(static_cast<unsigned>(plane_blocks(a))), block((d.tx * d.ty * a.g.Ls + 63) / 64 * 64);
+    const size_t lds = plane_lds_bytes(d, a.g.Ls, SP::kChunks, SP::kScaled);
+    hipStream_t st = a.stream;
+#define GRIDMI_LAUNCH(DAG, KIND, FUSE)                                                                          \
+    hipLaunchKernelGGL((k_dhop_plane<SP, LK, DAG, KIND, FUSE>), grid, block, lds, st, a.U, a.psi, a.psi_scale, a.out, \
+                       a.out_scale, a.g, d, a.diag, a.mf, a.fz)
+    if (a.fuse != kFuseNone) {
+        switch (a.kind * 4 + a.fuse * 2 + (a.dag ? 1 : 0)) {
+            case GRID_DWF * 4 + kFuseNorm * 2 + 0: GRIDMI_LAUNCH(false, GRID_DWF, kFuseNorm); break;
+            case GRID_DWF * 4 + kFuseAxpy * 2 + 1: GRIDMI_LAUNCH(true, GRID_DWF, kFuseAxpy); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
+    switch (a.kind * 2 + (a.dag ? 1 : 0)) {
+        case GRID_HOP * 2 + 0: GRIDMI_LAUNCH(false, GRID_HOP, kFuseNone); break;
+        case GRID_HOP * 2 + 1: GRIDMI_LAUNCH(true, GRID_HOP, kFuseNone); break;
+        case GRID_DWF * 2 + 0: GRIDMI_LAUNCH(false, GRID_DWF, kFuseNone); break;
+        case GRID_DWF * 2 + 1: GRIDMI_LAUNCH(true, GRID_DWF, kFuseNone); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef GRIDMI_LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t launch_plane(const DhopArgs &a) {
+    switch (a.prec * 2 + a.link_fmt) {
+        case GRID_F32 * 2 + GRID_L18: return launch_plane_t<SpF32, LkF32<3>>(a);
+        case GRID_F32 * 2 + GRID_L12: return launch_plane_t<SpF32, LkF32<2>>(a);
+        case GRID_F16S * 2 + GRID_L18: return launch_plane_t<SpF16S, LkF16<3>>(a);
+        case GRID_F16S * 2 + GRID_L12: return launch_plane_t<SpF16S, LkF16<2>>(a);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace gridmi
