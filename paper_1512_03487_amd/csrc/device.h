@@ -891,6 +891,16 @@ struct Rec<SpF32> {
             o = {o.r + a * p[j / 3][j % 3].r, o.i + a * p[j / 3][j % 3].i};
         }
     }
+    // acc (spins 2 HF, 2 HF + 1) += f psi of the lane that DPP control CTRL names
+    template <int CTRL, int HF>
+    __device__ __forceinline__ void shift_axpy(Cx<C> acc[4][3], C f) const {
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            Cx<C> &o = acc[2 * HF + j / 3][j % 3];
+            const Cx<C> v = p[2 * HF + j / 3][j % 3];
+            o = {o.r + f * dpp_f32<CTRL>(v.r), o.i + f * dpp_f32<CTRL>(v.i)};
+        }
+    }
 };
 
 template <>
@@ -949,7 +959,28 @@ struct Rec<SpF16S> {
             o = {__builtin_fmaf(half_lo(w[j]), as, o.r), __builtin_fmaf(half_hi(w[j]), as, o.i)};
         }
     }
+    template <int CTRL, int HF>
+    __device__ __forceinline__ void shift_axpy(Cx<C> acc[4][3], C f) const {
+        const C fs = f * dpp_f32<CTRL>(s);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            Cx<C> &o = acc[2 * HF + j / 3][j % 3];
+            const uint32_t v = __builtin_amdgcn_mov_dpp(static_cast<int>(w[6 * HF + j]), CTRL, 0xf, 0xf, false);
+            o = {__builtin_fmaf(half_lo(v), fs, o.r), __builtin_fmaf(half_hi(v), fs, o.i)};
+        }
+    }
 };
+
+// Fifth-dimension columns of 16: a column is one DPP row, rotated by one lane either way.
+constexpr int kDppNext = 0x12F, kDppPrev = 0x121;   // the lane of s + 1, of s - 1 (row_ror 15 and 1)
+
+// acc += f S psi (S^dagger with DAG), S psi = P_- psi~_{s+1} + P_+ psi~_{s-1}; fp and fm are f times
+// the wall factors of s + 1 and s - 1.
+template <bool DAG, class R>
+__device__ __forceinline__ void column_shift_axpy(const R &r, Cx<float> acc[4][3], float fp, float fm) {
+    r.template shift_axpy<kDppNext, DAG ? 0 : 1>(acc, fp);
+    r.template shift_axpy<kDppPrev, DAG ? 1 : 0>(acc, fm);
+}
 
 // acc += s [chi; E A_MU^dagger chi] (reconstruct_add with the record's scale; s = 1 unless SCALED)
 template <int MU, int E, bool SCALED, typename C>

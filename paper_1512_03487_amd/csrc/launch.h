@@ -82,7 +82,7 @@ bool walk_mobius_applies(const DhopArgs &a);
 bool tile_applies(const DhopArgs &a);
 long tile_blocks(const DhopArgs &a);
 hipError_t launch_tile(const DhopArgs &a);
-// Plane walk (plane.hip): full-lattice 5D FP32 / FP16-storage fields, the plain operators H and M.
+// Plane walk (plane.hip): full-lattice 5D FP32 / FP16-storage fields, H and the domain-wall and Moebius M.
 bool plane_applies(const DhopArgs &a);
 long plane_blocks(const DhopArgs &a);
 hipError_t launch_plane(const DhopArgs &a);

@@ -14,6 +14,9 @@
 // against this kernel: 24^4 x 12 FP32 376 -> 335 us, FP16 storage 218 -> 193 us; 16^4 x 16 105 -> 80 us
 // and 59 -> 48 us. What remains is the latency of the lines that miss the L2: at this size a step of
 // the blocks an XCD holds moves as much as its L2, so the z neighbours are mostly fetched again.
+// Moebius (16^4 x 16, column walk against this kernel): FP32 M 107 -> 81 us and M^dagger 99 -> 84, FP16
+// storage 90 -> 60 and 68 -> 56 us: B is applied once to each of the four records a site loads instead
+// of to all eight it hops.
 // Tried and not kept: the next slice's loads in registers during the hops (345 against 325 us in
 // FP32, registers spill), streaming stores (580 us), tiles ordered over 2 x 2 x 2 XCD domains (+- 2 %).
 //
@@ -43,13 +46,24 @@ static size_t plane_lds_bytes(const PlaneDev &d, int Ls, int chunks, bool scaled
     return (nc + nh) * Ls * (chunks * 16 + (scaled ? 4 : 0)) + ((slots * 72 + 15) & ~size_t(15));
 }
 
+// Registers: three wavefronts per SIMD, two for the Moebius operators with FP32 records in LDS, of
+// which two blocks fit a CU in any case (their 17 to 31 spilled registers at three).
 template <class SP, class LK, bool DAG, int KIND, int FUSE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(KIND == GRID_MOBIUS && !(SP::kScaled && DAG) ? 2 : 3)))
 k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const float *__restrict__ psi_scale, void *out,
-             float *out_scale, GeomDev g, PlaneDev pd, double diag, double mf, FuseDev fz) {
-    static_assert(KIND == GRID_HOP || KIND == GRID_DWF, "plain operators only");
-    constexpr bool SC = SP::kScaled;
-    constexpr int CH = SP::kChunks;
+             float *out_scale, GeomDev g, PlaneDev pd, double diag, double mf, double cs, double b5, double c5,
+             FuseDev fz) {
+    static_assert(KIND == GRID_HOP || KIND == GRID_DWF || KIND == GRID_MOBIUS, "plain operators only");
+    // Moebius (Ls = 16). M psi hops chi = B psi, B = b5 + c5 S: every record becomes chi where it is
+    // loaded (a column is a DPP row), LDS holds chi in FP32, and out adds diag psi - cs S psi (diag =
+    // 1 + (4 - M5) b5, cs = 1 - (4 - M5) c5). M^dagger psi hops psi, forms w = (4 - M5) psi - H^dagger
+    // psi / 2 (diag = 4 - M5) and ends with b5 w + psi + S^dagger (c5 w - psi).
+    constexpr bool MOBF = KIND == GRID_MOBIUS && !DAG;
+    constexpr bool MOBA = KIND == GRID_MOBIUS && DAG;
+    using SL = std::conditional_t<MOBF, SpF32, SP>;   // records in LDS
+    constexpr bool SC = SL::kScaled;
+    constexpr int CH = SL::kChunks;
     constexpr int KH = CH;   // halo chunks per thread (no more halo columns than own ones)
     extern __shared__ chunk_t plane_lds[];
     const int Ls = g.Ls, TX = pd.tx, TY = pd.ty, NC = TX * TY, NH = 2 * (TX + TY), NT = NC * Ls;
@@ -77,10 +91,13 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     const float dgb = static_cast<float>(diag) / bt;
     const float fpb = -((s == Ls - 1) ? static_cast<float>(-mf) : 1.0f) / bt;
     const float fmb = -((s == 0) ? static_cast<float>(-mf) : 1.0f) / bt;
+    [[maybe_unused]] const float wp = (s == Ls - 1) ? static_cast<float>(-mf) : 1.0f;
+    [[maybe_unused]] const float wm = (s == 0) ? static_cast<float>(-mf) : 1.0f;
+    [[maybe_unused]] const float mb5 = static_cast<float>(b5), mc5 = static_cast<float>(c5);
 
     // Byte offsets, within a time slice, of this thread's loads: own chunks j NT + tid, halo chunks
-    // j NT + tid, halo scales, one link.
-    unsigned og[CH], hg[KH], hso = 0, ug;
+    // j NT + tid, halo scales, one link. (MOBF loads whole records: its own and halo record td.)
+    [[maybe_unused]] unsigned og[CH], hg[KH], hso = 0, ug, hq = 0;
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
         const int cc = j * NT + td, row = cc / (TX * Ls * CH), off = cc - row * (TX * Ls * CH);
@@ -102,6 +119,10 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     for (int j = 0; j < KH; ++j) {
         const int h = j * NT + td, hc = h / (Ls * CH), off = h - hc * (Ls * CH);
         hg[j] = h < nhc ? (halo_col(hc) * CH + off) * 16u : og[0];
+    }
+    if constexpr (MOBF) {
+        const int hc = td / Ls;
+        hq = td < NH * Ls ? halo_col(hc) + (td - hc * Ls) : q;
     }
     if constexpr (SC) {
         const int hc = td / Ls;
@@ -147,21 +168,34 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     };
     Cx<float> A[4][3], hb[2][3];
     float hs;
-    Rec<SP> p;
+    Rec<SL> p;
     MatRow u, utf, utb;
-    // record q + dq of a slice, straight from memory
-    auto direct = [&](int tt, int dq, Rec<SP> &r) {
-        const char *b = static_cast<const char *>(psi) + static_cast<size_t>(slice(tt)) * nq * (CH * 16);
-        unsigned o = static_cast<unsigned>(q + dq) * (CH * 16u);
+    // record n of a slice, straight from memory
+    auto direct = [&](int tt, unsigned n, Rec<SP> &r) {
+        constexpr int CM = SP::kChunks;
+        const char *b = static_cast<const char *>(psi) + static_cast<size_t>(slice(tt)) * nq * (CM * 16);
+        unsigned o = n * (CM * 16u);
         __asm__("" : "+v"(o));
-        uint4 w[CH];
+        uint4 w[CM];
 #pragma unroll
-        for (int j = 0; j < CH; ++j) {
+        for (int j = 0; j < CM; ++j) {
             const chunk_t v = *reinterpret_cast<const chunk_t *>(b + o + j * 16);
             w[j] = make_uint4(v.x, v.y, v.z, v.w);
         }
-        r.set(w, SC ? (psi_scale + static_cast<size_t>(slice(tt)) * nq)[static_cast<unsigned>(q + dq)] : 1.0f);
+        r.set(w, SP::kScaled ? (psi_scale + static_cast<size_t>(slice(tt)) * nq)[n] : 1.0f);
     };
+    // the record the hops use: chi = B psi for M, else psi itself
+    auto hopped = [&](const Rec<SP> &r, Rec<SL> &h) {
+        if constexpr (MOBF) {
+#pragma unroll
+            for (int j = 0; j < 12; ++j) h.p[j / 3][j % 3] = {0.f, 0.f};
+            r.axpy(h.p, mb5);
+            column_shift_axpy<false>(r, h.p, mc5 * wp, mc5 * wm);
+        } else {
+            h = r;
+        }
+    };
+    [[maybe_unused]] Rec<SP> raw;   // MOBF: psi(x, tt); MOBA: psi(x, tt - 1) until out(tt - 1) is finished
     auto staged = [&](int r) {
         uint4 w[CH];
 #pragma unroll
@@ -176,6 +210,20 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     auto finish = [&](int tt) {
 #pragma unroll
         for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {bt * A[j / 3][j % 3].r, bt * A[j / 3][j % 3].i};
+        if constexpr (MOBA) {
+            // A = -H^dagger psi / 2: v = c5 w - psi, out = b5 w + psi + S^dagger v
+            const float d4 = static_cast<float>(diag);
+            Rec<SpF32> v;
+#pragma unroll
+            for (int j = 0; j < 12; ++j) {
+                Cx<float> &a = A[j / 3][j % 3];
+                v.p[j / 3][j % 3] = {mc5 * a.r, mc5 * a.i};
+                a = {mb5 * a.r, mb5 * a.i};
+            }
+            raw.axpy(v.p, mc5 * d4 - 1.0f);
+            raw.axpy(A, mb5 * d4 + 1.0f);
+            column_shift_axpy<true>(v, A, wp, wm);
+        }
         const size_t o = static_cast<size_t>(tt) * nq + q;
         if constexpr (FUSE == kFuseAxpy) {
             // r - alpha op psi; r may alias out: the thread reads its record before storing it
@@ -198,7 +246,9 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     {
         // the backward t-hop of slice t0: U_t(x, t0 - 1) and h(psi(x, t0 - 1))
         const int tm = t0 == 0 ? Lt - 1 : t0 - 1;
-        direct(tm, 0, p);
+        Rec<SP> r;
+        direct(tm, q, r);
+        hopped(r, p);
         p.template proj<3, -EF>(hb);
         hs = p.scale();
         Cx<float> w[3][3];
@@ -215,7 +265,51 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
 #pragma unroll 1
     for (int k = 0; k < pd.T; ++k) {
         const int tt = t0 + k;
-        {
+        // finishes out(tt - 1) with psi(x, tt) (p) and starts the sum of out(tt)
+        auto t_hops = [&](const Rec<SP> &centre) {
+            if (k > 0) {
+                hop_mfma<3, EF, false, SL>(A, p, utf);
+                finish(tt - 1);
+            }
+            Cx<float> chi[2][3];
+            su3_mfma<true>(utb, hb, chi);
+#pragma unroll
+            for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {0.f, 0.f};
+            reconstruct_fma<3, -EF, SC>(A, chi, hs);
+            p.template proj<3, -EF>(hb);
+            hs = p.scale();
+            if constexpr (KIND == GRID_DWF || MOBF) centre.axpy(A, dgb);
+            if constexpr (MOBF) column_shift_axpy<false>(centre, A, static_cast<float>(cs) * fpb, static_cast<float>(cs) * fmb);
+            if constexpr (MOBA) raw = centre;
+        };
+        if constexpr (MOBF) {
+            Rec<SP> hr;
+            Cx<float> wu[3][3];
+            direct(tt, q, raw);
+            direct(tt, hq, hr);
+            LK::load(static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes), ug, wu);
+            hopped(raw, p);
+            Rec<SL> hp;
+            // a halo record's s is td mod 16, this thread's own
+            hopped(hr, hp);
+            auto put = [&](int r, const Rec<SL> &x) {
+                float4 *d = reinterpret_cast<float4 *>(rec + r * CH);
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {
+                    const Cx<float> a = x.p[(2 * j) / 3][(2 * j) % 3], b = x.p[(2 * j + 1) / 3][(2 * j + 1) % 3];
+                    d[j] = make_float4(a.r, a.i, b.r, b.i);
+                }
+            };
+            put(td, p);
+            if (td < NH * Ls) put(NT + td, hp);
+            if (td < NS) {
+                float2 *d = lks + td * 9;
+#pragma unroll
+                for (int e = 0; e < 9; ++e) d[e] = make_float2(wu[e / 3][e % 3].r, wu[e / 3][e % 3].i);
+            }
+            t_hops(raw);
+            __syncthreads();
+        } else {
             const char *b = static_cast<const char *>(psi) + static_cast<size_t>(slice(tt)) * nq * (CH * 16);
             const char *lk = static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes);
             chunk_t wo[CH], wh[KH];
@@ -248,22 +342,13 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
                 }
             }
         }
-        __syncthreads();
-        staged(td);
-        if (k > 0) {
-            hop_mfma<3, EF, false, SP>(A, p, utf);   // the forward t-hop finishes out(tt - 1)
-            finish(tt - 1);
+        if constexpr (!MOBF) {
+            __syncthreads();
+            staged(td);
+            t_hops(p);
         }
-        Cx<float> chi[2][3];
-        su3_mfma<true>(utb, hb, chi);
-#pragma unroll
-        for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {0.f, 0.f};
-        reconstruct_fma<3, -EF, SC>(A, chi, hs);
-        p.template proj<3, -EF>(hb);
-        hs = p.scale();
-        if constexpr (KIND != GRID_HOP) p.axpy(A, dgb);
-        Rec<SP> pz;
-        direct(tt, zpo, pz);   // in flight during the x hops
+        Rec<SP> rz;
+        direct(tt, q + zpo, rz);   // in flight during the x hops
         if constexpr (KIND == GRID_DWF) {
             // - P_- psi~_{s+1} - P_+ psi~_{s-1} (M; P_+ and P_- exchanged for M^dagger)
             constexpr int hup = DAG ? 0 : 1;
@@ -272,21 +357,29 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
         }
         staged(nxp);
         mat_row<false>(lks + (c * 4) * 9, u);
-        hop_mfma<0, EF, false, SP>(A, p, u);
+        hop_mfma<0, EF, false, SL>(A, p, u);
         staged(nxm);
         mat_row<true>(lks + lxm * 9, u);
-        hop_mfma<0, -EF, true, SP>(A, p, u);
+        hop_mfma<0, -EF, true, SL>(A, p, u);
         mat_row<false>(lks + (c * 4 + 2) * 9, u);
-        hop_mfma<2, EF, false, SP>(A, pz, u);
-        direct(tt, zmo, pz);   // in flight during the y hops
+        {
+            Rec<SL> pz;
+            hopped(rz, pz);
+            hop_mfma<2, EF, false, SL>(A, pz, u);
+        }
+        direct(tt, q + zmo, rz);   // in flight during the y hops
         staged(nyp);
         mat_row<false>(lks + (c * 4 + 1) * 9, u);
-        hop_mfma<1, EF, false, SP>(A, p, u);
+        hop_mfma<1, EF, false, SL>(A, p, u);
         staged(nym);
         mat_row<true>(lks + lym * 9, u);
-        hop_mfma<1, -EF, true, SP>(A, p, u);
+        hop_mfma<1, -EF, true, SL>(A, p, u);
         mat_row<true>(lks + (4 * NC + c) * 9, u);
-        hop_mfma<2, -EF, true, SP>(A, pz, u);
+        {
+            Rec<SL> pz;
+            hopped(rz, pz);
+            hop_mfma<2, -EF, true, SL>(A, pz, u);
+        }
         // U_t(x, tt): the forward t-hop of out(tt) and the backward one of out(tt + 1)
         mat_row<false>(lks + (c * 4 + 3) * 9, utf);
         mat_row<true>(lks + (c * 4 + 3) * 9, utb);
@@ -294,8 +387,10 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     }
     {
         const int tl = t0 + pd.T - 1;
-        direct(tl == Lt - 1 ? 0 : tl + 1, 0, p);
-        hop_mfma<3, EF, false, SP>(A, p, utf);
+        Rec<SP> r;
+        direct(tl == Lt - 1 ? 0 : tl + 1, q, r);
+        hopped(r, p);
+        hop_mfma<3, EF, false, SL>(A, p, utf);
         finish(tl);
     }
     if constexpr (FUSE != kFuseNone) {
@@ -334,11 +429,10 @@ static bool plane_tile(const GeomDev &g, PlaneDev *d) {
 // 197 / 201 us, FP32 371 / 339 / 339 / 336 / 348 / 340 / 371 us, 24^4 x 8 FP32 248 / 229 / 227 / 221 / 236 / 237 /
 // 239 us; T = 2 / 4 / 8 / 16: 16^4 x 16 FP32 93 / 85 / 80 / 89 us, 16^4 x 12 FP16 storage 45 / 39 / 45 / 58 us;
 // T = 1 / 2 / 3 / 4 / 6: 12^4 x 16 FP32 38 / 34 / 29 / 34 / 34 us.
-static PlaneDev plane_dev(const GeomDev &g, int prec) {
+static PlaneDev plane_dev(const GeomDev &g, bool scaled) {
     PlaneDev d{};
     if (!plane_tile(g, &d)) return d;
     const int waves = (d.tx * d.ty * g.Ls + 63) / 64;
-    const bool scaled = prec == GRID_F16S;
     const long granules = (static_cast<long>(plane_lds_bytes(d, g.Ls, scaled ? 3 : 6, scaled)) + 1279) / 1280;
     const long by_lds = 128 / granules;   // 160 KB in granules of 1280 bytes
     const long per_cu = by_lds < 12 / waves ? by_lds : 12 / waves;   // three wavefronts per SIMD
@@ -362,28 +456,34 @@ static PlaneDev plane_dev(const GeomDev &g, int prec) {
 bool plane_applies(const DhopArgs &a) {
     PlaneDev d;
     const int least = a.prec == GRID_F16S ? 300000 : 160000;
-    return !a.custom && (a.kind == GRID_HOP || a.kind == GRID_DWF) && (a.prec == GRID_F32 || a.prec == GRID_F16S) &&
-           a.g.n5 >= least && plane_tile(a.g, &d);
+    const bool kind = a.kind == GRID_HOP || a.kind == GRID_DWF || (a.kind == GRID_MOBIUS && a.g.Ls == 16);
+    return !a.custom && kind && (a.prec == GRID_F32 || a.prec == GRID_F16S) && a.g.n5 >= least && plane_tile(a.g, &d);
 }
 
+// Whether the block's records lie in LDS as FP16 codes and scales.
+static bool plane_scaled(const DhopArgs &a) { return a.prec == GRID_F16S && !(a.kind == GRID_MOBIUS && !a.dag); }
+
 long plane_blocks(const DhopArgs &a) {
-    const PlaneDev d = plane_dev(a.g, a.prec);
+    const PlaneDev d = plane_dev(a.g, plane_scaled(a));
     return static_cast<long>(a.g.vol / a.g.L[3]) / (d.tx * d.ty) * (a.g.L[3] / d.T);
 }
 
 template <class SP, class LK>
 static hipError_t launch_plane_t(const DhopArgs &a) {
-    const PlaneDev d = plane_dev(a.g, a.prec);
+    const bool scaled = plane_scaled(a);
+    const PlaneDev d = plane_dev(a.g, scaled);
     const dim3 grid(static_cast<unsigned>(plane_blocks(a))), block((d.tx * d.ty * a.g.Ls + 63) / 64 * 64);
-    const size_t lds = plane_lds_bytes(d, a.g.Ls, SP::kChunks, SP::kScaled);
+    const size_t lds = plane_lds_bytes(d, a.g.Ls, scaled ? 3 : 6, scaled);
     hipStream_t st = a.stream;
 #define GRIDMI_LAUNCH(DAG, KIND, FUSE)                                                                          \
     hipLaunchKernelGGL((k_dhop_plane<SP, LK, DAG, KIND, FUSE>), grid, block, lds, st, a.U, a.psi, a.psi_scale, a.out, \
-                       a.out_scale, a.g, d, a.diag, a.mf, a.fz)
+                       a.out_scale, a.g, d, a.diag, a.mf, a.cs, a.b5, a.c5, a.fz)
     if (a.fuse != kFuseNone) {
         switch (a.kind * 4 + a.fuse * 2 + (a.dag ? 1 : 0)) {
             case GRID_DWF * 4 + kFuseNorm * 2 + 0: GRIDMI_LAUNCH(false, GRID_DWF, kFuseNorm); break;
             case GRID_DWF * 4 + kFuseAxpy * 2 + 1: GRIDMI_LAUNCH(true, GRID_DWF, kFuseAxpy); break;
+            case GRID_MOBIUS * 4 + kFuseNorm * 2 + 0: GRIDMI_LAUNCH(false, GRID_MOBIUS, kFuseNorm); break;
+            case GRID_MOBIUS * 4 + kFuseAxpy * 2 + 1: GRIDMI_LAUNCH(true, GRID_MOBIUS, kFuseAxpy); break;
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
@@ -393,6 +493,8 @@ static hipError_t launch_plane_t(const DhopArgs &a) {
         case GRID_HOP * 2 + 1: GRIDMI_LAUNCH(true, GRID_HOP, kFuseNone); break;
         case GRID_DWF * 2 + 0: GRIDMI_LAUNCH(false, GRID_DWF, kFuseNone); break;
         case GRID_DWF * 2 + 1: GRIDMI_LAUNCH(true, GRID_DWF, kFuseNone); break;
+        case GRID_MOBIUS * 2 + 0: GRIDMI_LAUNCH(false, GRID_MOBIUS, kFuseNone); break;
+        case GRID_MOBIUS * 2 + 1: GRIDMI_LAUNCH(true, GRID_MOBIUS, kFuseNone); break;
         default: return hipErrorInvalidValue;
     }
 #undef GRIDMI_LAUNCH

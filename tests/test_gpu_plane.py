@@ -69,3 +69,31 @@ def test_plane_fused_epilogues(gpu, sloppy, shape):
     assert st["converged"]
     back = O.normal(O.Op.dwf(Ls, 1.8, 0.1), U, host(x))
     assert rel(back, b) <= 1.1e-10
+
+
+@pytest.mark.parametrize("shape", [((4, 4, 41, 20), 16), ((4, 4, 79, 16), 16), ((16, 12, 8, 13), 16), ((16, 16, 16, 6), 16)])
+@pytest.mark.parametrize("prec,fmt", [("f32", "L18"), ("f32", "L12"), ("f16s", "L18"), ("f16s", "L12")])
+def test_plane_mobius_parity(gpu, shape, prec, fmt):
+    """The Moebius operator on the plane walk (Ls = 16: a fifth-dimension column per 16-lane row)."""
+    from oracle import mobius as MB
+    from tests.gpu_util import as_prec, cached, host
+    gm = _gm()
+    dims, Ls = shape
+    U, psi = cached("gauge", dims, 1, kind="haar"), cached("spinor", dims, 3, Ls=Ls)
+    Uk, pk, Ur, pr = as_prec(U, psi, prec, fmt)
+    for dag in (False, True):
+        got = host(gm.mobius(Uk, pk, 1.8, 0.3, 1.5, 0.5, dag=dag))
+        _check(got, MB.mobius(Ur, pr, 1.8, 0.3, 1.5, 0.5, dag), prec, dag)
+
+
+@pytest.mark.parametrize("sloppy", ["f32", "f16s"])
+def test_plane_mobius_fused_epilogues(gpu, sloppy):
+    from oracle import mobius as MB
+    from tests.gpu_util import dev, host, rel
+    gm = _gm()
+    dims, Ls = (16, 8, 16, 10), 16
+    U = F.gauge_field(dims, seed=1, kind="haar")
+    b = F.spinor_field(dims, seed=3, Ls=Ls)
+    x, st = gm.cg(dev(U), dev(b), kind="mobius", M5=1.8, mf=0.1, b5=1.5, c5=0.5, tol=1e-10, sloppy=sloppy, check_every=4)
+    assert st["converged"]
+    assert rel(MB.normal(U, host(x), 1.8, 0.1, 1.5, 0.5), b) <= 1.1e-10
