@@ -254,7 +254,7 @@ struct SpF16S {
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -879,6 +879,7 @@ struct Rec<SpF32> {
     Cx<float> p[4][3];
     __device__ __forceinline__ void set(const uint4 *w, float) { SpF32::unpack(w, 1.0f, p); }
     __device__ __forceinline__ float scale() const { return 1.0f; }
+    __device__ __forceinline__ void renew() {}
     template <int MU, int E>
     __device__ __forceinline__ void proj(Cx<C> h[2][3]) const {
         project<MU, E>(p, h);
@@ -919,6 +920,11 @@ struct Rec<SpF16S> {
         s = sc;
     }
     __device__ __forceinline__ float scale() const { return s; }
+    // hides the codes from the compiler, which would keep 24 conversions for a record's second use
+    __device__ __forceinline__ void renew() {
+#pragma unroll
+        for (int j = 0; j < 12; ++j) __asm__("" : "+v"(w[j]));
+    }
     // code (a, c) + EE code (b, c), or + EE i code (b, c) with IM. The factor 1 is hidden from the
     // compiler, which would otherwise turn the FMA into two conversions and an addition.
     template <int EE, bool IM>
@@ -965,7 +971,7 @@ struct Rec<SpF16S> {
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
             Cx<C> &o = acc[2 * HF + j / 3][j % 3];
-            const uint32_t v = __builtin_amdgcn_mov_dpp(static_cast<int>(w[6 * HF + j]), CTRL, 0xf, 0xf, false);
+            const uint32_t v = __builtin_amdgcn_mov_dpp(static_cast<int>(w[6 * HF + j]), CTRL, 0xf, 0xf, true);
             o = {__builtin_fmaf(half_lo(v), fs, o.r), __builtin_fmaf(half_hi(v), fs, o.i)};
         }
     }
@@ -980,6 +986,35 @@ template <bool DAG, class R>
 __device__ __forceinline__ void column_shift_axpy(const R &r, Cx<float> acc[4][3], float fp, float fm) {
     r.template shift_axpy<kDppNext, DAG ? 0 : 1>(acc, fp);
     r.template shift_axpy<kDppPrev, DAG ? 1 : 0>(acc, fm);
+}
+
+// v = (d - S)^-1 v (S^dagger with DAG) across a DPP row, r = 1 / d: column_m5inv's sum by doubling. After
+// step k a lane holds sum_{j < 2^(k+1)} r^j v_{s +- j}, -mf once s +- j wraps: a term 2^k further on wraps
+// either there or where the partial sum it takes already counts it.
+template <int SH, int HF, bool NEXT>
+__device__ __forceinline__ void column_m5inv_step(Cx<float> v[4][3], int s, float rj, float mf) {
+    const float f = (NEXT ? s + SH >= 16 : s < SH) ? -mf * rj : rj;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        Cx<float> &o = v[2 * HF + j / 3][j % 3];
+        constexpr int ctrl = 0x120 + (NEXT ? 16 - SH : SH);   // row_ror
+        o = {o.r + f * dpp_f32<ctrl>(o.r), o.i + f * dpp_f32<ctrl>(o.i)};
+    }
+}
+template <bool DAG>
+__device__ __forceinline__ void column_m5inv_row(Cx<float> v[4][3], int s, float r, float mf) {
+    const float r2 = r * r, r4 = r2 * r2, r8 = r4 * r4;
+    column_m5inv_step<1, 0, DAG>(v, s, r, mf);
+    column_m5inv_step<1, 1, !DAG>(v, s, r, mf);
+    column_m5inv_step<2, 0, DAG>(v, s, r2, mf);
+    column_m5inv_step<2, 1, !DAG>(v, s, r2, mf);
+    column_m5inv_step<4, 0, DAG>(v, s, r4, mf);
+    column_m5inv_step<4, 1, !DAG>(v, s, r4, mf);
+    column_m5inv_step<8, 0, DAG>(v, s, r8, mf);
+    column_m5inv_step<8, 1, !DAG>(v, s, r8, mf);
+    const float c0 = r / (1.0f + mf * (r8 * r8));
+#pragma unroll
+    for (int j = 0; j < 12; ++j) v[j / 3][j % 3] = {c0 * v[j / 3][j % 3].r, c0 * v[j / 3][j % 3].i};
 }
 
 // acc += s [chi; E A_MU^dagger chi] (reconstruct_add with the record's scale; s = 1 unless SCALED)

@@ -1219,7 +1219,7 @@ static hipError_t launch_walk_cb(const DhopArgs &a) {
 }
 
 // Schedules: the plane walk (plane.hip) for the plain operators on 5D FP32 and FP16-storage fields
-// its tiles divide, column walks for the other FP16-storage and 5D FP32 fields (full lattice, or
+// its tiles divide and its checkerboard form (plane_cb.hip) for Ls = 16, column walks for the other FP16-storage and 5D FP32 fields (full lattice, or
 // checkerboard fields in the even-odd form), direction-parallel otherwise (measured faster there). The
 // full-lattice walk also takes the custom form with a separate y and beta = -1/2 (the Moebius
 // operator's hopping pass).
@@ -1236,6 +1236,7 @@ static hipError_t launch_sched(const DhopArgs &a) {
         return hipErrorInvalidValue;
     if (tile_applies(a)) return launch_tile(a);
     if (plane_applies(a)) return launch_plane(a);
+    if (plane_cb_applies(a)) return launch_plane_cb(a);
     // the walks serve FP32 and FP16 storage, the direction-parallel kernel FP64 and FP32 (walk_prec)
     if constexpr (sizeof(typename SP::C) == 4) {
         if (use_walk(a)) return launch_walk<SP, LK>(a);
@@ -1248,6 +1249,7 @@ static hipError_t launch_sched(const DhopArgs &a) {
 long dhop_blocks(const DhopArgs &a) {
     if (tile_applies(a)) return tile_blocks(a);
     if (plane_applies(a)) return plane_blocks(a);
+    if (plane_cb_applies(a)) return plane_cb_blocks(a);
     if (use_walk(a)) {
         const long nbc = (static_cast<long>(a.g.L[0]) * a.g.L[1] * a.g.L[2] * a.g.Ls + 255) / 256;
         return nbc * (a.g.L[3] / choose_steps(a.g));

@@ -24,8 +24,8 @@ struct FuseDev {
     double *part = nullptr;
 };
 
-// Internal operator kinds of the checkerboard column walk (the even-odd Moebius Schur operator,
-// B = b5 + c5 S; see k_dhop_walk_cb): kMobHop out = beta H B psi (dag: B^dagger beta H^dagger psi),
+// Internal operator kinds of the checkerboard walks (the even-odd Moebius Schur operator,
+// B = b5 + c5 S; see k_dhop_walk_cb and k_dhop_plane_cb): kMobHop out = beta H B psi (dag: B^dagger beta H^dagger psi),
 // kMobDiag adds diag y - cs S y (dag: diag y - cs S^dagger y). Full-lattice FP32 / FP16-storage
 // checkerboard fields whose Ls divides 64 (mob_cb_applies).
 enum { kMobHop = 8, kMobDiag = 9 };
@@ -86,6 +86,10 @@ hipError_t launch_tile(const DhopArgs &a);
 bool plane_applies(const DhopArgs &a);
 long plane_blocks(const DhopArgs &a);
 hipError_t launch_plane(const DhopArgs &a);
+// Plane walk on checkerboard fields (plane_cb.hip): 5D FP32 / FP16-storage fields with Ls = 16.
+bool plane_cb_applies(const DhopArgs &a);
+long plane_cb_blocks(const DhopArgs &a);
+hipError_t launch_plane_cb(const DhopArgs &a);
 // Number of blocks (= partial sums written by a fused epilogue) launch_dhop uses for `a`.
 long dhop_blocks(const DhopArgs &a);
 // Upper bound of dhop_blocks over all schedules for a field of n5 sites and time extent Lt.
