@@ -1130,6 +1130,20 @@ __device__ __forceinline__ void hop_mfma(Cx<float> acc[4][3], const Rec<SP> &r, 
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// acc += the hop of a record as loaded, a lane's own link on the vector units
+template <int MU, int E, bool ADJ, class SP>
+__device__ __forceinline__ void hop_rec(Cx<float> acc[4][3], const Rec<SP> &r, const Cx<float> u[3][3]) {
+    Cx<float> h[2][3], chi[2][3];
+    r.template proj<MU, E>(h);
+    if (ADJ)
+        su3_adj_mul(u, h, chi);
+    else
+        su3_mul(u, h, chi);
+    reconstruct_fma<MU, E, SP::kScaled>(acc, chi, r.scale());
+    pin(acc);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Hardware dispatches workgroup b to XCD b % 8. Renumber so that each XCD receives one
 // contiguous range of logical blocks: neighbouring lattice sites then share an L2.
 __device__ __forceinline__ int xcd_block(int b, int nblocks) {

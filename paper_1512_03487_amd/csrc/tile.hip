@@ -35,12 +35,12 @@ struct TileShape {
 
 struct TileDev {
     int ntx, nty, ntz;   // tiles per direction
-    int T;               // time slices per block
+    int nseg;            // blocks along t: block i walks slices [i Lt / nseg, (i + 1) Lt / nseg)
 };
 
-// Record of LDS slot `slot` (16-byte chunks at the record pitch), decoded into p.
+// Record of LDS slot `slot` (16-byte chunks at the record pitch), undecoded.
 template <class SP>
-__device__ __forceinline__ void lds_record(const chunk_t *base, const float *sbase, int slot, Cx<typename SP::C> p[4][3]) {
+__device__ __forceinline__ void lds_record(const chunk_t *base, const float *sbase, int slot, Rec<SP> &p) {
     constexpr int CH = SP::kChunks;
     uint4 w[CH];
 #pragma unroll
@@ -48,7 +48,7 @@ __device__ __forceinline__ void lds_record(const chunk_t *base, const float *sba
         const chunk_t v = base[slot * CH + k];
         w[k] = make_uint4(v.x, v.y, v.z, v.w);
     }
-    SP::unpack(w, SP::kScaled ? sbase[slot] : 1.0f, p);
+    p.set(w, SP::kScaled ? sbase[slot] : 1.0f);
 }
 
 // Global chunk offset (relative to the start of a time slice) of chunk c of the tile's loads:
@@ -109,7 +109,7 @@ struct LinkStage {
 };
 
 template <class SP, class LK, bool DAG, int KIND, int FUSE, int TX, int TY, int TZ>
-__global__ void __launch_bounds__(TX * TY * TZ) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(TX * TY * TZ) __attribute__((amdgpu_waves_per_eu(LK::kRows == 2 ? 3 : 2)))
 k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const float *__restrict__ psi_scale, void *out,
             float *out_scale, GeomDev g, TileDev td, double diag, FuseDev fz) {
     using C = typename SP::C;
@@ -119,10 +119,8 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
     static_assert(TX * TY == 64, "one wavefront per z-plane of the tile");
     constexpr int N = S::N, CH = SP::kChunks, NU = LS::kUnits;
     constexpr int KH = (S::NH * CH + N - 1) / N;         // halo chunks per thread
-    __shared__ chunk_t sb[N * CH];                       // interior records of slice t
-    __shared__ chunk_t sh[S::NH * CH];                   // halo records of slice t
-    __shared__ float sbs[SP::kScaled ? N : 1];           // FP16 storage: per-record scales
-    __shared__ float shs[SP::kScaled ? S::NH : 1];
+    __shared__ chunk_t sb[(N + S::NH) * CH];             // interior, then halo records of slice t
+    __shared__ float sbs[SP::kScaled ? N + S::NH : 1];   // FP16 storage: their scales
     __shared__ LU sl[TZ][64 * NU];                       // per-wavefront link staging
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -135,7 +133,7 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
     const int V3 = Lx * Ly * Lz;
     const int x = x0 + cx, y = y0 + cy, z = z0 + cz;
     const int col = (z * Ly + y) * Lx + x;
-    const int t0 = seg * td.T;
+    const int t0 = seg * Lt / td.nseg, T = (seg + 1) * Lt / td.nseg - t0;
     constexpr int EF = DAG ? +1 : -1;
 
     // halo chunk offsets of this thread's loads (slice-relative, fixed along the walk)
@@ -219,7 +217,9 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
         }
         sc = SP::kScaled ? psi_scale[r] : 1.0f;
     };
-    Cx<C> chi_b[2][3], u[3][3], p[4][3];
+    Cx<C> chi_b[2][3], u[3][3];
+    C chi_s;   // chi_b is the transported half-spinor over the record's scale
+    Rec<SP> p;
     uint4 Pw[CH];      // centre record psi(x, t), raw
     float Ps = 1.0f;
     LU lw[NU];
@@ -228,18 +228,22 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
         // the centre record psi(x, t0) and slice t0's halo
         const int tm = t0 == 0 ? Lt - 1 : t0 - 1;
         link_units(tm, 3, false, lw);
-        SP::load(psi, psi_scale, static_cast<size_t>(tm) * V3 + col, p);
+        uint4 w[CH];
+        float sc;
+        own_raw(tm, w, sc);
         own_raw(t0, Pw, Ps);
         issue_halo(t0);
         link_take(lw, u);
         Cx<C> hb[2][3];
-        project<3, -EF>(p, hb);
+        p.set(w, sc);
+        p.template proj<3, -EF>(hb);
         su3_adj_mul(u, hb, chi_b);
+        chi_s = p.scale();
         link_units(t0, 0, false, lw);
     }
     [[maybe_unused]] double n2 = 0.0;
 #pragma unroll 1
-    for (int k = 0; k < td.T; ++k) {
+    for (int k = 0; k < T; ++k) {
         const int t = t0 + k;
         const int tn = t == Lt - 1 ? 0 : t + 1;
         // stage this thread's centre record and its share of the halo of slice t
@@ -248,73 +252,65 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
         if constexpr (SP::kScaled) sbs[tid] = Ps;
 #pragma unroll
         for (int j = 0; j < KH; ++j)
-            if (hoff[j] >= 0) sh[j * N + tid] = wh[j];
+            if (hoff[j] >= 0) sb[(CH + j) * N + tid] = wh[j];
         if constexpr (SP::kScaled)
-            if (hrec >= 0) shs[tid] = shv;
+            if (hrec >= 0) sbs[N + tid] = shv;
         __syncthreads();
         // the forward time neighbour psi(x, t + 1) (the next centre) and the next halo
         uint4 Qw[CH];
         float Qs = 1.0f;
         own_raw(tn, Qw, Qs);
-        if (k + 1 < td.T) issue_halo(tn);
-        auto rec = [&](int slot, Cx<C> q[4][3]) {
-            if (slot < N)
-                lds_record<SP>(sb, sbs, slot, q);
-            else
-                lds_record<SP>(sh, shs, slot - N, q);
-        };
+        if (k + 1 < T) issue_halo(tn);
+        auto rec = [&](int slot, Rec<SP> &q) { lds_record<SP>(sb, sbs, slot, q); };
         Cx<C> acc[4][3];
 #pragma unroll
         for (int j = 0; j < 12; ++j) acc[j / 3][j % 3] = {C(0), C(0)};
-        reconstruct_add<3, -EF>(acc, chi_b);
+        reconstruct_fma<3, -EF, SP::kScaled>(acc, chi_b, chi_s);
         // spatial hops: links of the next direction are in flight while this one computes
         link_take(lw, u);
         link_units(t, 0, true, lw);
         rec(nxp, p);
-        hop_term<0, EF, false>(acc, p, u);
+        hop_rec<0, EF, false, SP>(acc, p, u);
         link_take(lw, u);
         link_units(t, 1, false, lw);
         rec(nxm, p);
-        hop_term<0, -EF, true>(acc, p, u);
+        hop_rec<0, -EF, true, SP>(acc, p, u);
         link_take(lw, u);
         link_units(t, 1, true, lw);
         rec(nyp, p);
-        hop_term<1, EF, false>(acc, p, u);
+        hop_rec<1, EF, false, SP>(acc, p, u);
         link_take(lw, u);
         link_units(t, 2, false, lw);
         rec(nym, p);
-        hop_term<1, -EF, true>(acc, p, u);
+        hop_rec<1, -EF, true, SP>(acc, p, u);
         link_take(lw, u);
         link_units(t, 2, true, lw);
         rec(nzp, p);
-        hop_term<2, EF, false>(acc, p, u);
+        hop_rec<2, EF, false, SP>(acc, p, u);
         link_take(lw, u);
         link_units(t, 3, false, lw);
         rec(nzm, p);
-        hop_term<2, -EF, true>(acc, p, u);
+        hop_rec<2, -EF, true, SP>(acc, p, u);
         // forward time hop psi(x, t + 1) with U_t(x, t); the same link carries the backward time
         // hop of slice t + 1, U_t(x, t)^dagger h(psi(x, t))
         link_take(lw, u);
-        if (k + 1 < td.T) link_units(tn, 0, false, lw);
-        Cx<C> P[4][3];
-        lds_record<SP>(sb, sbs, own, P);   // the centre psi(x, t), as staged
-        {
-            Cx<C> h[2][3], ch[2][3];
-            SP::unpack(Qw, Qs, p);
-            project<3, EF>(p, h);
-            su3_mul(u, h, ch);
-            reconstruct_add<3, EF>(acc, ch);
-            project<3, -EF>(P, h);
-            su3_adj_mul(u, h, chi_b);
-        }
+        if (k + 1 < T) link_units(tn, 0, false, lw);
+        p.set(Qw, Qs);
+        hop_rec<3, EF, false, SP>(acc, p, u);
+        rec(own, p);   // the centre psi(x, t), as staged
         if constexpr (KIND != GRID_HOP) {
             // D = (4 + m) - H/2
-            const C dg = static_cast<C>(diag), half = static_cast<C>(0.5);
+            const C dg = static_cast<C>(diag);
 #pragma unroll
-            for (int j = 0; j < 12; ++j) {
-                const Cx<C> a = acc[j / 3][j % 3], v = P[j / 3][j % 3];
-                acc[j / 3][j % 3] = {dg * v.r - half * a.r, dg * v.i - half * a.i};
-            }
+            for (int j = 0; j < 12; ++j) acc[j / 3][j % 3] = {C(-0.5) * acc[j / 3][j % 3].r, C(-0.5) * acc[j / 3][j % 3].i};
+            p.axpy(acc, dg);
+        }
+        {
+            Cx<C> h[2][3];
+            p.renew();
+            p.template proj<3, -EF>(h);
+            su3_adj_mul(u, h, chi_b);
+            chi_s = p.scale();
         }
         const size_t q = static_cast<size_t>(t) * V3 + col;
         if constexpr (FUSE == kFuseAxpy) {
@@ -352,8 +348,10 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
     }
 }
 
-// 4D: tile 8 x 8 x 4 (256 threads), walks of the longest divisor of Lt that keeps >= 1024 blocks
-// (>= 1 otherwise).
+// 4D: tile 8 x 8 x 4 (256 threads). Blocks along t: the count with the least (slices of the longest +
+// 0.7) x (0.5 + m) summed over the rounds of m <= 3 blocks a CU runs at a time. Measured, nseg = 2 / 4 / 6 /
+// 8 / 12 / 16 / 32, 12-real links: 32^4 71 / 58 / 62 / 60 / 65 / 65 / 73 us, 24^4 51 / 30 / 31 / 25 / 26 / 26 us,
+// 16^3 x 64 126 / 67 / 48 / 37 / 29 / 21 / 19 us.
 constexpr int kTX = 8, kTY = 8, kTZ = 4;
 static TileDev tile_dev(const GeomDev &g) {
     TileDev td;
@@ -361,9 +359,15 @@ static TileDev tile_dev(const GeomDev &g) {
     td.nty = g.L[1] / kTY;
     td.ntz = g.L[2] / kTZ;
     const long ntiles = static_cast<long>(td.ntx) * td.nty * td.ntz;
-    td.T = 1;
-    for (int T = 1; T <= g.L[3]; ++T)
-        if (g.L[3] % T == 0 && ntiles * (g.L[3] / T) >= 1024) td.T = T;
+    double best = 0.0;
+    for (int n = 1; n <= g.L[3]; ++n) {
+        const long m = (ntiles * n + 255) / 256, rem = m % 3;
+        const double cost = ((g.L[3] + n - 1) / n + 0.7) * ((m / 3) * 3.5 + (rem ? 0.5 + rem : 0.0));
+        if (n == 1 || cost < best) {
+            best = cost;
+            td.nseg = n;
+        }
+    }
     return td;
 }
 
@@ -382,7 +386,7 @@ bool tile_applies(const DhopArgs &a) { return tile4_applies(a); }
 
 long tile_blocks(const DhopArgs &a) {
     const TileDev td = tile_dev(a.g);
-    return static_cast<long>(td.ntx) * td.nty * td.ntz * (a.g.L[3] / td.T);
+    return static_cast<long>(td.ntx) * td.nty * td.ntz * td.nseg;
 }
 
 template <class SP, class LK>
