@@ -12,8 +12,16 @@
 // previous slice) go beside it; the six spatial hops read LDS. The forward time neighbour
 // psi(x, t + 1) is the thread's next centre and stays in registers; the backward time hop
 // U_t(x, t-1)^dagger h(psi(x, t-1)) is formed one step ahead from the record and link already in
-// hand and carried, as in the column walk. Links: a wavefront stages one direction's 64 links in
-// its LDS area with coalesced loads (LinkStage) while the previous direction computes.
+// hand and carried, as in the column walk. Links: the tile's own, four per site, are contiguous rows
+// of memory and go to LDS as stored, with the links of the -x, -y and -z faces beside them; forward
+// and backward hops decode theirs from there.
+//
+// What bounds it: vector instructions (1290 per slice of a wavefront, 36 of 55 us at 32^4) beside the
+// 41 us its bytes take. A wavefront that staged one direction's 64 links at a time, seven times per
+// slice, touched the same cache lines (24-byte links of four directions at 96-byte pitch) each time:
+// 12-real 32^4 70 -> 62 us from memory, 58 -> 55 in cache, 18-real 72 -> 56, 24^4 x 18-real 30 -> 26; before
+// that the records' conversion and scaling ahead of the projection, and a last round of blocks a third
+// full: 75.5 -> 70 us, 18-real 79 -> 72.
 //
 // Per site: 8 x (12 + 132) + 7 x 24 = 1320 flops, the convention of the flop counts quoted for
 // this operator.
@@ -93,35 +101,34 @@ __device__ __forceinline__ int tile_chunk_offset(const GeomDev &g, int x0, int y
     return ((z * Ly + y) * Lx + x) * CH + j;
 }
 
-// Coalesced staging of one direction's links for a wavefront's 64 sites: the links of consecutive
-// sites are LB-byte pieces at a 4 LB stride (site-major, four directions per site), so consecutive
-// lanes load consecutive units of the same or the next link (unit = the largest of 16, 8, 4 bytes
-// dividing LB), write them to the wavefront's LDS area in link order, and each lane then decodes
-// its own link. A lane loading its own link directly instead touches a different cache line in
-// every lane, which the vector-memory path serves several times slower.
+// Links of a tile in LDS: a site's four links as stored and eight bytes of padding (the reads of a
+// wavefront, one link per lane at this pitch, then spread over all banks), the face links after them.
 template <class LK>
-struct LinkStage {
+struct LinkTile {
     static constexpr int LB = LK::kBytes;
-    static constexpr int kUnit = LB % 16 == 0 ? 16 : LB % 8 == 0 ? 8 : 4;
-    static constexpr int kUnits = LB / kUnit;            // units per link = units per lane
+    static constexpr int kPitch = 4 * LB + 8;
+    static constexpr int kChunks = 4 * LB / 16;         // 16-byte chunks per site = chunks per lane
+    static constexpr int kUnit = LB % 8 == 0 ? 8 : 4;   // a face link is copied in these
+    static constexpr int kUnits = LB / kUnit;
     typedef unsigned int u2v __attribute__((ext_vector_type(2)));
-    using T = std::conditional_t<kUnit == 16, chunk_t, std::conditional_t<kUnit == 8, u2v, uint32_t>>;
+    using T = std::conditional_t<kUnit == 8, u2v, uint32_t>;
 };
 
 template <class SP, class LK, bool DAG, int KIND, int FUSE, int TX, int TY, int TZ>
-__global__ void __launch_bounds__(TX * TY * TZ) __attribute__((amdgpu_waves_per_eu(LK::kRows == 2 ? 3 : 2)))
+__global__ void __launch_bounds__(TX * TY * TZ) __attribute__((amdgpu_waves_per_eu(2)))
 k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const float *__restrict__ psi_scale, void *out,
             float *out_scale, GeomDev g, TileDev td, double diag, FuseDev fz) {
     using C = typename SP::C;
     using S = TileShape<TX, TY, TZ>;
-    using LS = LinkStage<LK>;
-    using LU = typename LS::T;
+    using LT = LinkTile<LK>;
+    using LU = typename LT::T;
     static_assert(TX * TY == 64, "one wavefront per z-plane of the tile");
-    constexpr int N = S::N, CH = SP::kChunks, NU = LS::kUnits;
+    constexpr int N = S::N, CH = SP::kChunks, NU = LT::kUnits, NL = LT::kChunks;
     constexpr int KH = (S::NH * CH + N - 1) / N;         // halo chunks per thread
     __shared__ chunk_t sb[(N + S::NH) * CH];             // interior, then halo records of slice t
     __shared__ float sbs[SP::kScaled ? N + S::NH : 1];   // FP16 storage: their scales
-    __shared__ LU sl[TZ][64 * NU];                       // per-wavefront link staging
+    constexpr int NF = S::HX + S::HY + S::HZ;            // links of the -x, -y and -z faces
+    __shared__ __align__(16) char sl[N * LT::kPitch + NF * LT::LB];
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int lb = xcd_block(blockIdx.x, gridDim.x);
@@ -156,44 +163,66 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
     const int nym = cy > 0 ? own - TX : N + S::YM + cx + TX * cz;
     const int nzp = cz < TZ - 1 ? own + TX * TY : N + S::ZP + cx + TX * cy;
     const int nzm = cz > 0 ? own - TX * TY : N + S::ZM + cx + TX * cy;
-    // link staging: byte offset (within a time slice) of this lane's units of the forward link
-    // of direction 0, and whether the unit's site sits on x = 0 / y = 0 (backward hops wrap)
-    unsigned lofs[NU];
-    unsigned wrapx = 0, wrapy = 0;
+    // links: a wavefront loads the four links of its z-plane's 64 sites, rows of TX sites contiguous in
+    // memory, and threads below NF one link of a -x, -y or -z face each
+    unsigned lofs[NL], lfof = 0;
 #pragma unroll
-    for (int k = 0; k < NU; ++k) {
-        const int u = k * 64 + lane, i = u / NU, j = u - (u / NU) * NU;
-        const int xi = x0 + (i % TX), yi = y0 + (i / TX);
-        lofs[k] = static_cast<unsigned>(((z * Ly + yi) * Lx + xi) * 4) * LS::LB + j * LS::kUnit;
-        wrapx |= (xi == 0 ? 1u : 0u) << k;
-        wrapy |= (yi == 0 ? 1u : 0u) << k;
+    for (int k = 0; k < NL; ++k) {
+        const int u = k * 64 + lane, row = u / (TX * NL), off = u - row * (TX * NL);
+        lofs[k] = static_cast<unsigned>(((z * Ly + y0 + row) * Lx + x0) * NL + off) * 16u;
     }
-    const bool wrapz = z == 0;   // uniform over the wavefront
-    LU *stage = sl[wv];
-    const char *ub = static_cast<const char *>(U);
-    // units of link U_mu(site - BWD mu-hat) at slice t for this lane's staging slots
-    auto link_units = [&](int t, int mu, bool bwd, LU w[NU]) {
-        const size_t tb = static_cast<size_t>(t) * V3 * 4 * LS::LB;
-#pragma unroll
-        for (int k = 0; k < NU; ++k) {
-            long off = static_cast<long>(lofs[k]) + mu * LS::LB;
-            if (bwd) {
-                if (mu == 0) off += ((wrapx >> k) & 1) ? static_cast<long>(Lx - 1) * 4 * LS::LB : -4L * LS::LB;
-                else if (mu == 1) off += ((wrapy >> k) & 1) ? static_cast<long>(Ly - 1) * Lx * 4 * LS::LB
-                                                           : -static_cast<long>(Lx) * 4 * LS::LB;
-                else off += wrapz ? static_cast<long>(Lz - 1) * Ly * Lx * 4 * LS::LB
-                                  : -static_cast<long>(Ly) * Lx * 4 * LS::LB;
-            }
-            w[k] = *reinterpret_cast<const LU *>(ub + tb + off);
+    if (tid < NF) {
+        int fx = x0, fy = y0, fz0 = z0, mu;
+        if (tid < S::HX) {
+            fx = x0 == 0 ? Lx - 1 : x0 - 1;
+            fy += tid % TY;
+            fz0 += tid / TY;
+            mu = 0;
+        } else if (tid < S::HX + S::HY) {
+            const int i = tid - S::HX;
+            fy = y0 == 0 ? Ly - 1 : y0 - 1;
+            fx += i % TX;
+            fz0 += i / TX;
+            mu = 1;
+        } else {
+            const int i = tid - S::HX - S::HY;
+            fz0 = z0 == 0 ? Lz - 1 : z0 - 1;
+            fx += i % TX;
+            fy += i / TX;
+            mu = 2;
         }
-    };
-    // staged units -> LDS -> this lane's link
-    auto link_take = [&](const LU w[NU], Cx<C> uu[3][3]) {
+        lfof = static_cast<unsigned>(((fz0 * Ly + fy) * Lx + fx) * 4 + mu) * LT::LB;
+    }
+    // LDS byte offsets of the links: own site, and the backward hops'
+    constexpr int FB = N * LT::kPitch;
+    const int lown = tid * LT::kPitch;
+    const int lxm = cx > 0 ? lown - LT::kPitch : FB + (cy + TY * cz) * LT::LB;
+    const int lym = cy > 0 ? lown - TX * LT::kPitch + LT::LB : FB + (S::HX + cx + TX * cz) * LT::LB;
+    const int lzm = cz > 0 ? lown - TX * TY * LT::kPitch + 2 * LT::LB : FB + (S::HX + S::HY + cx + TX * cy) * LT::LB;
+    const char *ub = static_cast<const char *>(U);
+    chunk_t lw[NL];
+    LU lf[NU];
+    auto issue_links = [&](int t) {
+        const char *tb = ub + static_cast<size_t>(t) * V3 * (4 * LT::LB);
 #pragma unroll
-        for (int k = 0; k < NU; ++k) stage[k * 64 + lane] = w[k];
-        wave_sync();
-        LK::load(stage, lane, uu);
-        wave_sync();   // every lane has its link before the area is reused
+        for (int k = 0; k < NL; ++k) lw[k] = *reinterpret_cast<const chunk_t *>(tb + lofs[k]);
+        if (tid < NF)
+#pragma unroll
+            for (int k = 0; k < NU; ++k) lf[k] = *reinterpret_cast<const LU *>(tb + lfof + k * LT::kUnit);
+    };
+    auto put_links = [&]() {
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+            typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+            const int u = k * 64 + lane;
+            u2v *d = reinterpret_cast<u2v *>(sl + wv * (64 * LT::kPitch) + u * 16 + (u / NL) * 8);
+            // a chunk of a site starts 16 (u mod NL) bytes into it
+            d[0] = u2v{lw[k].x, lw[k].y};
+            d[1] = u2v{lw[k].z, lw[k].w};
+        }
+        if (tid < NF)
+#pragma unroll
+            for (int k = 0; k < NU; ++k) *reinterpret_cast<LU *>(sl + FB + tid * LT::LB + k * LT::kUnit) = lf[k];
     };
 
     const chunk_t *src = reinterpret_cast<const chunk_t *>(psi);
@@ -222,24 +251,22 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
     Rec<SP> p;
     uint4 Pw[CH];      // centre record psi(x, t), raw
     float Ps = 1.0f;
-    LU lw[NU];
     {
         // prologue: the backward time hop of slice t0, U_t(x, t0 - 1)^dagger h(psi(x, t0 - 1)),
         // the centre record psi(x, t0) and slice t0's halo
         const int tm = t0 == 0 ? Lt - 1 : t0 - 1;
-        link_units(tm, 3, false, lw);
         uint4 w[CH];
         float sc;
         own_raw(tm, w, sc);
         own_raw(t0, Pw, Ps);
         issue_halo(t0);
-        link_take(lw, u);
+        issue_links(t0);
+        LK::load(U, (static_cast<size_t>(tm) * V3 + col) * 4 + 3, u);
         Cx<C> hb[2][3];
         p.set(w, sc);
         p.template proj<3, -EF>(hb);
         su3_adj_mul(u, hb, chi_b);
         chi_s = p.scale();
-        link_units(t0, 0, false, lw);
     }
     [[maybe_unused]] double n2 = 0.0;
 #pragma unroll 1
@@ -255,46 +282,42 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
             if (hoff[j] >= 0) sb[(CH + j) * N + tid] = wh[j];
         if constexpr (SP::kScaled)
             if (hrec >= 0) sbs[N + tid] = shv;
+        put_links();
         __syncthreads();
         // the forward time neighbour psi(x, t + 1) (the next centre) and the next halo
         uint4 Qw[CH];
         float Qs = 1.0f;
         own_raw(tn, Qw, Qs);
-        if (k + 1 < T) issue_halo(tn);
+        if (k + 1 < T) {
+            issue_halo(tn);
+            issue_links(tn);
+        }
         auto rec = [&](int slot, Rec<SP> &q) { lds_record<SP>(sb, sbs, slot, q); };
         Cx<C> acc[4][3];
 #pragma unroll
         for (int j = 0; j < 12; ++j) acc[j / 3][j % 3] = {C(0), C(0)};
         reconstruct_fma<3, -EF, SP::kScaled>(acc, chi_b, chi_s);
-        // spatial hops: links of the next direction are in flight while this one computes
-        link_take(lw, u);
-        link_units(t, 0, true, lw);
         rec(nxp, p);
+        LK::load(sl + lown, 0, u);
         hop_rec<0, EF, false, SP>(acc, p, u);
-        link_take(lw, u);
-        link_units(t, 1, false, lw);
         rec(nxm, p);
+        LK::load(sl + lxm, 0, u);
         hop_rec<0, -EF, true, SP>(acc, p, u);
-        link_take(lw, u);
-        link_units(t, 1, true, lw);
         rec(nyp, p);
+        LK::load(sl + lown + LT::LB, 0, u);
         hop_rec<1, EF, false, SP>(acc, p, u);
-        link_take(lw, u);
-        link_units(t, 2, false, lw);
         rec(nym, p);
+        LK::load(sl + lym, 0, u);
         hop_rec<1, -EF, true, SP>(acc, p, u);
-        link_take(lw, u);
-        link_units(t, 2, true, lw);
         rec(nzp, p);
+        LK::load(sl + lown + 2 * LT::LB, 0, u);
         hop_rec<2, EF, false, SP>(acc, p, u);
-        link_take(lw, u);
-        link_units(t, 3, false, lw);
         rec(nzm, p);
+        LK::load(sl + lzm, 0, u);
         hop_rec<2, -EF, true, SP>(acc, p, u);
         // forward time hop psi(x, t + 1) with U_t(x, t); the same link carries the backward time
         // hop of slice t + 1, U_t(x, t)^dagger h(psi(x, t))
-        link_take(lw, u);
-        if (k + 1 < T) link_units(tn, 0, false, lw);
+        LK::load(sl + lown + 3 * LT::LB, 0, u);
         p.set(Qw, Qs);
         hop_rec<3, EF, false, SP>(acc, p, u);
         rec(own, p);   // the centre psi(x, t), as staged
@@ -349,9 +372,9 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
 }
 
 // 4D: tile 8 x 8 x 4 (256 threads). Blocks along t: the count with the least (slices of the longest +
-// 0.7) x (0.5 + m) summed over the rounds of m <= 3 blocks a CU runs at a time. Measured, nseg = 2 / 4 / 6 /
-// 8 / 12 / 16 / 32, 12-real links: 32^4 71 / 58 / 62 / 60 / 65 / 65 / 73 us, 24^4 51 / 30 / 31 / 25 / 26 / 26 us,
-// 16^3 x 64 126 / 67 / 48 / 37 / 29 / 21 / 19 us.
+// 0.7) x (0.5 + m) summed over the rounds of m <= 2 blocks a CU runs at a time. Measured, nseg = 2 / 4 / 6 /
+// 8 / 12 / 16 / 32, 12-real links: 32^4 64 / 55 / 62 / 59 / 65 / 62 / 71 us, 24^4 47 / 28 / 30 / 25 / 26 / 29 us,
+// 16^3 x 64 115 / 60 / 43 / 33 / 26 / 20 / 19 us.
 constexpr int kTX = 8, kTY = 8, kTZ = 4;
 static TileDev tile_dev(const GeomDev &g) {
     TileDev td;
@@ -361,8 +384,8 @@ static TileDev tile_dev(const GeomDev &g) {
     const long ntiles = static_cast<long>(td.ntx) * td.nty * td.ntz;
     double best = 0.0;
     for (int n = 1; n <= g.L[3]; ++n) {
-        const long m = (ntiles * n + 255) / 256, rem = m % 3;
-        const double cost = ((g.L[3] + n - 1) / n + 0.7) * ((m / 3) * 3.5 + (rem ? 0.5 + rem : 0.0));
+        const long m = (ntiles * n + 255) / 256, rem = m % 2;
+        const double cost = ((g.L[3] + n - 1) / n + 0.7) * ((m / 2) * 2.5 + (rem ? 1.5 : 0.0));
         if (n == 1 || cost < best) {
             best = cost;
             td.nseg = n;
@@ -371,14 +394,10 @@ static TileDev tile_dev(const GeomDev &g) {
     return td;
 }
 
-// 4D FP16 storage only (86 against 93 us for the column walk, 74 against 132 us for the
-// direction-parallel kernel at 32^4). 4D FP32 fields, 12-real links included, run faster on the
-// direction-parallel kernel with its blocks as 4 x 2 x 2 x 2 boxes (32^4 12-real: 122.0 against
-// 132.1 us here; 18-real: the eight direction wavefronts read a site's four links at about the
-// same time, whereas this walk reads them one direction after another).
+// 4D FP16 storage only: with FP32 records and links a block fills the LDS of a CU (134 KB). The column
+// walk takes 93 us and the direction-parallel kernel 132 us at 32^4, against 55 here.
 static bool tile4_applies(const DhopArgs &a) {
-    const bool prec_ok = a.prec == GRID_F16S;
-    return !a.custom && a.g.Ls == 1 && prec_ok && a.g.L[0] % kTX == 0 && a.g.L[1] % kTY == 0 &&
+    return !a.custom && a.g.Ls == 1 && a.prec == GRID_F16S && a.g.L[0] % kTX == 0 && a.g.L[1] % kTY == 0 &&
            a.g.L[2] % kTZ == 0 && (a.kind == GRID_HOP || a.kind == GRID_WILSON);
 }
 
@@ -418,7 +437,6 @@ static hipError_t launch_tile_t(const DhopArgs &a) {
 
 hipError_t launch_tile(const DhopArgs &a) {
     switch (a.prec * 2 + a.link_fmt) {
-        case GRID_F32 * 2 + GRID_L12: return launch_tile_t<SpF32, LkF32<2>>(a);
         case GRID_F16S * 2 + GRID_L18: return launch_tile_t<SpF16S, LkF16<3>>(a);
         case GRID_F16S * 2 + GRID_L12: return launch_tile_t<SpF16S, LkF16<2>>(a);
         default: return hipErrorInvalidValue;
