@@ -9,6 +9,8 @@
 // h(v) h(w)^dagger of the projected half-spinors (with the same e), so each term is a sum of two
 // 3x3 outer products of half-spinors. One thread per (4D site, mu), one mu per wavefront; the
 // fifth coordinate is summed inside the thread; no atomics, so results are bitwise reproducible.
+#include <type_traits>
+
 #include "device.h"
 #include "launch.h"
 
@@ -51,6 +53,53 @@ __device__ __forceinline__ void grad_mu(const void *chi, const void *psi, int x4
     }
 }
 
+// G <- coef G, or its force TA(coef G U^dagger), stored as link `link` if live.
+template <typename C>
+__device__ __forceinline__ void grad_finish(const void *U, void *Gout, size_t link, bool live, double coef, int force_mode,
+                                            Cx<C> G[3][3]) {
+    const C c = static_cast<C>(coef);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) G[k / 3][k % 3] = cscale(c, G[k / 3][k % 3]);
+    if (force_mode) {
+        // F = TA(G U^dagger), TA(A) = (A - A^dagger)/2 - tr(A - A^dagger)/6
+        Cx<C> u[3][3], m[3][3];
+        if constexpr (sizeof(C) == 8)
+            LkF64<3>::load(U, link, u);
+        else
+            LkF32<3>::load(U, link, u);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                Cx<C> s = cmul(G[a][0], cconj(u[b][0]));
+                s = cmac(s, G[a][1], cconj(u[b][1]));
+                s = cmac(s, G[a][2], cconj(u[b][2]));
+                m[a][b] = s;
+            }
+        // tr(A - A^dagger) = 2 i Im tr A
+        const C imtr = m[0][0].i + m[1][1].i + m[2][2].i;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                Cx<C> f = {C(0.5) * (m[a][b].r - m[b][a].r), C(0.5) * (m[a][b].i + m[b][a].i)};
+                if (a == b) f.i -= imtr / C(3);
+                G[a][b] = f;
+            }
+    }
+    if (!live) return;
+    if constexpr (sizeof(C) == 8) {
+        double2 *q = reinterpret_cast<double2 *>(Gout) + link * 9;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) q[k] = make_double2(G[k / 3][k % 3].r, G[k / 3][k % 3].i);
+    } else {
+        float2 *q = reinterpret_cast<float2 *>(Gout) + link * 9;
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+            q[k] = make_float2(static_cast<float>(G[k / 3][k % 3].r), static_cast<float>(G[k / 3][k % 3].i));
+    }
+}
+
 template <class SP, bool DAG>
 __global__ void __launch_bounds__(256)
 k_link_grad(const void *__restrict__ U, const void *__restrict__ chi, const void *__restrict__ psi, void *__restrict__ Gout,
@@ -79,70 +128,182 @@ k_link_grad(const void *__restrict__ U, const void *__restrict__ chi, const void
         case 2: grad_mu<2, EF, SP, C>(chi, psi, x4, nb[4], g.Ls, lds, G); break;
         default: grad_mu<3, EF, SP, C>(chi, psi, x4, nb[6], g.Ls, lds, G); break;
     }
-    const C c = static_cast<C>(coef);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) G[k / 3][k % 3] = cscale(c, G[k / 3][k % 3]);
-    if (force_mode) {
-        // F = TA(G U^dagger), TA(A) = (A - A^dagger)/2 - tr(A - A^dagger)/6
-        Cx<C> u[3][3], m[3][3];
-        if constexpr (sizeof(C) == 8)
-            LkF64<3>::load(U, static_cast<size_t>(t), u);
-        else
-            LkF32<3>::load(U, static_cast<size_t>(t), u);
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                Cx<C> s = cmul(G[a][0], cconj(u[b][0]));
-                s = cmac(s, G[a][1], cconj(u[b][1]));
-                s = cmac(s, G[a][2], cconj(u[b][2]));
-                m[a][b] = s;
+    grad_finish(U, Gout, static_cast<size_t>(t), live, coef, force_mode, G);
+}
+
+// The same sums on a tile of 4 x 4 x 2 x 2 sites, for lattices it divides: per s the tile's records of
+// both fields and those of its +x, +y, +z and +t faces (64 + 96 of each) go through LDS, loaded an s
+// ahead, and the four wavefronts (one per mu) read the records of their two sites there. What bounds
+// k_link_grad is the 128-byte lines a CU requests: ten records per site and s, in lines of which a pass over
+// one s uses three quarters; a tile requests five. k_link_grad against this kernel: 16^4 x 8 FP64 136 ->
+// 69 us, FP32 65 -> 45, 16^4 x 16 358 -> 137 and 126 -> 79 us, 24^4 x 4 465 -> 234 and 199 -> 120 us (the
+// bytes it cannot do without take 47 us at 16^4 x 8 in FP64).
+constexpr int kGtSites = 64, kGtRecs = 160;
+
+template <class SP, bool DAG>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_link_grad_tile(const void *__restrict__ U, const void *__restrict__ chi, const void *__restrict__ psi,
+                 void *__restrict__ Gout, GeomDev g, double coef, int force_mode) {
+    using C = typename SP::C;
+    // record pitch in LDS: 208 bytes FP64, 104 FP32 (16- and 8-byte reads of a wavefront on all banks)
+    constexpr int CH = SP::kChunks, PITCH = CH * 16 + 2 * sizeof(C);
+    constexpr int NLD = (kGtRecs * CH + 255) / 256;      // chunks of one field per thread
+    constexpr int EF = DAG ? +1 : -1;
+    extern __shared__ chunk_t grad_smem[];               // chi's records, then psi's
+    char *grad_lds = reinterpret_cast<char *>(grad_smem);
+    const int tid = threadIdx.x, mu = tid >> 6, lane = tid & 63;
+    const int Lx = g.L[0], Ly = g.L[1], Lz = g.L[2], Lt = g.L[3], Ls = g.Ls;
+    int lb = xcd_block(blockIdx.x, gridDim.x);
+    const int x0 = lb % (Lx / 4) * 4;
+    lb /= Lx / 4;
+    const int y0 = lb % (Ly / 4) * 4;
+    lb /= Ly / 4;
+    const int z0 = lb % (Lz / 2) * 2, t0 = lb / (Lz / 2) * 2;
+    auto site = [&](int x, int y, int z, int t) { return ((t * Lz + z) * Ly + y) * Lx + x; };
+    // 4D site of LDS record r: the tile's (x fastest), then the +x, +y, +z and +t faces
+    auto record_site = [&](int r) {
+        int x = r & 3, y = (r >> 2) & 3, z = (r >> 4) & 1, t = (r >> 5) & 1;
+        if (r >= 128) {
+            t = 2;
+        } else if (r >= 96) {
+            t = (r >> 4) & 1;
+            z = 2;
+        } else if (r >= 64) {
+            z = (r >> 2) & 1;
+            t = (r >> 3) & 1;
+            if (r >= 80) {
+                y = 4;
+            } else {
+                y = r & 3;
+                z = (r >> 2) & 1;
+                x = 4;
             }
-        // tr(A - A^dagger) = 2 i Im tr A
-        const C imtr = m[0][0].i + m[1][1].i + m[2][2].i;
+        }
+        x = x0 + x == Lx ? 0 : x0 + x;
+        y = y0 + y == Ly ? 0 : y0 + y;
+        z = z0 + z == Lz ? 0 : z0 + z;
+        t = t0 + t == Lt ? 0 : t0 + t;
+        return site(x, y, z, t);
+    };
+    const int cx = lane & 3, cy = (lane >> 2) & 3, cz = (lane >> 4) & 1, ct = lane >> 5;
+    const int nb = mu == 0   ? (cx < 3 ? lane + 1 : 64 + cy + 4 * cz + 8 * ct)
+                   : mu == 1 ? (cy < 3 ? lane + 4 : 80 + cx + 4 * cz + 8 * ct)
+                   : mu == 2 ? (cz < 1 ? lane + 16 : 96 + cx + 4 * cy + 16 * ct)
+                             : (ct < 1 ? lane + 32 : 128 + cx + 4 * cy + 16 * cz);
+    unsigned off[NLD];   // chunk offset of this thread's loads, s = 0
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+    for (int k = 0; k < NLD; ++k) {
+        const int c = min(k * 256 + tid, kGtRecs * CH - 1), r = c / CH;
+        off[k] = static_cast<unsigned>(record_site(r)) * Ls * CH + (c - r * CH);
+    }
+    const chunk_t *pc = static_cast<const chunk_t *>(chi), *pp = static_cast<const chunk_t *>(psi);
+    chunk_t wc[NLD], wp[NLD];
+    auto issue = [&](int s) {
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                Cx<C> f = {C(0.5) * (m[a][b].r - m[b][a].r), C(0.5) * (m[a][b].i + m[b][a].i)};
-                if (a == b) f.i -= imtr / C(3);
-                G[a][b] = f;
+        for (int k = 0; k < NLD; ++k) {
+            unsigned o = off[k];
+            __asm__("" : "+v"(o));   // else a 64-bit address per load stays live
+            wc[k] = (pc + s * CH)[o];
+            wp[k] = (pp + s * CH)[o];
+        }
+    };
+    // spin K of the projected record r of a field (project(), one spin at a time: 12 registers live
+    // in place of 48)
+    auto half = [&](auto m, auto e, auto kk, int field, int r, Cx<C> h[3]) {
+        constexpr int MU = decltype(m)::value, K = decltype(kk)::value, B = MU < 2 ? 3 - K : 2 + K;
+        constexpr int E = (MU == 1 && K == 0) || (MU == 2 && K == 1) ? -decltype(e)::value : decltype(e)::value;
+        const Cx<C> *v = reinterpret_cast<const Cx<C> *>(grad_lds + (field * kGtRecs + r) * PITCH);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const Cx<C> p = v[K * 3 + a], b = v[B * 3 + a];
+            if (MU == 0 || MU == 2)   // p - i E b
+                h[a] = {E > 0 ? p.r + b.i : p.r - b.i, E > 0 ? p.i - b.r : p.i + b.r};
+            else                      // p + E b
+                h[a] = {E > 0 ? p.r + b.r : p.r - b.r, E > 0 ? p.i + b.i : p.i - b.i};
+        }
+    };
+    Cx<C> G[3][3];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) G[k / 3][k % 3] = {C(0), C(0)};
+    auto add = [&](auto m) {
+        // [(1 + EF gamma) g(x)] psi(x+mu)^dagger (field 0, 1), then psi(x) [(1 - EF gamma) g(x+mu)]^dagger
+        auto term = [&](auto e, auto kk, int field) {
+            Cx<C> a[3], b[3];
+            half(m, e, kk, field, lane, a);
+            half(m, e, kk, 1 - field, nb, b);
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) G[i][j] = cmac(G[i][j], a[i], cconj(b[j]));
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        term(std::integral_constant<int, EF>{}, std::integral_constant<int, 0>{}, 0);
+        term(std::integral_constant<int, EF>{}, std::integral_constant<int, 1>{}, 0);
+        term(std::integral_constant<int, -EF>{}, std::integral_constant<int, 0>{}, 1);
+        term(std::integral_constant<int, -EF>{}, std::integral_constant<int, 1>{}, 1);
+    };
+    auto put = [&](int o, chunk_t v) {
+        typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+        if constexpr (PITCH % 16 == 0) {
+            *reinterpret_cast<chunk_t *>(grad_lds + o) = v;
+        } else {
+            u2v *d = reinterpret_cast<u2v *>(grad_lds + o);
+            d[0] = u2v{v.x, v.y};
+            d[1] = u2v{v.z, v.w};
+        }
+    };
+    issue(0);
+#pragma unroll 1
+    for (int s = 0; s < Ls; ++s) {
+        if (s > 0) __syncthreads();   // the records of s - 1 have been read
+#pragma unroll
+        for (int k = 0; k < NLD; ++k) {
+            const int c = k * 256 + tid, r = c / CH;
+            if (c < kGtRecs * CH) {
+                put(r * PITCH + (c - r * CH) * 16, wc[k]);
+                put((kGtRecs + r) * PITCH + (c - r * CH) * 16, wp[k]);
             }
+        }
+        __syncthreads();
+        if (s + 1 < Ls) issue(s + 1);
+        if (mu == 0) add(std::integral_constant<int, 0>{});
+        else if (mu == 1) add(std::integral_constant<int, 1>{});
+        else if (mu == 2) add(std::integral_constant<int, 2>{});
+        else add(std::integral_constant<int, 3>{});
     }
-    if (!live) return;
-    if constexpr (sizeof(C) == 8) {
-        double2 *q = reinterpret_cast<double2 *>(Gout) + static_cast<size_t>(t) * 9;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) q[k] = make_double2(G[k / 3][k % 3].r, G[k / 3][k % 3].i);
-    } else {
-        float2 *q = reinterpret_cast<float2 *>(Gout) + static_cast<size_t>(t) * 9;
-#pragma unroll
-        for (int k = 0; k < 9; ++k)
-            q[k] = make_float2(static_cast<float>(G[k / 3][k % 3].r), static_cast<float>(G[k / 3][k % 3].i));
+    const size_t link = static_cast<size_t>(site(x0 + cx, y0 + cy, z0 + cz, t0 + ct)) * 4 + mu;
+    grad_finish(U, Gout, link, true, coef, force_mode, G);
+}
+
+// The tile divides the lattice, a field's chunks have 32-bit offsets, and the sum is long enough: FP32
+// fields of Ls = 1 are as fast on k_link_grad (24^4 47.4 against 48.9 us here; FP64 109 against 107, 16^4 28
+// against 22; Ls = 2: FP32 78 against 68, FP64 238 against 141).
+static bool grad_tile_applies(const LinkGradArgs &a) {
+    return a.g.L[0] % 4 == 0 && a.g.L[1] % 4 == 0 && a.g.L[2] % 2 == 0 && a.g.L[3] % 2 == 0 &&
+           static_cast<double>(a.g.n5) * 12 < 4294967296.0 && (a.prec == GRID_F64 || a.g.Ls > 1);
+}
+
+template <class SP, bool DAG>
+static void launch_grad(const LinkGradArgs &a) {
+    const dim3 block(256);
+    if (grad_tile_applies(a)) {
+        const size_t lds = 2 * kGtRecs * (SP::kChunks * 16 + 2 * sizeof(typename SP::C));
+        hipLaunchKernelGGL((k_link_grad_tile<SP, DAG>), dim3(a.g.vol / kGtSites), block, lds, a.stream, a.U, a.chi, a.psi,
+                           a.G, a.g, a.coef, a.force_mode);
+        return;
     }
+    hipLaunchKernelGGL((k_link_grad<SP, DAG>), dim3((a.g.vol + 63) / 64), block, 0, a.stream, a.U, a.chi, a.psi, a.G,
+                       a.g, a.coef, a.force_mode);
 }
 
 hipError_t launch_link_grad(const LinkGradArgs &a) {
     if (a.g.vol == 0) return hipSuccess;
-    const int blocks = (a.g.vol + 63) / 64;
-    const dim3 grid(blocks), block(256);
-    if (a.prec == GRID_F64) {
-        if (a.dag)
-            hipLaunchKernelGGL((k_link_grad<SpF64, true>), grid, block, 0, a.stream, a.U, a.chi, a.psi, a.G, a.g, a.coef,
-                               a.force_mode);
-        else
-            hipLaunchKernelGGL((k_link_grad<SpF64, false>), grid, block, 0, a.stream, a.U, a.chi, a.psi, a.G, a.g,
-                               a.coef, a.force_mode);
-    } else if (a.prec == GRID_F32) {
-        if (a.dag)
-            hipLaunchKernelGGL((k_link_grad<SpF32, true>), grid, block, 0, a.stream, a.U, a.chi, a.psi, a.G, a.g, a.coef,
-                               a.force_mode);
-        else
-            hipLaunchKernelGGL((k_link_grad<SpF32, false>), grid, block, 0, a.stream, a.U, a.chi, a.psi, a.G, a.g,
-                               a.coef, a.force_mode);
-    } else {
+    if (a.prec == GRID_F64)
+        a.dag ? launch_grad<SpF64, true>(a) : launch_grad<SpF64, false>(a);
+    else if (a.prec == GRID_F32)
+        a.dag ? launch_grad<SpF32, true>(a) : launch_grad<SpF32, false>(a);
+    else
         return hipErrorInvalidValue;
-    }
     return hipGetLastError();
 }
 
