@@ -77,8 +77,8 @@ hipError_t launch_dhop(const DhopArgs &a);
 // life of the process; cg.hip).
 hipError_t capture_stream(hipStream_t *s);
 bool walk_mobius_applies(const DhopArgs &a);
-// Tiled time-walk schedule (tile.hip): full-lattice 4D FP32 / FP16-storage fields whose x, y, z
-// extents the tile divides.
+// Tiled time-walk schedule (tile.hip): full-lattice 4D FP16-storage and large FP32 fields
+// whose x, y, z extents the tile divides.
 bool tile_applies(const DhopArgs &a);
 long tile_blocks(const DhopArgs &a);
 hipError_t launch_tile(const DhopArgs &a);

@@ -3,8 +3,8 @@
 // Why a third schedule. The column walk fetches each spinor record once per use (eight times)
 // and each link once per lane, so it requests several times the compulsory bytes per site. Here
 // neighbour reuse happens in LDS instead (Grid's observation, Section 3, that a neighbour spinor
-// is used eight times, turned into on-chip reuse). It serves 4D fields in FP16 storage, where it
-// is the fastest schedule measured.
+// is used eight times, turned into on-chip reuse). It serves 4D fields in FP16 storage and large
+// ones in FP32, where it is the fastest schedule measured.
 //
 // A block owns a TX x TY x TZ tile of (x, y, z) columns, one thread per column (a wavefront per
 // z-plane of the tile), and walks T time slices. Per slice every thread writes its own record
@@ -21,10 +21,13 @@
 // slice, touched the same cache lines (24-byte links of four directions at 96-byte pitch) each time:
 // 12-real 32^4 70 -> 62 us from memory, 58 -> 55 in cache, 18-real 72 -> 56, 24^4 x 18-real 30 -> 26; before
 // that the records' conversion and scaling ahead of the projection, and a last round of blocks a third
-// full: 75.5 -> 70 us, 18-real 79 -> 72.
+// full: 75.5 -> 70 us, 18-real 79 -> 72. FP32: 32^4 138 (direction-parallel) -> 110 us from memory, whose
+// bytes take 99 us.
 //
 // Per site: 8 x (12 + 132) + 7 x 24 = 1320 flops, the convention of the flop counts quoted for
 // this operator.
+#include <math.h>
+
 #include <type_traits>
 
 #include "device.h"
@@ -115,7 +118,7 @@ struct LinkTile {
 };
 
 template <class SP, class LK, bool DAG, int KIND, int FUSE, int TX, int TY, int TZ>
-__global__ void __launch_bounds__(TX * TY * TZ) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(TX * TY * TZ) __attribute__((amdgpu_waves_per_eu(SP::kScaled ? 2 : 1)))
 k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const float *__restrict__ psi_scale, void *out,
             float *out_scale, GeomDev g, TileDev td, double diag, FuseDev fz) {
     using C = typename SP::C;
@@ -303,18 +306,30 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
         rec(nxm, p);
         LK::load(sl + lxm, 0, u);
         hop_rec<0, -EF, true, SP>(acc, p, u);
+        // FP32: a second sum for four of the hops halves the chain of roundings (error at 32^4 7.5e-8 of
+        // the result, with one sum 7.8e-8)
+        [[maybe_unused]] Cx<C> acc2[4][3];
+        if constexpr (!SP::kScaled) {
+#pragma unroll
+            for (int j = 0; j < 12; ++j) acc2[j / 3][j % 3] = {C(0), C(0)};
+        }
+        Cx<C>(&sum2)[4][3] = SP::kScaled ? acc : acc2;
         rec(nyp, p);
         LK::load(sl + lown + LT::LB, 0, u);
-        hop_rec<1, EF, false, SP>(acc, p, u);
+        hop_rec<1, EF, false, SP>(sum2, p, u);
         rec(nym, p);
         LK::load(sl + lym, 0, u);
-        hop_rec<1, -EF, true, SP>(acc, p, u);
+        hop_rec<1, -EF, true, SP>(sum2, p, u);
         rec(nzp, p);
         LK::load(sl + lown + 2 * LT::LB, 0, u);
-        hop_rec<2, EF, false, SP>(acc, p, u);
+        hop_rec<2, EF, false, SP>(sum2, p, u);
         rec(nzm, p);
         LK::load(sl + lzm, 0, u);
-        hop_rec<2, -EF, true, SP>(acc, p, u);
+        hop_rec<2, -EF, true, SP>(sum2, p, u);
+        if constexpr (!SP::kScaled) {
+#pragma unroll
+            for (int j = 0; j < 12; ++j) acc[j / 3][j % 3] = cadd(acc[j / 3][j % 3], acc2[j / 3][j % 3]);
+        }
         // forward time hop psi(x, t + 1) with U_t(x, t); the same link carries the backward time
         // hop of slice t + 1, U_t(x, t)^dagger h(psi(x, t))
         LK::load(sl + lown + 3 * LT::LB, 0, u);
@@ -371,16 +386,24 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
     }
 }
 
-// 4D: tile 8 x 8 x 4 (256 threads). Blocks along t: the count with the least (slices of the longest +
-// 0.7) x (0.5 + m) summed over the rounds of m <= 2 blocks a CU runs at a time. Measured, nseg = 2 / 4 / 6 /
-// 8 / 12 / 16 / 32, 12-real links: 32^4 64 / 55 / 62 / 59 / 65 / 62 / 71 us, 24^4 47 / 28 / 30 / 25 / 26 / 29 us,
-// 16^3 x 64 115 / 60 / 43 / 33 / 26 / 20 / 19 us.
-constexpr int kTX = 8, kTY = 8, kTZ = 4;
-static TileDev tile_dev(const GeomDev &g) {
+// Tiles: 8 x 8 x 4 (256 threads) for FP16 storage, 8 x 8 x 2 for FP32, whose links and records fill the
+// LDS (76 KB; 8 x 8 x 4 takes 134 KB and one block per CU: 32^4 18-real 108 against 110 us, 12-real 105 against
+// 101, 32^3 x 16 51 and 53 against 50 and 51). Two blocks fit a CU. Blocks along t: the count with the least
+// (slices of the longest + 0.7) x (0.5 + m) summed over the rounds of m <= 2 blocks a CU runs at a
+// time. Measured, nseg = 1 / 2 / 4 / 6 / 8 / 12 / 16, 12-real links: FP16 storage 32^4 116 / 64 / 55 / 62 / 59 / 65 /
+// 62 us, 24^4 87 / 47 / 28 / 30 / 25 / 26 / 29 us; FP32 32^4 141 / 101 / 104 / 117 / 114 / 128 / 134 us.
+constexpr int kTX = 8, kTY = 8;
+template <class SP>
+constexpr int kTZ = SP::kScaled ? 4 : 2;
+
+static int tile_z(const DhopArgs &a) { return a.prec == GRID_F16S ? kTZ<SpF16S> : kTZ<SpF32>; }
+
+static TileDev tile_dev(const DhopArgs &a) {
+    const GeomDev &g = a.g;
     TileDev td;
     td.ntx = g.L[0] / kTX;
     td.nty = g.L[1] / kTY;
-    td.ntz = g.L[2] / kTZ;
+    td.ntz = g.L[2] / tile_z(a);
     const long ntiles = static_cast<long>(td.ntx) * td.nty * td.ntz;
     double best = 0.0;
     for (int n = 1; n <= g.L[3]; ++n) {
@@ -394,27 +417,35 @@ static TileDev tile_dev(const GeomDev &g) {
     return td;
 }
 
-// 4D FP16 storage only: with FP32 records and links a block fills the LDS of a CU (134 KB). The column
-// walk takes 93 us and the direction-parallel kernel 132 us at 32^4, against 55 here.
-static bool tile4_applies(const DhopArgs &a) {
-    return !a.custom && a.g.Ls == 1 && a.prec == GRID_F16S && a.g.L[0] % kTX == 0 && a.g.L[1] % kTY == 0 &&
-           a.g.L[2] % kTZ == 0 && (a.kind == GRID_HOP || a.kind == GRID_WILSON);
+// 4D fields the tile divides: all in FP16 storage (32^4: 55 us, the column walk 93, the direction-
+// parallel kernel 132); in FP32 from 500000 sites on where the blocks keep the CUs evenly busy, the
+// mean number of slices of a CU at least 0.93 (12-real: 0.95) of the largest. Tile against the
+// direction-parallel kernel, 18-real / 12-real: 32^4 110 / 101 and 145 / 126 us, 40^4 254 / 233 and 358 / 322, 32^3 x
+// 16 50 / 51 and 59 / 53, 56 x 32 x 24^2 (0.98) 116 / 105 and 141 / 121, 40^2 x 24^2 (0.94) 109 / 102 and 125 / 96,
+// 32^2 x 24^2 (0.90) 68 / 65 and 66 / 61, 24^4 (331776 sites, which the caches hold) 38 / 39 and 35 / 34.
+bool tile_applies(const DhopArgs &a) {
+    if (a.custom || a.g.Ls != 1 || (a.kind != GRID_HOP && a.kind != GRID_WILSON)) return false;
+    if (a.prec != GRID_F16S && a.prec != GRID_F32) return false;
+    if (a.g.L[0] % kTX || a.g.L[1] % kTY || a.g.L[2] % tile_z(a)) return false;
+    if (a.prec == GRID_F16S) return true;
+    const TileDev td = tile_dev(a);
+    const double ntiles = static_cast<double>(td.ntx) * td.nty * td.ntz;
+    const double most = ceil(ntiles * td.nseg / 256.0) * ((a.g.L[3] + td.nseg - 1) / td.nseg);
+    return a.g.n5 >= 500000 && ntiles * a.g.L[3] / 256.0 >= (a.link_fmt == GRID_L12 ? 0.95 : 0.93) * most;
 }
 
-bool tile_applies(const DhopArgs &a) { return tile4_applies(a); }
-
 long tile_blocks(const DhopArgs &a) {
-    const TileDev td = tile_dev(a.g);
+    const TileDev td = tile_dev(a);
     return static_cast<long>(td.ntx) * td.nty * td.ntz * td.nseg;
 }
 
 template <class SP, class LK>
 static hipError_t launch_tile_t(const DhopArgs &a) {
-    const TileDev td = tile_dev(a.g);
-    const dim3 grid(static_cast<unsigned>(tile_blocks(a))), block(kTX * kTY * kTZ);
+    const TileDev td = tile_dev(a);
+    const dim3 grid(static_cast<unsigned>(tile_blocks(a))), block(kTX * kTY * kTZ<SP>);
     hipStream_t st = a.stream;
 #define GRIDMI_LAUNCH(DAG, KIND, FUSE)                                                                          \
-    hipLaunchKernelGGL((k_dhop_tile<SP, LK, DAG, KIND, FUSE, kTX, kTY, kTZ>), grid, block, 0, st, a.U, a.psi,      \
+    hipLaunchKernelGGL((k_dhop_tile<SP, LK, DAG, KIND, FUSE, kTX, kTY, kTZ<SP>>), grid, block, 0, st, a.U, a.psi,      \
                        a.psi_scale, a.out, a.out_scale, a.g, td, a.diag, a.fz)
     if (a.fuse != kFuseNone) {
         switch (a.kind * 4 + a.fuse * 2 + (a.dag ? 1 : 0)) {
@@ -437,6 +468,8 @@ static hipError_t launch_tile_t(const DhopArgs &a) {
 
 hipError_t launch_tile(const DhopArgs &a) {
     switch (a.prec * 2 + a.link_fmt) {
+        case GRID_F32 * 2 + GRID_L18: return launch_tile_t<SpF32, LkF32<3>>(a);
+        case GRID_F32 * 2 + GRID_L12: return launch_tile_t<SpF32, LkF32<2>>(a);
         case GRID_F16S * 2 + GRID_L18: return launch_tile_t<SpF16S, LkF16<3>>(a);
         case GRID_F16S * 2 + GRID_L12: return launch_tile_t<SpF16S, LkF16<2>>(a);
         default: return hipErrorInvalidValue;
