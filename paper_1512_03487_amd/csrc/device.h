@@ -1070,6 +1070,32 @@ __device__ __forceinline__ void half_axpy(Cx<float> acc[4][3], const void *rec, 
     }
 }
 
+// Stores the records A of a wavefront's 64 lanes through LDS (room for 64 records and scales that no
+// other wavefront uses), so that consecutive lanes write consecutive 16 bytes: chunk j 64 + lane of the
+// 64 records goes to byte o[j] of ob, the lane's own scale to *scale. A store of 16 bytes per lane at the
+// record's pitch sends a request per lane to the L2 instead of one per 64 bytes. Returns |A|^2 as stored
+// with N2.
+template <class SP, bool N2>
+__device__ __forceinline__ double wave_store(chunk_t *lds, float *ls, char *ob, const unsigned (&o)[SP::kChunks], float *scale,
+                                             const Cx<typename SP::C> A[4][3]) {
+    const int lane = threadIdx.x & 63;
+    double n = 0.0;
+    if constexpr (N2)
+        n = SP::store_n2(lds, ls, lane, A);
+    else
+        SP::store(lds, ls, lane, A);
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < SP::kChunks; ++j) {
+        unsigned oo = o[j];
+        __asm__("" : "+v"(oo));   // scalar base, 32-bit offset
+        *reinterpret_cast<chunk_t *>(ob + oo) = lds[j * 64 + lane];
+    }
+    if constexpr (SP::kScaled) *scale = ls[lane];
+    wave_sync();
+    return n;
+}
+
 // A link as the A operand of v_mfma_f32_4x4x1 (16 blocks): the four lanes of a block are four s of
 // one 4D site, lane i holds row i of the 3x3 matrix V (V = U or U^dagger; lane 3 repeats row 2, its
 // row of the result is not read), lane j's vector is column j of the B operand, and the block's

@@ -5,20 +5,24 @@
 // the tile's four faces and every link the slice's hops use go through LDS, so the four x and y
 // hops, the fifth-dimension hop and the diagonal read LDS; the two z neighbours are read straight
 // from memory; psi(x, t + 1) is the next slice's own record and the backward t-hop is carried in
-// registers, as in the column walks.
+// registers, as in the column walks. The finished records of a slice leave through LDS (wave_store)
+// before the next slice's take their place there.
 //
 // Why. A CU keeps about 56 vector-L1 misses in flight (requests x latency / time, the same in every
 // schedule measured, a plain copy included), so the time goes with the number of 128-byte lines a
 // site requests times their latency: 6.9 lines in the same-step column walk, which fetches a record
-// for each of its uses, and 4.0 here (FP32, 24^4 x 12; FP16 storage 3.9 and 2.4). Same-step walk
-// against this kernel: 24^4 x 12 FP32 376 -> 335 us, FP16 storage 218 -> 193 us; 16^4 x 16 105 -> 80 us
-// and 59 -> 48 us. What remains is the latency of the lines that miss the L2: at this size a step of
-// the blocks an XCD holds moves as much as its L2, so the z neighbours are mostly fetched again.
-// Moebius (16^4 x 16, column walk against this kernel): FP32 M 107 -> 81 us and M^dagger 99 -> 84, FP16
-// storage 90 -> 60 and 68 -> 56 us: B is applied once to each of the four records a site loads instead
-// of to all eight it hops.
+// for each of its uses, and 4.0 here (FP32, 24^4 x 12; FP16 storage 3.9 and 2.4); and stores of 16 bytes per
+// lane at the record's pitch send 24 million requests to the L2 there, more than the 16.6 million reads,
+// against 6 million through LDS. Same-step walk / this kernel without / with the stores through LDS:
+// 24^4 x 12 FP32 376 / 335 / 272 us from memory, in cache 320 -> 279, FP16 storage 190 -> 185; 16^4 x 16 FP32
+// 105 / 72 / 60 us, FP16 storage 59 / 48 / 46; 16^4 x 8 FP32 40 -> 31 us. Moebius (16^4 x 16): FP32 M 107 (column
+// walk) / 70 / 66 us, FP16 storage 90 / 54 / 56 us: B is applied once to each of the four records a site
+// loads instead of to all eight it hops. What remains is the latency of the lines that miss the L2: at
+// this size a step of the blocks an XCD holds moves as much as its L2, so the z neighbours are mostly
+// fetched again.
 // Tried and not kept: the next slice's loads in registers during the hops (345 against 325 us in
-// FP32, registers spill), streaming stores (580 us), tiles ordered over 2 x 2 x 2 XCD domains (+- 2 %).
+// FP32, registers spill), streaming stores (580 us), tiles ordered over 2 x 2 x 2 XCD domains (+- 2 %),
+// tiles of two z planes (a quarter fewer requests, but one block per CU: 352 against 307 us).
 //
 // The SU(3) products run on the matrix cores: the four lanes of a v_mfma_f32_4x4x1 block are four s
 // of one 4D site and share its link (su3_mfma), which needs Ls to be a multiple of four. A lane then
@@ -71,9 +75,7 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     chunk_t *rec = plane_lds;                                             // own records, then the halo's
     float2 *lks = reinterpret_cast<float2 *>(rec + (NC + NH) * Ls * CH);  // links, FP32, nine to a slot
     float *rsc = reinterpret_cast<float *>(rec + (NC + NH) * Ls * CH + (NS * 72 + 15) / 16);   // scales
-    const int tid = threadIdx.x;
-    const bool act = tid < NT;
-    const int td = act ? tid : 0;   // idle lanes take part in the matrix products
+    const int td = threadIdx.x;   // NT threads, a multiple of 64
     const int Lx = g.L[0], Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
     const int ntx = Lx >> pd.ltx, nty = Ly >> pd.lty, ntile = ntx * nty * Lz;
     const int lb = xcd_block(blockIdx.x, gridDim.x);
@@ -95,13 +97,15 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     [[maybe_unused]] const float wm = (s == 0) ? static_cast<float>(-mf) : 1.0f;
     [[maybe_unused]] const float mb5 = static_cast<float>(b5), mc5 = static_cast<float>(c5);
 
-    // Byte offsets, within a time slice, of this thread's loads: own chunks j NT + tid, halo chunks
-    // j NT + tid, halo scales, one link. (MOBF loads whole records: its own and halo record td.)
-    [[maybe_unused]] unsigned og[CH], hg[KH], hso = 0, ug, hq = 0;
+    // Byte offsets, within a time slice, of this thread's stores (chunks j 64 + lane of the wavefront's
+    // 64 records) and loads: halo chunks j NT + td, halo scales, one link. Its own record it loads whole
+    // (and for MOBF a halo record).
+    constexpr int CM = SP::kChunks;
+    [[maybe_unused]] unsigned og[CM], hg[KH], hso = 0, ug, hq = 0;
 #pragma unroll
-    for (int j = 0; j < CH; ++j) {
-        const int cc = j * NT + td, row = cc / (TX * Ls * CH), off = cc - row * (TX * Ls * CH);
-        og[j] = (((z * Ly + y0 + row) * Lx + x0) * Ls * CH + off) * 16u;
+    for (int j = 0; j < CM; ++j) {
+        const int i = j * 64 + (td & 63), r = (td & ~63) + i / CM, row = r / (TX * Ls);
+        og[j] = ((((z * Ly + y0 + row) * Lx + x0) * Ls + (r - row * (TX * Ls))) * CM + i % CM) * 16u;
     }
     auto halo_col = [&](int hc) -> int {   // first record of a halo column
         int hx, hy;
@@ -118,7 +122,7 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
 #pragma unroll
     for (int j = 0; j < KH; ++j) {
         const int h = j * NT + td, hc = h / (Ls * CH), off = h - hc * (Ls * CH);
-        hg[j] = h < nhc ? (halo_col(hc) * CH + off) * 16u : og[0];
+        hg[j] = h < nhc ? (halo_col(hc) * CH + off) * 16u : static_cast<unsigned>(q) * (CH * 16u);
     }
     if constexpr (MOBF) {
         const int hc = td / Ls;
@@ -172,7 +176,6 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     MatRow u, utf, utb;
     // record n of a slice, straight from memory
     auto direct = [&](int tt, unsigned n, Rec<SP> &r) {
-        constexpr int CM = SP::kChunks;
         const char *b = static_cast<const char *>(psi) + static_cast<size_t>(slice(tt)) * nq * (CM * 16);
         unsigned o = n * (CM * 16u);
         __asm__("" : "+v"(o));
@@ -182,7 +185,14 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
             const chunk_t v = *reinterpret_cast<const chunk_t *>(b + o + j * 16);
             w[j] = make_uint4(v.x, v.y, v.z, v.w);
         }
-        r.set(w, SP::kScaled ? (psi_scale + static_cast<size_t>(slice(tt)) * nq)[n] : 1.0f);
+        float sc = 1.0f;
+        if constexpr (SP::kScaled) {
+            const char *sb = reinterpret_cast<const char *>(psi_scale) + static_cast<size_t>(slice(tt)) * nq * 4;
+            unsigned so = n * 4u;
+            __asm__("" : "+v"(so));
+            sc = *reinterpret_cast<const float *>(sb + so);
+        }
+        r.set(w, sc);
     };
     // the record the hops use: chi = B psi for M, else psi itself
     auto hopped = [&](const Rec<SP> &r, Rec<SL> &h) {
@@ -196,7 +206,23 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
         }
     };
     [[maybe_unused]] Rec<SP> raw;   // MOBF: psi(x, tt); MOBA: psi(x, tt - 1) until out(tt - 1) is finished
+    auto put = [&](int r, const Rec<SL> &x) {
+        if constexpr (SC) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                rec[r * CH + j] = chunk_t{x.w[4 * j], x.w[4 * j + 1], x.w[4 * j + 2], x.w[4 * j + 3]};
+            rsc[r] = x.s;
+        } else {
+            float4 *d = reinterpret_cast<float4 *>(rec + r * CH);
+#pragma unroll
+            for (int j = 0; j < 6; ++j) {
+                const Cx<float> a = x.p[(2 * j) / 3][(2 * j) % 3], b = x.p[(2 * j + 1) / 3][(2 * j + 1) % 3];
+                d[j] = make_float4(a.r, a.i, b.r, b.i);
+            }
+        }
+    };
     auto staged = [&](int r) {
+        __asm__("" : "+v"(r));
         uint4 w[CH];
 #pragma unroll
         for (int k = 0; k < CH; ++k) {
@@ -236,12 +262,10 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
                 A[j / 3][j % 3] = {b.r - al * a.r, b.i - al * a.i};
             }
         }
-        if (act) {
-            if constexpr (FUSE == kFuseNone)
-                SP::store(out, out_scale, o, A);
-            else
-                n2 += SP::store_n2(out, out_scale, o, A);
-        }
+        chunk_t *wl = rec + (td & ~63) * CH;   // free here: own records go to LDS after this
+        n2 += wave_store<SP, FUSE != kFuseNone>(wl, SC ? rsc + (td & ~63) : reinterpret_cast<float *>(wl + 64 * CM),
+                                                static_cast<char *>(out) + static_cast<size_t>(slice(tt)) * nq * (CM * 16),
+                                                og, SP::kScaled ? out_scale + o : nullptr, A);
     };
     {
         // the backward t-hop of slice t0: U_t(x, t0 - 1) and h(psi(x, t0 - 1))
@@ -253,12 +277,12 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
         hs = p.scale();
         Cx<float> w[3][3];
         LK::load(U, (static_cast<size_t>(tm) * V3 + col) * 4 + 3, w);
-        const int i = min(tid & 3, 2);
+        const int i = min(td & 3, 2);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const Cx<float> e = i == 0 ? w[k][0] : i == 1 ? w[k][1] : w[k][2];
-            utb.r[k] = e.r;
-            utb.i[k] = e.i;
+            const float r0 = w[k][0].r, r1 = w[k][1].r, r2 = w[k][2].r, i0 = w[k][0].i, i1 = w[k][1].i, i2 = w[k][2].i;
+            utb.r[k] = i == 0 ? r0 : i == 1 ? r1 : r2;
+            utb.i[k] = i == 0 ? i0 : i == 1 ? i1 : i2;
         }
         utf = utb;
     }
@@ -276,77 +300,67 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
 #pragma unroll
             for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {0.f, 0.f};
             reconstruct_fma<3, -EF, SC>(A, chi, hs);
+            p.renew();
             p.template proj<3, -EF>(hb);
             hs = p.scale();
             if constexpr (KIND == GRID_DWF || MOBF) centre.axpy(A, dgb);
             if constexpr (MOBF) column_shift_axpy<false>(centre, A, static_cast<float>(cs) * fpb, static_cast<float>(cs) * fmb);
             if constexpr (MOBA) raw = centre;
         };
-        if constexpr (MOBF) {
-            Rec<SP> hr;
-            Cx<float> wu[3][3];
-            direct(tt, q, raw);
-            direct(tt, hq, hr);
-            LK::load(static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes), ug, wu);
-            hopped(raw, p);
-            Rec<SL> hp;
-            // a halo record's s is td mod 16, this thread's own
-            hopped(hr, hp);
-            auto put = [&](int r, const Rec<SL> &x) {
-                float4 *d = reinterpret_cast<float4 *>(rec + r * CH);
-#pragma unroll
-                for (int j = 0; j < 6; ++j) {
-                    const Cx<float> a = x.p[(2 * j) / 3][(2 * j) % 3], b = x.p[(2 * j + 1) / 3][(2 * j + 1) % 3];
-                    d[j] = make_float4(a.r, a.i, b.r, b.i);
-                }
-            };
-            put(td, p);
-            if (td < NH * Ls) put(NT + td, hp);
+        // Own record first: the t-hops need no other load.
+        uint32_t wl[LK::kBytes / 4];
+        auto link_load = [&]() {
+            const char *l = static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes) +
+                            static_cast<size_t>(ug) * LK::kBytes;
+            constexpr int al = LK::kBytes % 16 == 0 ? 16 : LK::kBytes % 8 == 0 ? 8 : 4;
+            __builtin_memcpy(wl, __builtin_assume_aligned(l, al), sizeof(wl));
+        };
+        auto link_put = [&]() {
             if (td < NS) {
+                Cx<float> wu[3][3];
+                LK::load(wl, 0, wu);
                 float2 *d = lks + td * 9;
 #pragma unroll
                 for (int e = 0; e < 9; ++e) d[e] = make_float2(wu[e / 3][e % 3].r, wu[e / 3][e % 3].i);
             }
+        };
+        if constexpr (MOBF) {
+            Rec<SP> hr;
+            direct(tt, q, raw);
+            direct(tt, hq, hr);
+            link_load();
+            hopped(raw, p);
             t_hops(raw);
-            __syncthreads();
+            put(td, p);
+            // a halo record's s is td mod 16, this thread's own
+            Rec<SL> hp;
+            hopped(hr, hp);
+            if (td < NH * Ls) put(NT + td, hp);
+            link_put();
         } else {
             const char *b = static_cast<const char *>(psi) + static_cast<size_t>(slice(tt)) * nq * (CH * 16);
-            const char *lk = static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes);
-            chunk_t wo[CH], wh[KH];
-            Cx<float> wu[3][3];
-            float so = 1.f, sh = 1.f;
-#pragma unroll
-            for (int j = 0; j < CH; ++j) wo[j] = load16(b, og[j]);
+            chunk_t wh[KH];
+            float sh = 1.f;
+            direct(tt, q, p);
 #pragma unroll
             for (int j = 0; j < KH; ++j) wh[j] = load16(b, hg[j]);
-            LK::load(lk, ug, wu);
+            if (SC) link_load();
             if constexpr (SC) {
                 const char *sb = reinterpret_cast<const char *>(psi_scale) + static_cast<size_t>(slice(tt)) * nq * 4;
-                so = *reinterpret_cast<const float *>(sb + static_cast<unsigned>(q) * 4u);
                 sh = *reinterpret_cast<const float *>(sb + hso);
             }
-            if (act) {
-#pragma unroll
-                for (int j = 0; j < CH; ++j) rec[j * NT + td] = wo[j];
-#pragma unroll
-                for (int j = 0; j < KH; ++j)
-                    if (j * NT + td < nhc) rec[(CH + j) * NT + td] = wh[j];
-                if (td < NS) {
-                    float2 *d = lks + td * 9;
-#pragma unroll
-                    for (int e = 0; e < 9; ++e) d[e] = make_float2(wu[e / 3][e % 3].r, wu[e / 3][e % 3].i);
-                }
-                if constexpr (SC) {
-                    rsc[td] = so;
-                    if (td < NH * Ls) rsc[NT + td] = sh;
-                }
-            }
-        }
-        if constexpr (!MOBF) {
-            __syncthreads();
-            staged(td);
             t_hops(p);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!SC) link_load();   // FP32: not in registers beside the t-hops' (18 spilled)
+            put(td, p);
+#pragma unroll
+            for (int j = 0; j < KH; ++j)
+                if (j * NT + td < nhc) rec[(CH + j) * NT + td] = wh[j];
+            if constexpr (SC)
+                if (td < NH * Ls) rsc[NT + td] = sh;
+            link_put();
         }
+        __syncthreads();
         Rec<SP> rz;
         direct(tt, q + zpo, rz);   // in flight during the x hops
         if constexpr (KIND == GRID_DWF) {
@@ -396,9 +410,9 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     if constexpr (FUSE != kFuseNone) {
         n2 = wave_sum64(n2);
         __shared__ double fred[4];
-        if ((tid & 63) == 0) fred[tid >> 6] = n2;
+        if ((td & 63) == 0) fred[td >> 6] = n2;
         __syncthreads();
-        if (tid == 0) {
+        if (td == 0) {
             double v = 0.0;
             for (int w = 0; w < static_cast<int>(blockDim.x >> 6); ++w) v += fred[w];
             fz.part[blockIdx.x] = v;
@@ -472,7 +486,7 @@ template <class SP, class LK>
 static hipError_t launch_plane_t(const DhopArgs &a) {
     const bool scaled = plane_scaled(a);
     const PlaneDev d = plane_dev(a.g, scaled);
-    const dim3 grid(static_cast<unsigned>(plane_blocks(a))), block((d.tx * d.ty * a.g.Ls + 63) / 64 * 64);
+    const dim3 grid(static_cast<unsigned>(plane_blocks(a))), block(d.tx * d.ty * a.g.Ls);
     const size_t lds = plane_lds_bytes(d, a.g.Ls, scaled ? 3 : 6, scaled);
     hipStream_t st = a.stream;
 #define GRIDMI_LAUNCH(DAG, KIND, FUSE)                                                                          \
