@@ -14,8 +14,8 @@
 // fifth dimension goes across the DPP row (column_m5inv_row: four steps of doubling in place of 96
 // LDS reads). As in the full-field walk the time goes with the 128-byte lines requested: checkerboard
 // column walk against this kernel, 16^4 x 16, FP16 storage: (d - S)^-1 H 45.7 -> 27.7 us, M with |out|^2
-// 34.6 -> 30 us, M^dagger with r - alpha (...) 38 -> 32 us; FP32 H 48 -> 36 us, with y 57 -> 41 us; 24^4 x 16 H
-// FP32 275 -> 204 us, FP16 storage 137 -> 106 us. The even-odd domain-wall solve at 16^4 x 16: 50.1 -> 40.7 ms.
+// 34.6 -> 30 us, M^dagger with r - alpha (...) 38 -> 32 us; FP32 H 48 -> 33 us, with y 57 -> 40 us; 24^4 x 16 H
+// FP32 275 -> 184 us, FP16 storage 137 -> 106 us. The even-odd domain-wall solve at 16^4 x 16: 50.1 -> 40.7 ms.
 // Tried and not kept: four wavefronts per SIMD (24 to 48 registers spilled: 38 against 28 us).
 #include <math.h>
 
@@ -83,6 +83,19 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
     [[maybe_unused]] const float dgb = static_cast<float>(diag) / bt, csb = -static_cast<float>(cs) / bt;
     [[maybe_unused]] const float mb5 = static_cast<float>(b5), mc5 = static_cast<float>(c5);
 
+    // FP32 records are stored through LDS (wave_store; 16^4 x 16 H 36 -> 33 us, 24^4 x 16 204 -> 184), for which
+    // out(t - 1) is finished before slice t's records go there; FP16-storage ones, at half the pitch, are
+    // as fast stored by their lane (28 against 29 us), and their LDS writes need not wait.
+    constexpr bool STAGE = !SP::kScaled;
+    // Byte offsets, within a slice, of this thread's stores: chunks j 64 + lane of the wavefront's records
+    constexpr int CM = SP::kChunks;
+    [[maybe_unused]] unsigned og[CM];
+#pragma unroll
+    for (int j = 0; j < CM; ++j) {
+        const int i = j * 64 + (td & 63), r = (td & ~63) + i / CM, rc = r / Ls;
+        og[j] = static_cast<unsigned>(((z * plane + (y0 + (rc >> ltx)) * Lxh + x0 + (rc & (TX - 1))) * Ls + (r & (Ls - 1))) * CM +
+                                      i % CM) * 16u;
+    }
     // This thread's halo record (b = 0 and b = 1 slices) and link.
     int hq0 = q, hq1 = q, hb0 = 0;
     {
@@ -139,7 +152,6 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
         return lks + slot * 9;
     };
     auto direct = [&](const void *f, const float *fs, int tt, unsigned n, Rec<SP> &r) {
-        constexpr int CM = SP::kChunks;
         const char *b = static_cast<const char *>(f) + static_cast<size_t>(slice(tt)) * nq * (CM * 16);
         unsigned o = n * (CM * 16u);
         __asm__("" : "+v"(o));
@@ -230,7 +242,11 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
                 A[j / 3][j % 3] = {e.r - al * a.r, e.i - al * a.i};
             }
         }
-        if constexpr (FUSE == kFuseNone)
+        if constexpr (STAGE)   // the wavefront's part of the LDS is free: own records go there after this
+            n2 += wave_store<SP, FUSE != kFuseNone>(rec + (td & ~63) * CH, nullptr,
+                                                    static_cast<char *>(out) + static_cast<size_t>(slice(tt)) * nq * (CM * 16),
+                                                    og, nullptr, A);
+        else if constexpr (FUSE == kFuseNone)
             SP::store(out, out_scale, o, A);
         else
             n2 += SP::store_n2(out, out_scale, o, A);
@@ -259,16 +275,16 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
     for (int k = 0; k < T; ++k) {
         const int tt = t0 + k;
         const int b = (b0 + tt) & 1;
-        Rec<SP> own, yr;
-        direct(psi, psi_scale, tt, q, own);
-        {
-            Rec<SP> hr;
-            Cx<float> wu[3][3];
+        Rec<SP> own, hr, yr;
+        uint32_t wl[LK::kBytes / 4];
+        auto others = [&]() {   // halo record and link
             if (c < NH) direct(psi, psi_scale, tt, (hb0 + tt) & 1 ? hq1 : hq0, hr);
-            if (td < NS)
-                LK::load(static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes),
-                         ug + ((ub + tt) & 1) * 4, wu);
-            hopped(own, p);
+            const char *l = static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes) +
+                            static_cast<size_t>(ug + ((ub + tt) & 1) * 4) * LK::kBytes;
+            constexpr int al = LK::kBytes % 16 == 0 ? 16 : LK::kBytes % 8 == 0 ? 8 : 4;
+            if (td < NS) __builtin_memcpy(wl, __builtin_assume_aligned(l, al), sizeof(wl));
+        };
+        auto put_all = [&]() {
             put(td, p);
             if (c < NH) {
                 Rec<SL> hp;
@@ -276,22 +292,33 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
                 put(NC * Ls + td, hp);
             }
             if (td < NS) {
+                Cx<float> wu[3][3];
+                LK::load(wl, 0, wu);
                 float2 *d = lks + td * 9;
 #pragma unroll
                 for (int e = 0; e < 9; ++e) d[e] = make_float2(wu[e / 3][e % 3].r, wu[e / 3][e % 3].i);
             }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (HASY && !MOBA && SP::kScaled) direct(yv, y_scale, tt, q, yr);
-        if constexpr (HASY && MOBA)
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        direct(psi, psi_scale, tt, q, own);
+        if constexpr (HASY && MOBA && STAGE)
             if (k > 0) direct(yv, y_scale, tt - 1, q, yr);
+        if constexpr (!STAGE) others();
+        hopped(own, p);
+        if constexpr (!STAGE) {
+            put_all();
+            if constexpr (HASY && !MOBA) direct(yv, y_scale, tt, q, yr);
+            if constexpr (HASY && MOBA)
+                if (k > 0) direct(yv, y_scale, tt - 1, q, yr);
+        }
         // finish out(tt - 1) with psi(x, tt) and start the sum of out(tt)
         if (k > 0) {
             hop_mfma<3, EF, false, SL>(A, p, utf);
             finish(tt - 1, yr);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (HASY && !MOBA && !SP::kScaled) direct(yv, y_scale, tt, q, yr);
+        if constexpr (STAGE) others();   // not in registers beside the t-hop's
+        if constexpr (HASY && !MOBA && STAGE) direct(yv, y_scale, tt, q, yr);
         {
             Cx<float> chi[2][3];
             su3_mfma<true>(utb, hb, chi);
@@ -302,6 +329,7 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
             p.template proj<3, -EF>(hb);
             hs = p.scale();
         }
+        if constexpr (STAGE) put_all();
         if constexpr (HASY && !MOBA) {
             yr.axpy(A, dgb);
             column_shift_axpy<DAG>(yr, A, csb * wp, csb * wm);
