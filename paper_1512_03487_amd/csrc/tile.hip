@@ -21,7 +21,7 @@
 // slice, touched the same cache lines (24-byte links of four directions at 96-byte pitch) each time:
 // 12-real 32^4 70 -> 62 us from memory, 58 -> 55 in cache, 18-real 72 -> 56, 24^4 x 18-real 30 -> 26; before
 // that the records' conversion and scaling ahead of the projection, and a last round of blocks a third
-// full: 75.5 -> 70 us, 18-real 79 -> 72. FP32: 32^4 138 (direction-parallel) -> 110 us from memory, whose
+// full: 75.5 -> 70 us, 18-real 79 -> 72. FP32: 32^4 138 (direction-parallel) -> 107 us from memory, whose
 // bytes take 99 us.
 //
 // Per site: 8 x (12 + 132) + 7 x 24 = 1320 flops, the convention of the flop counts quoted for
@@ -196,6 +196,13 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
         }
         lfof = static_cast<unsigned>(((fz0 * Ly + fy) * Lx + fx) * 4 + mu) * LT::LB;
     }
+    // stores: byte offsets, within a slice, of chunks k 64 + lane of the wavefront's records
+    [[maybe_unused]] unsigned oofs[CH];
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+        const int i = k * 64 + lane, r = i / CH;
+        oofs[k] = static_cast<unsigned>(((z * Ly + y0 + r / TX) * Lx + x0 + r % TX) * CH + i % CH) * 16u;
+    }
     // LDS byte offsets of the links: own site, and the backward hops'
     constexpr int FB = N * LT::kPitch;
     const int lown = tid * LT::kPitch;
@@ -362,14 +369,22 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
                 acc[j / 3][j % 3] = {b.r - al * a.r, b.i - al * a.i};
             }
         }
-        if constexpr (FUSE == kFuseNone)
-            SP::store(out, out_scale, q, acc);
-        else
-            n2 += SP::store_n2(out, out_scale, q, acc);
+        if constexpr (SP::kScaled) {
+            if constexpr (FUSE == kFuseNone)
+                SP::store(out, out_scale, q, acc);
+            else
+                n2 += SP::store_n2(out, out_scale, q, acc);
+        }
 #pragma unroll
         for (int j = 0; j < CH; ++j) Pw[j] = Qw[j];
         Ps = Qs;
         __syncthreads();   // the next slice overwrites the records read here
+        // FP32: stored through the wavefront's part of the records (110.5 -> 106.6 us at 32^4); FP16 storage,
+        // at half the pitch, is as fast stored by its lane (61.7 against 62.1 us)
+        if constexpr (!SP::kScaled)
+            n2 += wave_store<SP, FUSE != kFuseNone>(sb + (tid & ~63) * CH, nullptr,
+                                                    static_cast<char *>(out) + static_cast<size_t>(t) * V3 * (CH * 16), oofs,
+                                                    nullptr, acc);
     }
     if constexpr (FUSE != kFuseNone) {
         n2 = wave_sum64(n2);
