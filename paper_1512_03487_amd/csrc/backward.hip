@@ -53,10 +53,9 @@ __device__ __forceinline__ void grad_mu(const void *chi, const void *psi, int x4
     }
 }
 
-// G <- coef G, or its force TA(coef G U^dagger), stored as link `link` if live.
+// G <- coef G of link `link`, or its force TA(coef G U^dagger).
 template <typename C>
-__device__ __forceinline__ void grad_finish(const void *U, void *Gout, size_t link, bool live, double coef, int force_mode,
-                                            Cx<C> G[3][3]) {
+__device__ __forceinline__ void grad_finish(const void *U, size_t link, double coef, int force_mode, Cx<C> G[3][3]) {
     const C c = static_cast<C>(coef);
 #pragma unroll
     for (int k = 0; k < 9; ++k) G[k / 3][k % 3] = cscale(c, G[k / 3][k % 3]);
@@ -86,17 +85,6 @@ __device__ __forceinline__ void grad_finish(const void *U, void *Gout, size_t li
                 if (a == b) f.i -= imtr / C(3);
                 G[a][b] = f;
             }
-    }
-    if (!live) return;
-    if constexpr (sizeof(C) == 8) {
-        double2 *q = reinterpret_cast<double2 *>(Gout) + link * 9;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) q[k] = make_double2(G[k / 3][k % 3].r, G[k / 3][k % 3].i);
-    } else {
-        float2 *q = reinterpret_cast<float2 *>(Gout) + link * 9;
-#pragma unroll
-        for (int k = 0; k < 9; ++k)
-            q[k] = make_float2(static_cast<float>(G[k / 3][k % 3].r), static_cast<float>(G[k / 3][k % 3].i));
     }
 }
 
@@ -128,7 +116,11 @@ k_link_grad(const void *__restrict__ U, const void *__restrict__ chi, const void
         case 2: grad_mu<2, EF, SP, C>(chi, psi, x4, nb[4], g.Ls, lds, G); break;
         default: grad_mu<3, EF, SP, C>(chi, psi, x4, nb[6], g.Ls, lds, G); break;
     }
-    grad_finish(U, Gout, static_cast<size_t>(t), live, coef, force_mode, G);
+    grad_finish(U, static_cast<size_t>(t), coef, force_mode, G);
+    if (!live) return;
+    Cx<C> *q = static_cast<Cx<C> *>(Gout) + static_cast<size_t>(t) * 9;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) q[k] = G[k / 3][k % 3];
 }
 
 // The same sums on a tile of 4 x 4 x 2 x 2 sites, for lattices it divides: per s the tile's records of
@@ -136,8 +128,9 @@ k_link_grad(const void *__restrict__ U, const void *__restrict__ chi, const void
 // ahead, and the four wavefronts (one per mu) read the records of their two sites there. What bounds
 // k_link_grad is the 128-byte lines a CU requests: ten records per site and s, in lines of which a pass over
 // one s uses three quarters; a tile requests five. k_link_grad against this kernel: 16^4 x 8 FP64 136 ->
-// 69 us, FP32 65 -> 45, 16^4 x 16 358 -> 137 and 126 -> 79 us, 24^4 x 4 465 -> 234 and 199 -> 120 us (the
-// bytes it cannot do without take 47 us at 16^4 x 8 in FP64).
+// 69 us, FP32 65 -> 43, 16^4 x 16 358 -> 138 and 126 -> 78 us, 24^4 x 4 465 -> 224 and 199 -> 110 us (the
+// bytes it cannot do without take 47 us at 16^4 x 8 in FP64); with the gradients stored by their lanes
+// 24^4 x 4 took 234 and 120 us.
 constexpr int kGtSites = 64, kGtRecs = 160;
 
 template <class SP, bool DAG>
@@ -272,21 +265,34 @@ k_link_grad_tile(const void *__restrict__ U, const void *__restrict__ chi, const
         else add(std::integral_constant<int, 3>{});
     }
     const size_t link = static_cast<size_t>(site(x0 + cx, y0 + cy, z0 + cz, t0 + ct)) * 4 + mu;
-    grad_finish(U, Gout, link, true, coef, force_mode, G);
+    grad_finish(U, link, coef, force_mode, G);
+    // Stored through LDS, the four sites of a row contiguous: a lane's own 144 bytes at 576-byte pitch
+    // would cost a request to the L2 per 16 of them.
+    __syncthreads();
+    Cx<C> *gl = reinterpret_cast<Cx<C> *>(grad_lds);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) gl[(lane * 4 + mu) * 9 + k] = G[k / 3][k % 3];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const int e = k * 256 + tid, row = e / 144;
+        static_cast<Cx<C> *>(Gout)[static_cast<size_t>(site(x0, y0 + (row & 3), z0 + ((row >> 2) & 1), t0 + (row >> 3))) * 36 +
+                                   (e - row * 144)] = gl[e];
+    }
 }
 
-// The tile divides the lattice, a field's chunks have 32-bit offsets, and the sum is long enough: FP32
-// fields of Ls = 1 are as fast on k_link_grad (24^4 47.4 against 48.9 us here; FP64 109 against 107, 16^4 28
-// against 22; Ls = 2: FP32 78 against 68, FP64 238 against 141).
-static bool grad_tile_applies(const LinkGradArgs &a) {
-    return a.g.L[0] % 4 == 0 && a.g.L[1] % 4 == 0 && a.g.L[2] % 2 == 0 && a.g.L[3] % 2 == 0 &&
-           static_cast<double>(a.g.n5) * 12 < 4294967296.0 && (a.prec == GRID_F64 || a.g.Ls > 1);
+// The tile divides the lattice and a field's chunks have 32-bit offsets. It is the faster kernel for short
+// sums too: Ls = 1, 24^4 FP64 116 (k_link_grad) against 95 us, FP32 51 against 36, 16^4 28 against 19 and 13.5
+// both; Ls = 2, 24^4 238 against 123 and 78 against 53.
+static bool grad_tile_applies(const GeomDev &g) {
+    return g.L[0] % 4 == 0 && g.L[1] % 4 == 0 && g.L[2] % 2 == 0 && g.L[3] % 2 == 0 &&
+           static_cast<double>(g.n5) * 12 < 4294967296.0;
 }
 
 template <class SP, bool DAG>
 static void launch_grad(const LinkGradArgs &a) {
     const dim3 block(256);
-    if (grad_tile_applies(a)) {
+    if (grad_tile_applies(a.g)) {
         const size_t lds = 2 * kGtRecs * (SP::kChunks * 16 + 2 * sizeof(typename SP::C));
         hipLaunchKernelGGL((k_link_grad_tile<SP, DAG>), dim3(a.g.vol / kGtSites), block, lds, a.stream, a.U, a.chi, a.psi,
                            a.G, a.g, a.coef, a.force_mode);
