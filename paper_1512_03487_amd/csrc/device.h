@@ -705,6 +705,39 @@ __device__ __forceinline__ void gather(const void *__restrict__ base, const floa
     stage<SP>(f, lds, p);
 }
 
+// Stores the records A of a wavefront's lanes, consecutive ones (this lane's is rec, idle lanes counting on; live lanes come first).
+// FP32 records go through the wavefront's staging area so that consecutive lanes write consecutive
+// 16 bytes: stored by their lanes, 16 bytes at a time at 96-byte pitch, each piece is a request to the
+// L2 by itself. (FP16-storage records are as fast stored by their lanes.) Returns |A|^2 as stored with N2.
+template <class SP, bool N2>
+__device__ __forceinline__ double store_run(chunk_t *lds, void *out, float *out_scale, size_t rec, bool live,
+                                            const Cx<typename SP::C> A[4][3]) {
+    double n = 0.0;
+    if constexpr (SP::kScaled) {
+        if (live) {
+            if constexpr (N2)
+                n = SP::store_n2(out, out_scale, rec, A);
+            else
+                SP::store(out, out_scale, rec, A);
+        }
+    } else {
+        constexpr int CH = SP::kChunks;
+        const int lane = threadIdx.x & 63, nl = __popcll(__ballot(live)) * CH;
+        if constexpr (N2)
+            n = SP::store_n2(lds, nullptr, lane, A);
+        else
+            SP::store(lds, nullptr, lane, A);
+        if (!live) n = 0.0;
+        wave_sync();
+        chunk_t *o = static_cast<chunk_t *>(out) + (rec - lane) * CH + lane;
+#pragma unroll
+        for (int j = 0; j < CH; ++j)
+            if (j * 64 + lane < nl) o[j * 64] = lds[j * 64 + lane];
+        wave_sync();
+    }
+    return n;
+}
+
 // Fifth-dimension columns inside a wavefront (the Moebius operator's fused passes): when Ls
 // divides 64 and the wavefront's first lane holds s = 0, lanes lbase .. lbase + Ls - 1 hold
 // s = 0 .. Ls - 1 of one 4D site, and the lanes of s + 1 and s - 1 (cyclic in the column) are

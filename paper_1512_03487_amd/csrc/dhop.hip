@@ -665,11 +665,7 @@ k_dhop_walk(const void *__restrict__ U, const void *__restrict__ psi, const floa
                 acc[j / 3][j % 3] = {b.r - al * a.r, b.i - al * a.i};
             }
         }
-        if constexpr (FUSE == kFuseNone) {
-            if (live) SP::store(out, out_scale, static_cast<size_t>(off) + q, acc);
-        } else {
-            if (live) n2 += SP::store_n2(out, out_scale, static_cast<size_t>(off) + q, acc);
-        }
+        n2 += store_run<SP, FUSE != kFuseNone>(lds, out, out_scale, static_cast<size_t>(off) + q, live, acc);
     }
     if constexpr (FUSE != kFuseNone) {
         n2 = wave_sum64(n2);
@@ -811,11 +807,7 @@ k_dhop_walk2(const void *__restrict__ U, const void *__restrict__ psi, const flo
                 A[j / 3][j % 3] = {b.r - al * a.r, b.i - al * a.i};
             }
         }
-        if constexpr (FUSE == kFuseNone) {
-            if (live) SP::store(out, out_scale, static_cast<size_t>(off) + q, A);
-        } else {
-            if (live) n2 += SP::store_n2(out, out_scale, static_cast<size_t>(off) + q, A);
-        }
+        n2 += store_run<SP, FUSE != kFuseNone>(lds, out, out_scale, static_cast<size_t>(off) + q, live, A);
         if (k + 1 == T) break;
         // out(t + 1): backward t-hop U_t(x, t)^dagger h(psi(x, t)), centre, spatial hops
         Cx<C> chi[2][3];
@@ -1043,11 +1035,7 @@ k_dhop_walk_cb(const void *__restrict__ U, const void *__restrict__ psi, const f
                 acc[j / 3][j % 3] = {b.r - al * a.r, b.i - al * a.i};
             }
         }
-        if constexpr (FUSE == kFuseNone) {
-            if (live) SP::store(out, out_scale, static_cast<size_t>(oq), acc);
-        } else {
-            if (live) n2 += SP::store_n2(out, out_scale, static_cast<size_t>(oq), acc);
-        }
+        n2 += store_run<SP, FUSE != kFuseNone>(lds, out, out_scale, static_cast<size_t>(offh) * Ls + q, live, acc);
     }
     if constexpr (FUSE != kFuseNone) {
         n2 = wave_sum64(n2);
