@@ -97,13 +97,10 @@ __device__ __forceinline__ int coarse_of(const MgDims &m, int x4) {
 
 // Sum of one double2 per thread over the block, in a fixed order; every thread gets the result.
 __device__ double2 block_sum2(double2 v, double2 *sm) {
-    sm[threadIdx.x] = v;
+    v = {wave_sum64(v.x), wave_sum64(v.y)};
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = blockDim.x >> 1; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sm[threadIdx.x] = add2(sm[threadIdx.x], sm[threadIdx.x + s]);
-        __syncthreads();
-    }
-    const double2 r = sm[0];
+    const double2 r = add2(add2(sm[0], sm[1]), add2(sm[2], sm[3]));
     __syncthreads();
     return r;
 }
@@ -127,6 +124,9 @@ struct CoarseGeo {
     int nvec;   // G5 split (N / 2)
 };
 
+// The matrices are read once, nothing is reused: what counts is how many loads are in flight. Without dag
+// a thread's elements are G N apart, so eight are loaded ahead of their products: 6^4 sites x N = 24 in FP32
+// (54 MB) 16.4 -> 11.7 us.
 template <typename TA>
 __global__ void __launch_bounds__(kMgThreads)
 k_coarse_stencil(const TA *__restrict__ A, const double2 *__restrict__ v, double2 *__restrict__ out, CoarseGeo cg,
@@ -146,17 +146,24 @@ k_coarse_stencil(const TA *__restrict__ A, const double2 *__restrict__ v, double
     __syncthreads();
     const int g = t / N, i = t - g * N;
     double2 acc = {0.0, 0.0};
-    if (g < G) {
+    if (g < G && !dag) {
+        constexpr int U = 8;
+        const TA *a = A + static_cast<size_t>(xc) * 9 * N * N + t;   // element (p, i) at p N + i
+        int p = g;
+        for (; p + (U - 1) * G < 9 * N; p += U * G, a += U * G * N) {
+            TA w[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) w[k] = a[k * G * N];
+#pragma unroll
+            for (int k = 0; k < U; ++k) acc = add2(acc, cmul2(ld2(w[k]), vnb[p + k * G]));
+        }
+        for (; p < 9 * N; p += G, a += G * N) acc = add2(acc, cmul2(ld2(*a), vnb[p]));
+    } else if (g < G) {
         for (int p = g; p < 9 * N; p += G) {
             const int d = p / N, j = p - d * N;
-            if (!dag) {
-                const double2 a = ld2(A[((static_cast<size_t>(xc) * 9 + d) * N + j) * N + i]);
-                acc = add2(acc, cmul2(a, vnb[p]));
-            } else {
-                const int y = coarse_nb(cg.Lc, xc, opposite(d));
-                const double2 a = ld2(A[((static_cast<size_t>(y) * 9 + d) * N + i) * N + j]);
-                acc = add2(acc, cmulc2(a, vnb[p]));
-            }
+            const int y = coarse_nb(cg.Lc, xc, opposite(d));
+            const double2 a = ld2(A[((static_cast<size_t>(y) * 9 + d) * N + i) * N + j]);
+            acc = add2(acc, cmulc2(a, vnb[p]));
         }
     }
     part[t] = acc;
@@ -236,7 +243,7 @@ k_mg_prolong(const TB *__restrict__ vecs, const double2 *__restrict__ vc, double
 
 // One block per (aggregate, chirality): modified Gram-Schmidt of the nvec restrictions, in place.
 __global__ void __launch_bounds__(kMgThreads) k_mg_orth(double2 *__restrict__ vecs, MgDims m) {
-    __shared__ double2 sm[kMgThreads];
+    __shared__ double2 sm[4];
     const int xc = blockIdx.x >> 1, chi = blockIdx.x & 1;
     const int E = m.nb * 6;
     const size_t vs = static_cast<size_t>(m.vol) * 12;
@@ -399,7 +406,7 @@ k_mg_coarse_col(const double2 *__restrict__ vecs, const double2 *__restrict__ ph
 // ---------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(kMgThreads)
 k_zdot_part(const double2 *__restrict__ a, const double2 *__restrict__ b, long n, double2 *__restrict__ part) {
-    __shared__ double2 sm[kMgThreads];
+    __shared__ double2 sm[4];
     double2 acc = {0.0, 0.0};
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
          i += static_cast<long>(gridDim.x) * kMgThreads)
@@ -412,7 +419,7 @@ k_zdot_part(const double2 *__restrict__ a, const double2 *__restrict__ b, long n
 __global__ void __launch_bounds__(kMgThreads)
 k_zdot2_part(const double2 *__restrict__ a1, const double2 *__restrict__ b1, const double2 *__restrict__ a2,
              const double2 *__restrict__ b2, long n, double2 *__restrict__ part) {
-    __shared__ double2 sm[kMgThreads];
+    __shared__ double2 sm[4];
     double2 c1 = {0.0, 0.0}, c2 = {0.0, 0.0};
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
          i += static_cast<long>(gridDim.x) * kMgThreads) {
@@ -432,7 +439,7 @@ __device__ __forceinline__ double2 up2(float2 v) { return {double(v.x), double(v
 __global__ void __launch_bounds__(kMgThreads)
 k_zdot2_part_f(const float2 *__restrict__ a1, const float2 *__restrict__ b1, const float2 *__restrict__ a2,
                const float2 *__restrict__ b2, long n, double2 *__restrict__ part) {
-    __shared__ double2 sm[kMgThreads];
+    __shared__ double2 sm[4];
     double2 c1 = {0.0, 0.0}, c2 = {0.0, 0.0};
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
          i += static_cast<long>(gridDim.x) * kMgThreads) {
@@ -473,14 +480,14 @@ k_zsub_f(float2 *__restrict__ out, const float2 *__restrict__ a, const float2 *_
         out[i] = {a[i].x - b[i].x, a[i].y - b[i].y};
 }
 
-// One block: thread t adds partials t, t + 256, ... then a tree sum (fixed order).
+// Block b sums set b of the partials into out[b]: thread t adds partials t, t + 256, ... (fixed order).
 __global__ void __launch_bounds__(kMgThreads)
 k_zsum(const double2 *__restrict__ part, int np, double2 *__restrict__ out) {
-    __shared__ double2 sm[kMgThreads];
+    __shared__ double2 sm[4];
     double2 s = {0.0, 0.0};
-    for (int i = threadIdx.x; i < np; i += kMgThreads) s = add2(s, part[i]);
+    for (int i = threadIdx.x; i < np; i += kMgThreads) s = add2(s, part[blockIdx.x * kMgParts + i]);
     s = block_sum2(s, sm);
-    if (threadIdx.x == 0) *out = s;
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // y += a x; if x2: y2 += a2 x2 (two independent updates in one pass)
@@ -547,17 +554,19 @@ k_zscale2(double2 *__restrict__ y, double2 *__restrict__ y2, double s, long n) {
 // Coarse CGNR with device scalars. ctl[0] = stop (tol_c^2 rho_0), ctl[1 + P] = rho entering an
 // iteration of parity P. Partials: pq (<p, q>) and rr (|r|^2), np per set, in `part`.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ double sum_parts(const double *p, int np) {
-    double s = 0.0;
-    for (int i = 0; i < np; ++i) s += p[i];
-    return s;
+// Sum of the partials by the whole block (one thread adding all of them: 280 cycles each, 5 of the 9 us
+// an update of 6^4 x 24 took).
+__device__ __forceinline__ double sum_parts(const double *p, int np, double2 *sm) {
+    double2 s = {0.0, 0.0};
+    for (int i = threadIdx.x; i < np; i += kMgThreads) s.x += p[i];
+    return block_sum2(s, sm).x;
 }
 
 __global__ void __launch_bounds__(kMgThreads)
 k_cdot_re(const double2 *__restrict__ a, const double2 *__restrict__ b, long n, double *__restrict__ part,
           const double *__restrict__ ctl, int par) {
     if (ctl && ctl[1 + par] <= ctl[0]) return;
-    __shared__ double2 sm[kMgThreads];
+    __shared__ double2 sm[4];
     double2 acc = {0.0, 0.0};
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
          i += static_cast<long>(gridDim.x) * kMgThreads)
@@ -577,9 +586,11 @@ k_ccg_start(double2 *__restrict__ p, const double2 *__restrict__ r, double2 *__r
 }
 
 // rho_0 = sum of parts; ctl[0] = tol^2 rho_0; ctl[1] = rho_0
-__global__ void k_ccg_init(const double *__restrict__ part, int np, double tol, double *__restrict__ ctl) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        const double r0 = sum_parts(part, np);
+__global__ void __launch_bounds__(kMgThreads)
+k_ccg_init(const double *__restrict__ part, int np, double tol, double *__restrict__ ctl) {
+    __shared__ double2 sm[4];
+    const double r0 = sum_parts(part, np, sm);
+    if (threadIdx.x == 0) {
         ctl[0] = tol * tol * r0;
         ctl[1] = r0;
     }
@@ -591,8 +602,8 @@ k_ccg_update(double2 *__restrict__ e, double2 *__restrict__ r, const double2 *__
              const double2 *__restrict__ q, long n, const double *__restrict__ pq, double *__restrict__ rr, int np,
              const double *__restrict__ ctl, int par) {
     if (ctl[1 + par] <= ctl[0]) return;
-    __shared__ double2 sm[kMgThreads];
-    const double alpha = ctl[1 + par] / sum_parts(pq, np);
+    __shared__ double2 sm[4];
+    const double alpha = ctl[1 + par] / sum_parts(pq, np, sm);
     double2 acc = {0.0, 0.0};
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
          i += static_cast<long>(gridDim.x) * kMgThreads) {
@@ -614,7 +625,8 @@ k_ccg_p(double2 *__restrict__ p, const double2 *__restrict__ r, long n, const do
         if (blockIdx.x == 0 && threadIdx.x == 0) ctl[1 + (par ^ 1)] = rho;
         return;
     }
-    const double rho2 = sum_parts(rr, np);
+    __shared__ double2 sm[4];
+    const double rho2 = sum_parts(rr, np, sm);
     const double beta = rho2 / rho;
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
          i += static_cast<long>(gridDim.x) * kMgThreads)
@@ -738,9 +750,7 @@ struct MgCtx {
         const int nb = vec_blocks(n);
         hipLaunchKernelGGL(k_zdot2_part_f, dim3(nb), dim3(kMgThreads), 0, st, t, s, t, t, n, part());
         MGCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_zsum, dim3(1), dim3(kMgThreads), 0, st, part(), nb, scal());
-        MGCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_zsum, dim3(1), dim3(kMgThreads), 0, st, part() + kMgParts, nb, scal() + 1);
+        hipLaunchKernelGGL(k_zsum, dim3(2), dim3(kMgThreads), 0, st, part(), nb, scal());
         MGCHK(hipGetLastError());
         hipLaunchKernelGGL(k_mr_step_f, dim3(nb), dim3(kMgThreads), 0, st, z, s, s, t,
                            static_cast<const double2 *>(scal()), n);
@@ -780,9 +790,7 @@ struct MgCtx {
         const int nb = vec_blocks(n);
         hipLaunchKernelGGL(k_zdot2_part, dim3(nb), dim3(kMgThreads), 0, st, a1, b1, a2, b2, n, part());
         MGCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_zsum, dim3(1), dim3(kMgThreads), 0, st, part(), nb, scal());
-        MGCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_zsum, dim3(1), dim3(kMgThreads), 0, st, part() + kMgParts, nb, scal() + 1);
+        hipLaunchKernelGGL(k_zsum, dim3(2), dim3(kMgThreads), 0, st, part(), nb, scal());
         MGCHK(hipGetLastError());
         MGCHK(hipMemcpyAsync(res, scal(), 2 * sizeof(double2), hipMemcpyDeviceToHost, st));
         return hipStreamSynchronize(st);
@@ -799,9 +807,7 @@ struct MgCtx {
         const int nb = vec_blocks(n);
         hipLaunchKernelGGL(k_zdot2_part, dim3(nb), dim3(kMgThreads), 0, st, a1, b1, a2, b2, n, part());
         MGCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_zsum, dim3(1), dim3(kMgThreads), 0, st, part(), nb, scal());
-        MGCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_zsum, dim3(1), dim3(kMgThreads), 0, st, part() + kMgParts, nb, scal() + 1);
+        hipLaunchKernelGGL(k_zsum, dim3(2), dim3(kMgThreads), 0, st, part(), nb, scal());
         return hipGetLastError();
     }
     hipError_t axpy2_dev(double2 *y, const double2 *x, double2 *y2, const double2 *x2, int mode, long n) const {
@@ -981,7 +987,7 @@ static hipError_t mg_cycle(const MgCtx &c, const void *U, const double2 *V, cons
         hipLaunchKernelGGL(k_cdot_re, dim3(nb), dim3(kMgThreads), 0, s, cr, cr, n, rr, static_cast<const double *>(nullptr),
                            0);
         MGCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_ccg_init, dim3(1), dim3(64), 0, s, rr, nb, c.p->coarse_tol, ctl);
+        hipLaunchKernelGGL(k_ccg_init, dim3(1), dim3(kMgThreads), 0, s, rr, nb, c.p->coarse_tol, ctl);
         MGCHK(hipGetLastError());
         for (int i = 0; i < c.p->coarse_iters; ++i) {
             const int P = i & 1;
