@@ -228,9 +228,10 @@ k_mg_restrict(const TB *__restrict__ vecs, const double2 *__restrict__ psi, doub
     }
 }
 
-template <typename TB>
+// The result may be narrowed (TO = float2, for the FP32 smoother).
+template <typename TB, typename TO>
 __global__ void __launch_bounds__(kMgThreads)
-k_mg_prolong(const TB *__restrict__ vecs, const double2 *__restrict__ vc, double2 *__restrict__ out, MgDims m) {
+k_mg_prolong(const TB *__restrict__ vecs, const double2 *__restrict__ vc, TO *__restrict__ out, MgDims m) {
     const long id = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x;
     if (id >= static_cast<long>(m.vol) * 12) return;
     const int x4 = static_cast<int>(id / 12), e = static_cast<int>(id - static_cast<long>(x4) * 12);
@@ -238,7 +239,8 @@ k_mg_prolong(const TB *__restrict__ vecs, const double2 *__restrict__ vc, double
     const double2 *c = vc + static_cast<size_t>(coarse_of(m, x4)) * m.N + chi * m.nvec;
     double2 acc = {0.0, 0.0};
     for (int k = 0; k < m.nvec; ++k) acc = add2(acc, cmul2(ld2(vecs[static_cast<size_t>(k) * m.vol * 12 + id]), c[k]));
-    out[id] = acc;
+    using T = decltype(out[id].x);
+    out[id] = {static_cast<T>(acc.x), static_cast<T>(acc.y)};
 }
 
 // One block per (aggregate, chirality): modified Gram-Schmidt of the nvec restrictions, in place.
@@ -472,12 +474,27 @@ k_mr_step_f(float2 *__restrict__ y, const float2 *__restrict__ x, float2 *__rest
     }
 }
 
-// out = a - b (FP32)
+// z = y + alpha x widened, alpha = sc[0] / Re sc[1] (the last minimal-residual step)
 __global__ void __launch_bounds__(kMgThreads)
-k_zsub_f(float2 *__restrict__ out, const float2 *__restrict__ a, const float2 *__restrict__ b, long n) {
+k_mr_last_f(double2 *__restrict__ z, const float2 *__restrict__ y, const float2 *__restrict__ x,
+            const double2 *__restrict__ sc, long n) {
+    const float ar = static_cast<float>(sc[0].x / sc[1].x), ai = static_cast<float>(sc[0].y / sc[1].x);
+    for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
+         i += static_cast<long>(gridDim.x) * kMgThreads) {
+        const float2 xv = x[i];
+        float2 a = y[i];
+        a.x += ar * xv.x - ai * xv.y;
+        a.y += ar * xv.y + ai * xv.x;
+        z[i] = {double(a.x), double(a.y)};
+    }
+}
+
+// out = a narrowed - b (FP32)
+__global__ void __launch_bounds__(kMgThreads)
+k_zsub_f(float2 *__restrict__ out, const double2 *__restrict__ a, const float2 *__restrict__ b, long n) {
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
          i += static_cast<long>(gridDim.x) * kMgThreads)
-        out[i] = {a[i].x - b[i].x, a[i].y - b[i].y};
+        out[i] = {static_cast<float>(a[i].x) - b[i].x, static_cast<float>(a[i].y) - b[i].y};
 }
 
 // Block b sums set b of the partials into out[b]: thread t adds partials t, t + 256, ... (fixed order).
@@ -490,37 +507,69 @@ k_zsum(const double2 *__restrict__ part, int np, double2 *__restrict__ out) {
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// y += a x; if x2: y2 += a2 x2 (two independent updates in one pass)
+// Minimal-residual step: alpha = sc[0] / Re sc[1] (<t, s> and <t, t>, on the device: no read-back);
+// y += alpha x, y2 -= alpha x2.
 __global__ void __launch_bounds__(kMgThreads)
-k_zaxpy2(double2 *__restrict__ y, const double2 *__restrict__ x, double2 a, double2 *__restrict__ y2,
-         const double2 *__restrict__ x2, double2 a2, long n) {
-    for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
-         i += static_cast<long>(gridDim.x) * kMgThreads) {
-        y[i] = add2(y[i], cmul2(a, x[i]));
-        if (y2) y2[i] = add2(y2[i], cmul2(a2, x2[i]));
-    }
-}
-
-// The same two updates with the coefficient taken from device scalars sc (no read-back):
-// mode 0: y += -sc[0] x, y2 += -sc[0] x2 (Gram-Schmidt, sc[0] = <x, y>);
-// mode 1: alpha = sc[0] / Re sc[1]; y += alpha x, y2 += -alpha x2 (minimal residual,
-//         sc[0] = <t, s>, sc[1] = <t, t>).
-__global__ void __launch_bounds__(kMgThreads)
-k_zaxpy2_dev(double2 *__restrict__ y, const double2 *__restrict__ x, double2 *__restrict__ y2,
-             const double2 *__restrict__ x2, const double2 *__restrict__ sc, int mode, long n) {
-    double2 a, a2;
-    if (mode == 0) {
-        a = {-sc[0].x, -sc[0].y};
-        a2 = a;
-    } else {
-        a = {sc[0].x / sc[1].x, sc[0].y / sc[1].x};
-        a2 = {-a.x, -a.y};
-    }
+k_mr_step(double2 *__restrict__ y, const double2 *__restrict__ x, double2 *__restrict__ y2, const double2 *__restrict__ x2,
+          const double2 *__restrict__ sc, long n) {
+    const double2 a = {sc[0].x / sc[1].x, sc[0].y / sc[1].x}, a2 = {-a.x, -a.y};
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
          i += static_cast<long>(gridDim.x) * kMgThreads) {
         y[i] = add2(y[i], cmul2(a, x[i]));
         y2[i] = add2(y2[i], cmul2(a2, x2[i]));
     }
+}
+
+// A Gram-Schmidt step and the inner products that follow it: y -= sc[0] x, y2 -= sc[0] x2, then with q
+// part[b] = <q, y> (the next step's), else part[b] = <y, y> and part[kMgParts + b] = <y, r>. One pass over y
+// in place of two: 75 -> 65 us at 24^4.
+__global__ void __launch_bounds__(kMgThreads)
+k_gs_step(double2 *__restrict__ y, const double2 *__restrict__ x, double2 *__restrict__ y2,
+          const double2 *__restrict__ x2, const double2 *__restrict__ sc, const double2 *__restrict__ q,
+          const double2 *__restrict__ r, double2 *__restrict__ part, long n) {
+    __shared__ double2 sm[4];
+    const double2 a = {-sc[0].x, -sc[0].y};
+    double2 c1 = {0.0, 0.0}, c2 = {0.0, 0.0};
+    for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
+         i += static_cast<long>(gridDim.x) * kMgThreads) {
+        const double2 v = add2(y[i], cmul2(a, x[i]));
+        y[i] = v;
+        y2[i] = add2(y2[i], cmul2(a, x2[i]));
+        if (q) {
+            c1 = add2(c1, cmulc2(q[i], v));
+        } else {
+            c1 = add2(c1, cmulc2(v, v));
+            c2 = add2(c2, cmulc2(v, r[i]));
+        }
+    }
+    c1 = block_sum2(c1, sm);
+    if (threadIdx.x == 0) part[blockIdx.x] = c1;
+    if (!q) {
+        c2 = block_sum2(c2, sm);
+        if (threadIdx.x == 0) part[kMgParts + blockIdx.x] = c2;
+    }
+}
+
+// The end of a GCR step: w *= s, z *= s, x += a z, r -= a w, part[b] = <r, r>. One pass in place of
+// three: 112 -> 76 us at 24^4.
+__global__ void __launch_bounds__(kMgThreads)
+k_gcr_step(double2 *__restrict__ w, double2 *__restrict__ z, double2 *__restrict__ x, double2 *__restrict__ r, double s,
+           double2 a, double2 *__restrict__ part, long n) {
+    __shared__ double2 sm[4];
+    const double2 ma = {-a.x, -a.y};
+    double2 c = {0.0, 0.0};
+    for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
+         i += static_cast<long>(gridDim.x) * kMgThreads) {
+        const double2 wv = {w[i].x * s, w[i].y * s}, zv = {z[i].x * s, z[i].y * s};
+        w[i] = wv;
+        z[i] = zv;
+        x[i] = add2(x[i], cmul2(a, zv));
+        const double2 rv = add2(r[i], cmul2(ma, wv));
+        r[i] = rv;
+        c = add2(c, cmulc2(rv, rv));
+    }
+    c = block_sum2(c, sm);
+    if (threadIdx.x == 0) part[blockIdx.x] = c;
 }
 
 // out = a - b
@@ -540,14 +589,11 @@ __global__ void __launch_bounds__(kMgThreads) k_zg5(double2 *out, const double2 
     }
 }
 
-// y *= s, y2 *= s
-__global__ void __launch_bounds__(kMgThreads)
-k_zscale2(double2 *__restrict__ y, double2 *__restrict__ y2, double s, long n) {
+// y *= s
+__global__ void __launch_bounds__(kMgThreads) k_zscale(double2 *__restrict__ y, double s, long n) {
     for (long i = static_cast<long>(blockIdx.x) * kMgThreads + threadIdx.x; i < n;
-         i += static_cast<long>(gridDim.x) * kMgThreads) {
+         i += static_cast<long>(gridDim.x) * kMgThreads)
         y[i] = {y[i].x * s, y[i].y * s};
-        if (y2) y2[i] = {y2[i].x * s, y2[i].y * s};
-    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -651,7 +697,7 @@ struct MgLayout {
     size_t r, s, t, u, Z, W;   // fine (Z, W: restart vectors each; u: the pCG preconditioner's)
     size_t rc, ec, cr, cp, cq, cq1;
     size_t part, scal;      // 2 x kMgParts double2, 16 double2
-    size_t z32 = 0, s32 = 0, t32 = 0, r32 = 0, u32 = 0, v32 = 0, a32 = 0;   // FP32 cycle (cycle_prec GRID_F32)
+    size_t z32 = 0, s32 = 0, t32 = 0, u32 = 0, v32 = 0, a32 = 0;   // FP32 cycle (cycle_prec GRID_F32)
     size_t solve_end;
     size_t H, xb, cg, setup_end;   // setup: 8 directional fields, CG solution, CG workspace
     size_t total;
@@ -679,12 +725,11 @@ MgLayout mg_layout(const MgDims &m, int restart, int setup_prec, int cycle_prec)
     L.part = o; o += al256(2 * kMgParts * sizeof(double2));
     L.scal = o; o += al256(16 * sizeof(double2));
     if (cycle_prec == GRID_F32) {
-        // FP32 smoother: z, s, t, r in FP32 and the FP32 links
+        // FP32 smoother: z, s, t in FP32 and the FP32 links
         const size_t hv = al256(static_cast<size_t>(m.vol) * 96);
         L.z32 = o; o += hv;
         L.s32 = o; o += hv;
         L.t32 = o; o += hv;
-        L.r32 = o; o += hv;
         L.u32 = o; o += al256(static_cast<size_t>(m.vol) * 4 * 72);
         L.v32 = o; o += al256(static_cast<size_t>(m.nvec) * m.vol * 96);   // the basis for R and P
         L.a32 = o; o += al256(static_cast<size_t>(m.vc) * 9 * m.N * m.N * sizeof(float2));   // coarse A
@@ -746,14 +791,18 @@ struct MgCtx {
         a.stream = st;
         return launch_dhop(a);
     }
-    hipError_t mr_step_f(float2 *z, float2 *s, const float2 *t, long n) const {
+    // z += alpha s, s -= alpha t, or with last: last = z + alpha s
+    hipError_t mr_step_f(float2 *z, float2 *s, const float2 *t, double2 *last, long n) const {
         const int nb = vec_blocks(n);
         hipLaunchKernelGGL(k_zdot2_part_f, dim3(nb), dim3(kMgThreads), 0, st, t, s, t, t, n, part());
         MGCHK(hipGetLastError());
         hipLaunchKernelGGL(k_zsum, dim3(2), dim3(kMgThreads), 0, st, part(), nb, scal());
         MGCHK(hipGetLastError());
-        hipLaunchKernelGGL(k_mr_step_f, dim3(nb), dim3(kMgThreads), 0, st, z, s, s, t,
-                           static_cast<const double2 *>(scal()), n);
+        const double2 *sc = scal();
+        if (last)
+            hipLaunchKernelGGL(k_mr_last_f, dim3(nb), dim3(kMgThreads), 0, st, last, z, s, sc, n);
+        else
+            hipLaunchKernelGGL(k_mr_step_f, dim3(nb), dim3(kMgThreads), 0, st, z, s, s, t, sc, n);
         return hipGetLastError();
     }
 
@@ -795,7 +844,24 @@ struct MgCtx {
         MGCHK(hipMemcpyAsync(res, scal(), 2 * sizeof(double2), hipMemcpyDeviceToHost, st));
         return hipStreamSynchronize(st);
     }
-    // <a, b> (and <a2, b2>) into the device scalars only, for a following axpy2_dev
+    // the sums of nset sets of partials, read back (waits for the stream)
+    hipError_t sums(int nset, long n, double2 *res) const {
+        hipLaunchKernelGGL(k_zsum, dim3(nset), dim3(kMgThreads), 0, st, part(), vec_blocks(n), scal());
+        MGCHK(hipGetLastError());
+        MGCHK(hipMemcpyAsync(res, scal(), nset * sizeof(double2), hipMemcpyDeviceToHost, st));
+        return hipStreamSynchronize(st);
+    }
+    // y -= scal[0] x, y2 -= scal[0] x2; with q <q, y> into scal[0], else the partials of <y, y>, <y, r>
+    hipError_t gs_step(double2 *y, const double2 *x, double2 *y2, const double2 *x2, const double2 *q, const double2 *r,
+                       long n) const {
+        const int nb = vec_blocks(n);
+        hipLaunchKernelGGL(k_gs_step, dim3(nb), dim3(kMgThreads), 0, st, y, x, y2, x2,
+                           static_cast<const double2 *>(scal()), q, r, part(), n);
+        MGCHK(hipGetLastError());
+        if (q) hipLaunchKernelGGL(k_zsum, dim3(1), dim3(kMgThreads), 0, st, part(), nb, scal());
+        return hipGetLastError();
+    }
+    // <a, b> (and <a2, b2>) into the device scalars only, for a following step
     hipError_t zdot_dev(const double2 *a, const double2 *b, long n) const {
         const int nb = vec_blocks(n);
         hipLaunchKernelGGL(k_zdot_part, dim3(nb), dim3(kMgThreads), 0, st, a, b, n, part());
@@ -810,13 +876,9 @@ struct MgCtx {
         hipLaunchKernelGGL(k_zsum, dim3(2), dim3(kMgThreads), 0, st, part(), nb, scal());
         return hipGetLastError();
     }
-    hipError_t axpy2_dev(double2 *y, const double2 *x, double2 *y2, const double2 *x2, int mode, long n) const {
-        hipLaunchKernelGGL(k_zaxpy2_dev, dim3(vec_blocks(n)), dim3(kMgThreads), 0, st, y, x, y2, x2,
-                           static_cast<const double2 *>(scal()), mode, n);
-        return hipGetLastError();
-    }
-    hipError_t axpy2(double2 *y, const double2 *x, double2 a, double2 *y2, const double2 *x2, double2 a2, long n) const {
-        hipLaunchKernelGGL(k_zaxpy2, dim3(vec_blocks(n)), dim3(kMgThreads), 0, st, y, x, a, y2, x2, a2, n);
+    hipError_t mr_step(double2 *y, const double2 *x, double2 *y2, const double2 *x2, long n) const {
+        hipLaunchKernelGGL(k_mr_step, dim3(vec_blocks(n)), dim3(kMgThreads), 0, st, y, x, y2, x2,
+                           static_cast<const double2 *>(scal()), n);
         return hipGetLastError();
     }
     hipError_t sub(double2 *out, const double2 *a, const double2 *b, long n) const {
@@ -888,7 +950,7 @@ hipError_t launch_mg_prolong(const void *vecs, const void *vc, void *psi, const 
     MgDims m;
     mg_dims(g, p, &m);
     const long n = static_cast<long>(m.vol) * 12;
-    hipLaunchKernelGGL(k_mg_prolong<double2>, dim3(static_cast<unsigned>((n + kMgThreads - 1) / kMgThreads)), dim3(kMgThreads), 0,
+    hipLaunchKernelGGL((k_mg_prolong<double2, double2>), dim3(static_cast<unsigned>((n + kMgThreads - 1) / kMgThreads)), dim3(kMgThreads), 0,
                        st, static_cast<const double2 *>(vecs), static_cast<const double2 *>(vc),
                        static_cast<double2 *>(psi), m);
     return hipGetLastError();
@@ -927,8 +989,7 @@ hipError_t run_mg_basis(const void *U, void *vecs, const GeomDev &g, double mass
                 MGCHK(norm2_diff(x, nullptr, m.vol, part, st, &n2));
                 const double inv = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
                 MGCHK(hipMemcpyAsync(vk, x, static_cast<size_t>(nf) * sizeof(double2), hipMemcpyDeviceToDevice, st));
-                hipLaunchKernelGGL(k_zscale2, dim3(vec_blocks(nf)), dim3(kMgThreads), 0, st, vk,
-                                   static_cast<double2 *>(nullptr), inv, nf);
+                hipLaunchKernelGGL(k_zscale, dim3(vec_blocks(nf)), dim3(kMgThreads), 0, st, vk, inv, nf);
                 MGCHK(hipGetLastError());
             }
     }
@@ -1021,27 +1082,27 @@ static hipError_t mg_cycle(const MgCtx &c, const void *U, const double2 *V, cons
     }
     // z = P e_c
     const long nf = c.nf;
-    if (V32)
-        hipLaunchKernelGGL(k_mg_prolong<float2>, dim3(static_cast<unsigned>((nf + kMgThreads - 1) / kMgThreads)),
-                           dim3(kMgThreads), 0, c.st, V32, ec, z, m);
-    else
-        hipLaunchKernelGGL(k_mg_prolong<double2>, dim3(static_cast<unsigned>((nf + kMgThreads - 1) / kMgThreads)),
-                           dim3(kMgThreads), 0, c.st, V, ec, z, m);
-    MGCHK(hipGetLastError());
-    // MR smoothing on D z = r, in FP32 (cycle_prec): z and r narrowed, z widened after
+    const dim3 gp(static_cast<unsigned>((nf + kMgThreads - 1) / kMgThreads)), gv(vec_blocks(nf)), bt(kMgThreads);
+    // MR smoothing on D z = r, in FP32 (cycle_prec): P e_c and r narrowed where they are made and read, z
+    // widened by the last step (which leaves out the residual's update: nothing reads it)
     if (c.p->smooth_iters > 0 && c.p->cycle_prec == GRID_F32) {
-        float2 *z32 = c.h(c.L.z32), *s32 = c.h(c.L.s32), *t32 = c.h(c.L.t32), *r32 = c.h(c.L.r32);
-        MGCHK(launch_convert_spinor(z, GRID_F64, nullptr, z32, GRID_F32, nullptr, m.vol, c.st));
-        MGCHK(launch_convert_spinor(r, GRID_F64, nullptr, r32, GRID_F32, nullptr, m.vol, c.st));
+        float2 *z32 = c.h(c.L.z32), *s32 = c.h(c.L.s32), *t32 = c.h(c.L.t32);
+        hipLaunchKernelGGL((k_mg_prolong<float2, float2>), gp, bt, 0, c.st, V32, ec, z32, m);
+        MGCHK(hipGetLastError());
         MGCHK(c.D32(z32, t32));
-        hipLaunchKernelGGL(k_zsub_f, dim3(vec_blocks(nf)), dim3(kMgThreads), 0, c.st, s32, r32, t32, nf);
+        hipLaunchKernelGGL(k_zsub_f, gv, bt, 0, c.st, s32, r, t32, nf);
         MGCHK(hipGetLastError());
         for (int it = 0; it < c.p->smooth_iters; ++it) {
             MGCHK(c.D32(s32, t32));
-            MGCHK(c.mr_step_f(z32, s32, t32, nf));
+            MGCHK(c.mr_step_f(z32, s32, t32, it + 1 == c.p->smooth_iters ? z : nullptr, nf));
         }
-        return launch_convert_spinor(z32, GRID_F32, nullptr, z, GRID_F64, nullptr, m.vol, c.st);
+        return hipSuccess;
     }
+    if (V32)
+        hipLaunchKernelGGL((k_mg_prolong<float2, double2>), gp, bt, 0, c.st, V32, ec, z, m);
+    else
+        hipLaunchKernelGGL((k_mg_prolong<double2, double2>), gp, bt, 0, c.st, V, ec, z, m);
+    MGCHK(hipGetLastError());
     if (c.p->smooth_iters > 0) {
         double2 *s = c.f(c.L.s), *t = c.f(c.L.t);
         MGCHK(c.D(U, z, t));
@@ -1050,7 +1111,7 @@ static hipError_t mg_cycle(const MgCtx &c, const void *U, const double2 *V, cons
         for (int it = 0; it < c.p->smooth_iters; ++it) {
             MGCHK(c.D(U, s, t));
             MGCHK(c.zdot2_dev(t, s, t, t, nf));
-            MGCHK(c.axpy2_dev(z, s, s, t, 1, nf));
+            MGCHK(c.mr_step(z, s, s, t, nf));
         }
     }
     return hipSuccess;
@@ -1130,31 +1191,35 @@ hipError_t run_mg_solve(const void *U, const void *vecs, const void *A, const vo
         }
         MGCHK(c.D(U, zk, wk));
         // modified Gram-Schmidt, beta_j = <w_j, w> on the device: w -= beta_j w_j, z -= beta_j z_j
-        for (int j = 0; j < k; ++j) {
-            MGCHK(c.zdot_dev(W(j), wk, nf));
-            MGCHK(c.axpy2_dev(wk, W(j), zk, Z(j), 0, nf));
-        }
-        // |w|^2 and <w, r> in one pass; w, z scaled to |w| = 1, alpha = <w, r> / |w|
+        // with |w|^2 and <w, r> after the last; then w, z scaled to |w| = 1, alpha = <w, r> / |w|
         double2 d2[2];
-        MGCHK(c.zdot2(wk, wk, wk, r, nf, d2));
+        if (k == 0) {
+            MGCHK(c.zdot2(wk, wk, wk, r, nf, d2));
+        } else {
+            MGCHK(c.zdot_dev(W(0), wk, nf));
+            for (int j = 0; j < k; ++j) MGCHK(c.gs_step(wk, W(j), zk, Z(j), j + 1 < k ? W(j + 1) : nullptr, r, nf));
+            MGCHK(c.sums(2, nf, d2));
+        }
         const double nw = d2[0].x;
         if (!(nw > 0.0) || !isfinite(nw)) {
             *status = GRID_EBREAKDOWN;
             break;
         }
         const double inv = 1.0 / sqrt(nw);
-        hipLaunchKernelGGL(k_zscale2, dim3(vec_blocks(nf)), dim3(kMgThreads), 0, st, wk, zk, inv, nf);
-        MGCHK(hipGetLastError());
         const double2 alpha = {d2[1].x * inv, d2[1].y * inv};
-        MGCHK(c.axpy2(xx, zk, alpha, r, wk, {-alpha.x, -alpha.y}, nf));
+        hipLaunchKernelGGL(k_gcr_step, dim3(vec_blocks(nf)), dim3(kMgThreads), 0, st, wk, zk, xx, r, inv, alpha, c.part(),
+                           nf);
+        MGCHK(hipGetLastError());
         ++it;
         ++k;
         if (k == p.restart) {
             k = 0;
             ++stats->reliable_updates;   // restarts
             MGCHK(true_res());
+            MGCHK(c.zdot(r, r, nf, &d));
+        } else {
+            MGCHK(c.sums(1, nf, &d));
         }
-        MGCHK(c.zdot(r, r, nf, &d));
         rn = sqrt(d.x);
     }
     MGCHK(true_res());
