@@ -1225,6 +1225,7 @@ static hipError_t launch_sched(const DhopArgs &a) {
         return hipErrorInvalidValue;
     if (tile_applies(a)) return launch_tile(a);
     if (plane_applies(a)) return launch_plane(a);
+    if (plane64_applies(a)) return launch_plane64(a);
     if (plane_cb_applies(a)) return launch_plane_cb(a);
     // the walks serve FP32 and FP16 storage, the direction-parallel kernel FP64 and FP32 (walk_prec)
     if constexpr (sizeof(typename SP::C) == 4) {
@@ -1238,6 +1239,7 @@ static hipError_t launch_sched(const DhopArgs &a) {
 long dhop_blocks(const DhopArgs &a) {
     if (tile_applies(a)) return tile_blocks(a);
     if (plane_applies(a)) return plane_blocks(a);
+    if (plane64_applies(a)) return plane64_blocks(a);
     if (plane_cb_applies(a)) return plane_cb_blocks(a);
     if (use_walk(a)) {
         const long nbc = (static_cast<long>(a.g.L[0]) * a.g.L[1] * a.g.L[2] * a.g.Ls + 255) / 256;

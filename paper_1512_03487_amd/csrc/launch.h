@@ -77,6 +77,9 @@ hipError_t launch_dhop(const DhopArgs &a);
 // life of the process; cg.hip).
 hipError_t capture_stream(hipStream_t *s);
 bool walk_mobius_applies(const DhopArgs &a);
+// Whether n records or sites of `bytes` (a time slice's records or links) have 32-bit byte offsets, as
+// the tiled schedules form them.
+inline bool offsets32(long n, long bytes) { return n <= 0xffffffffL / bytes; }
 // Tiled time-walk schedule (tile.hip): full-lattice 4D FP16-storage and large FP32 fields
 // whose x, y, z extents the tile divides.
 bool tile_applies(const DhopArgs &a);
@@ -86,6 +89,10 @@ hipError_t launch_tile(const DhopArgs &a);
 bool plane_applies(const DhopArgs &a);
 long plane_blocks(const DhopArgs &a);
 hipError_t launch_plane(const DhopArgs &a);
+// Plane walk on 5D FP64 fields (plane64.hip): H and the domain-wall M.
+bool plane64_applies(const DhopArgs &a);
+long plane64_blocks(const DhopArgs &a);
+hipError_t launch_plane64(const DhopArgs &a);
 // Plane walk on checkerboard fields (plane_cb.hip): 5D FP32 / FP16-storage fields with Ls = 16.
 bool plane_cb_applies(const DhopArgs &a);
 long plane_cb_blocks(const DhopArgs &a);

@@ -471,7 +471,8 @@ bool plane_applies(const DhopArgs &a) {
     PlaneDev d;
     const int least = a.prec == GRID_F16S ? 300000 : 160000;
     const bool kind = a.kind == GRID_HOP || a.kind == GRID_DWF || (a.kind == GRID_MOBIUS && a.g.Ls == 16);
-    return !a.custom && kind && (a.prec == GRID_F32 || a.prec == GRID_F16S) && a.g.n5 >= least && plane_tile(a.g, &d);
+    return !a.custom && kind && (a.prec == GRID_F32 || a.prec == GRID_F16S) && a.g.n5 >= least && plane_tile(a.g, &d) &&
+           offsets32(a.g.n5 / a.g.L[3], 96);
 }
 
 // Whether the block's records lie in LDS as FP16 codes and scales.

@@ -416,7 +416,7 @@ bool plane_cb_applies(const DhopArgs &a) {
     const int least = a.prec == GRID_F16S ? 400000 : 200000;
     return a.custom && a.cb >= 0 && a.kind != GRID_WILSON && (a.prec == GRID_F32 || a.prec == GRID_F16S) &&
            a.g.Ls == kPcLs && a.g.n5 >= least && fabs(a.beta) >= 0x1p-20 && fabs(a.beta) <= 0x1p20 &&
-           plane_cb_dev(a.g).ltx != 0;
+           plane_cb_dev(a.g).ltx != 0 && offsets32(a.g.n5 / a.g.L[3], 48);
 }
 
 long plane_cb_blocks(const DhopArgs &a) {

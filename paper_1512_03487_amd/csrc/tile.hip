@@ -441,7 +441,7 @@ static TileDev tile_dev(const DhopArgs &a) {
 bool tile_applies(const DhopArgs &a) {
     if (a.custom || a.g.Ls != 1 || (a.kind != GRID_HOP && a.kind != GRID_WILSON)) return false;
     if (a.prec != GRID_F16S && a.prec != GRID_F32) return false;
-    if (a.g.L[0] % kTX || a.g.L[1] % kTY || a.g.L[2] % tile_z(a)) return false;
+    if (a.g.L[0] % kTX || a.g.L[1] % kTY || a.g.L[2] % tile_z(a) || !offsets32(a.g.vol / a.g.L[3], 288)) return false;
     if (a.prec == GRID_F16S) return true;
     const TileDev td = tile_dev(a);
     const double ntiles = static_cast<double>(td.ntx) * td.nty * td.ntz;
