@@ -725,11 +725,12 @@ MgLayout mg_layout(const MgDims &m, int restart, int setup_prec, int cycle_prec)
     L.part = o; o += al256(2 * kMgParts * sizeof(double2));
     L.scal = o; o += al256(16 * sizeof(double2));
     if (cycle_prec == GRID_F32) {
-        // FP32 smoother: z, s, t in FP32 and the FP32 links
+        // FP32 smoother: z, s, t in FP32 and the FP32 links (a fourth vector's place stays in the size that
+        // callers allocate)
         const size_t hv = al256(static_cast<size_t>(m.vol) * 96);
         L.z32 = o; o += hv;
         L.s32 = o; o += hv;
-        L.t32 = o; o += hv;
+        L.t32 = o; o += 2 * hv;
         L.u32 = o; o += al256(static_cast<size_t>(m.vol) * 4 * 72);
         L.v32 = o; o += al256(static_cast<size_t>(m.nvec) * m.vol * 96);   // the basis for R and P
         L.a32 = o; o += al256(static_cast<size_t>(m.vc) * 9 * m.N * m.N * sizeof(float2));   // coarse A
