@@ -276,7 +276,7 @@ k_link_exp(void *U, const void *__restrict__ P, double eps, long nlinks) {
         e2 = cscale(inv, a2);
     }
     {
-        // n = 1, with e0 - 1 in e0: the unit is added last, to the small rest of the diagonal
+        // n = 1, with e0 - 1 in e0
         const Cx<double> a0 = cmul(d, e2), a1 = csub(e0, cmul(s, e2)), a2 = cmac(e1, t, e2);
         e0 = a0;
         e1 = a1;
@@ -285,19 +285,20 @@ k_link_exp(void *U, const void *__restrict__ P, double eps, long nlinks) {
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
         Cx<double> x = cmac(cmul(e1, X[k / 3][k % 3]), e2, T[k / 3][k % 3]);
-        if (k % 4 == 0) {
-            x = cadd(x, e0);
-            x.r += 1.0;
-        }
+        if (k % 4 == 0) x = cadd(x, e0);
         E[k / 3][k % 3] = x;
     }
+    // E = exp - 1 throughout, (1 + E)^2 - 1 = 2 E + E E and U + E U: the products' roundings are relative to
+    // the small E (leapfrog at 16^4 off by 1.6e-16; with the unit added before the product 1.9e-16)
     for (int k = 0; k < sq; ++k) {
         mm<false, false>(E, E, T);
 #pragma unroll
-        for (int j = 0; j < 9; ++j) E[j / 3][j % 3] = T[j / 3][j % 3];
+        for (int j = 0; j < 9; ++j) E[j / 3][j % 3] = cadd(cadd(E[j / 3][j % 3], E[j / 3][j % 3]), T[j / 3][j % 3]);
     }
     link_take(fu, tmp, u);
     mm<false, false>(E, u, T);
+#pragma unroll
+    for (int j = 0; j < 9; ++j) T[j / 3][j % 3] = cadd(u[j / 3][j % 3], T[j / 3][j % 3]);
     link_leave(T, tmp);
     chunk_t *out = static_cast<chunk_t *>(U);
 #pragma unroll
