@@ -2,14 +2,15 @@
 //
 // As k_dhop_plane, a block owns a 4 x 4 tile of (x, y) columns at one z with all their s (16 Ls threads, a
 // multiple of 64) and walks slices of t: own records, the tile's faces and the links go through LDS, the z
-// neighbours are read straight from memory, the t-hops come from registers, and the finished records
-// leave through LDS. An FP64 block takes 62 to 112 KB of LDS, so a SIMD holds one wavefront and its
+// neighbours are read straight from memory, psi(x, t + 1) is the next slice's own record, the backward
+// t-hop is carried in registers, and the finished records leave through LDS. An FP64 block takes 62 to 112 KB of LDS, so a SIMD holds one wavefront and its
 // registers hold the next slice's own records, faces and links while this slice's hops run.
 //
 // Why. The direction-parallel kernel spends 5100 vector instructions per 64 sites (eight wavefronts
 // decode every site, 12 of 16 lanes reduce), 69 % of its time at 16^4 x 8, and requests 14 lines of 128 bytes
-// per site; here it is one site per lane and about eight lines. 16^4 x 8 M 104 -> 88 us
-// from memory (91 -> 83 in cache), 24^4 x 8 532 -> 397 us; domain-wall force at 16^4 x 8 177 -> 162 us.
+// per site; here it is one site per lane and about eight lines. 16^4 x 8 M 103 -> 82 us
+// from memory (91 -> 83 in cache), 20^4 x 8 251 -> 182, 24^4 x 8 532 -> 397 in cache; domain-wall force at
+// 16^4 x 8 177 -> 160 us.
 #include <type_traits>
 
 #include "device.h"
@@ -20,7 +21,7 @@ namespace gridmi {
 constexpr int kP6Cols = 16, kP6Halo = 16, kP6Slots = 4 * kP6Cols + kP6Cols + 8;
 
 static size_t plane64_lds_bytes(int Ls) {
-    return (kP6Cols + kP6Halo) * static_cast<size_t>(Ls) * 192 + (kP6Slots + kP6Cols) * 144;
+    return (kP6Cols + kP6Halo) * static_cast<size_t>(Ls) * 192 + kP6Slots * 144;
 }
 
 // acc (spins 2 hf, 2 hf + 1) += f * that half of the record at rec
@@ -45,7 +46,6 @@ k_dhop_plane64(const void *__restrict__ U, const void *__restrict__ psi, void *o
     const int Ls = g.Ls, NT = NC * Ls;
     chunk_t *rec = p64_lds;                                                    // own records, then the halo's
     double2 *lks = reinterpret_cast<double2 *>(rec + (NC + NH) * Ls * CH);     // links of the slice, nine to a slot
-    double2 *ltm = lks + kP6Slots * 9;                                         // U_t of the slice before
     const int td = threadIdx.x;
     const int Lx = g.L[0], Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
     const int ntx = Lx / 4, nty = Ly / 4, ntile = ntx * nty * Lz;
@@ -58,9 +58,6 @@ k_dhop_plane64(const void *__restrict__ U, const void *__restrict__ psi, void *o
     const int zpo = (z == Lz - 1 ? 1 - Lz : 1) * plane * Ls, zmo = (z == 0 ? Lz - 1 : -1) * plane * Ls;
     const int t0 = seg * Lt / nseg, T = (seg + 1) * Lt / nseg - t0;
     constexpr int EF = DAG ? +1 : -1;
-    // out = beta (H psi + (diag psi - S psi) / beta), beta = 1 for H and -1/2 for M
-    constexpr double bt = KIND == GRID_HOP ? 1.0 : -0.5;
-    const double dgb = diag / bt, fpb = -(s == Ls - 1 ? -mf : 1.0) / bt, fmb = -(s == 0 ? -mf : 1.0) / bt;
 
     // byte offsets, within a slice, of the stores (chunk j 64 + lane of the wavefront's records) and of the halo chunks
     unsigned og[CH], hg[CH], ug;
@@ -134,12 +131,23 @@ k_dhop_plane64(const void *__restrict__ U, const void *__restrict__ psi, void *o
 #pragma unroll
         for (int k = 0; k < 9; ++k) u[k / 3][k % 3] = {l[k].x, l[k].y};
     };
-    R A, P;
+    // The two hops of a direction are added to each other first (two), then to the sum, x, y, z, t, as in
+    // the direction-parallel kernel, and the diagonal part comes last: the same chain of roundings.
+    R A, P, two;
     Cx<double> u[3][3], chi_b[2][3];
+    auto clear = [](Cx<double> a[4][3]) {
+#pragma unroll
+        for (int j = 0; j < 12; ++j) a[j / 3][j % 3] = {0.0, 0.0};
+    };
+    auto pair_done = [&]() {
+#pragma unroll
+        for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = cadd(A[j / 3][j % 3], two[j / 3][j % 3]);
+        clear(two);
+        pin(A);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     double n2 = 0.0;
     auto finish = [&](int tt) {
-#pragma unroll
-        for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {bt * A[j / 3][j % 3].r, bt * A[j / 3][j % 3].i};
         if constexpr (FUSE == kFuseAxpy) {
             // r - alpha op psi; r may alias out: a wavefront reads its records before it stores them
             R rv;
@@ -190,28 +198,9 @@ k_dhop_plane64(const void *__restrict__ U, const void *__restrict__ psi, void *o
     for (int k = 0; k < T; ++k) {
         const int tt = t0 + k;
 #pragma unroll
-        for (int j = 0; j < 12; ++j) P[j / 3][j % 3] = Pn[j / 3][j % 3];
-        if (k > 0) {
-            link_of(ltm + c * 9, u);
-            hop_term<3, EF, false>(A, P, u);
-            pin(A);
-            __builtin_amdgcn_sched_barrier(0);
-            finish(tt - 1);
-        }
-#pragma unroll
-        for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {0.0, 0.0};
-        reconstruct_add<3, -EF>(A, chi_b);
-        if constexpr (KIND == GRID_DWF) {
-#pragma unroll
-            for (int j = 0; j < 12; ++j) {
-                Cx<double> &a = A[j / 3][j % 3];
-                a = {a.r + dgb * P[j / 3][j % 3].r, a.i + dgb * P[j / 3][j % 3].i};
-            }
-        }
-#pragma unroll
         for (int j = 0; j < CH; ++j) {
             chunk_t v;
-            __builtin_memcpy(&v, &P[j / 3][j % 3], 16);
+            __builtin_memcpy(&v, &Pn[j / 3][j % 3], 16);
             rec[td * CH + j] = v;
         }
 #pragma unroll
@@ -220,56 +209,61 @@ k_dhop_plane64(const void *__restrict__ U, const void *__restrict__ psi, void *o
         if (NT < kP6Slots && td + NT < kP6Slots)
             put_link(lks + (td + NT) * 9, U, static_cast<size_t>(tt) * V3 * 4 + link_index(td + NT));
         __syncthreads();
-        R p, rz;
-        direct(tt, q + zpo, rz);   // in flight with the next slice's loads during the x hops
+        R p, zp, zm;
+        direct(tt, q + zpo, zp);   // in flight, as the next slice's loads are, during the x and y hops
         direct(tt + 1 == Lt ? 0 : tt + 1, q, Pn);
         if (k + 1 < T) issue(tt + 1);
-        auto hops = [&](auto mu, int rp, int rm, int lp, int lm) {
+        clear(A);
+        clear(two);
+        auto hop = [&](auto mu, auto fwd, int r, int l) {
             constexpr int MU = decltype(mu)::value;
-            staged(rp, p);
-            link_of(lks + lp * 9, u);
-            hop_term<MU, EF, false>(A, p, u);
-            pin(A);
-            __builtin_amdgcn_sched_barrier(0);
-            staged(rm, p);
-            link_of(lks + lm * 9, u);
-            hop_term<MU, -EF, true>(A, p, u);
-            pin(A);
+            constexpr bool F = decltype(fwd)::value;
+            staged(r, p);
+            link_of(lks + l * 9, u);
+            hop_term<MU, F ? EF : -EF, !F>(two, p, u);
+            pin(two);
             __builtin_amdgcn_sched_barrier(0);
         };
-        if constexpr (KIND == GRID_DWF) {
-            constexpr int hup = DAG ? 0 : 1;
-            half_axpy64(A, rec + rsp * CH, hup, fpb);
-            half_axpy64(A, rec + rsm * CH, 1 - hup, fmb);
-        }
-        hops(std::integral_constant<int, 0>{}, nxp, nxm, c * 4, lxm);
+        hop(std::integral_constant<int, 0>{}, std::true_type{}, nxp, c * 4);
+        hop(std::integral_constant<int, 0>{}, std::false_type{}, nxm, lxm);
+        pair_done();
+        direct(tt, q + zmo, zm);
+        hop(std::integral_constant<int, 1>{}, std::true_type{}, nyp, c * 4 + 1);
+        hop(std::integral_constant<int, 1>{}, std::false_type{}, nym, lym);
+        pair_done();
         link_of(lks + (c * 4 + 2) * 9, u);
-        hop_term<2, EF, false>(A, rz, u);
-        pin(A);
+        hop_term<2, EF, false>(two, zp, u);
+        pin(two);
         __builtin_amdgcn_sched_barrier(0);
-        direct(tt, q + zmo, rz);   // in flight during the y hops
-        hops(std::integral_constant<int, 1>{}, nyp, nym, c * 4 + 1, lym);
         link_of(lks + (4 * NC + c) * 9, u);
-        hop_term<2, -EF, true>(A, rz, u);
-        pin(A);
-        __builtin_amdgcn_sched_barrier(0);
-        // U_t(x, tt): the backward t-hop of out(tt + 1) now, the forward one of out(tt) from ltm
+        hop_term<2, -EF, true>(two, zm, u);
+        pair_done();
+        // t: forward with psi(x, t + 1), the next slice's own record; the same link and psi(x, t) give the
+        // next slice's backward hop
+        link_of(lks + (c * 4 + 3) * 9, u);
+        hop_term<3, EF, false>(two, Pn, u);
+        reconstruct_add<3, -EF>(two, chi_b);
+        pair_done();
+        staged(td, P);
         {
             Cx<double> hb[2][3];
-            link_of(lks + (c * 4 + 3) * 9, u);
             project<3, -EF>(P, hb);
             su3_adj_mul(u, hb, chi_b);
         }
-        if (s == 0)
+        if constexpr (KIND == GRID_DWF) {
+            constexpr int hup = DAG ? 0 : 1;
 #pragma unroll
-            for (int k9 = 0; k9 < 9; ++k9) ltm[c * 9 + k9] = make_double2(u[k9 / 3][k9 % 3].r, u[k9 / 3][k9 % 3].i);
-        __syncthreads();   // the next slice overwrites what was read here
-    }
-    {
-        const int tl = t0 + T - 1;
-        link_of(ltm + c * 9, u);
-        hop_term<3, EF, false>(A, Pn, u);
-        finish(tl);
+            for (int j = 0; j < 12; ++j) {
+                Cx<double> &a = A[j / 3][j % 3];
+                // diag psi rounded, then - H psi / 2, as the direction-parallel kernel's multiply-adds are formed
+                a = {__builtin_fma(-0.5, a.r, diag * P[j / 3][j % 3].r), __builtin_fma(-0.5, a.i, diag * P[j / 3][j % 3].i)};
+            }
+            half_axpy64(A, rec + rsp * CH, hup, s == Ls - 1 ? mf : -1.0);
+            half_axpy64(A, rec + rsm * CH, 1 - hup, s == 0 ? mf : -1.0);
+        }
+        pin(A);
+        __syncthreads();   // what the slice read is free: the stores and the next slice go there
+        finish(tt);
     }
     if constexpr (FUSE != kFuseNone) {
         n2 = wave_sum64(n2);

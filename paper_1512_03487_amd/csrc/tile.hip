@@ -303,45 +303,57 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
             issue_links(tn);
         }
         auto rec = [&](int slot, Rec<SP> &q) { lds_record<SP>(sb, sbs, slot, q); };
+        // FP32: the two hops of a direction are added to each other first, then to the sum, which keeps the
+        // chain of roundings as short as the direction-parallel kernel's (error at 32^4 7.4e-8 of the
+        // result; one chain of eight 7.8e-8)
+        constexpr bool PAIR = !SP::kScaled;
         Cx<C> acc[4][3];
+        [[maybe_unused]] Cx<C> two[4][3];
+        Cx<C>(&sum)[4][3] = PAIR ? two : acc;
+        auto clear = [](Cx<C> a[4][3]) {
 #pragma unroll
-        for (int j = 0; j < 12; ++j) acc[j / 3][j % 3] = {C(0), C(0)};
-        reconstruct_fma<3, -EF, SP::kScaled>(acc, chi_b, chi_s);
+            for (int j = 0; j < 12; ++j) a[j / 3][j % 3] = {C(0), C(0)};
+        };
+        auto pair_done = [&]() {
+            if constexpr (PAIR) {
+#pragma unroll
+                for (int j = 0; j < 12; ++j) acc[j / 3][j % 3] = cadd(acc[j / 3][j % 3], two[j / 3][j % 3]);
+                clear(two);
+            }
+        };
+        clear(acc);
+        if constexpr (PAIR)
+            clear(two);
+        else
+            reconstruct_fma<3, -EF, SP::kScaled>(acc, chi_b, chi_s);
         rec(nxp, p);
         LK::load(sl + lown, 0, u);
-        hop_rec<0, EF, false, SP>(acc, p, u);
+        hop_rec<0, EF, false, SP>(sum, p, u);
         rec(nxm, p);
         LK::load(sl + lxm, 0, u);
-        hop_rec<0, -EF, true, SP>(acc, p, u);
-        // FP32: a second sum for four of the hops halves the chain of roundings (error at 32^4 7.5e-8 of
-        // the result, with one sum 7.8e-8)
-        [[maybe_unused]] Cx<C> acc2[4][3];
-        if constexpr (!SP::kScaled) {
-#pragma unroll
-            for (int j = 0; j < 12; ++j) acc2[j / 3][j % 3] = {C(0), C(0)};
-        }
-        Cx<C>(&sum2)[4][3] = SP::kScaled ? acc : acc2;
+        hop_rec<0, -EF, true, SP>(sum, p, u);
+        pair_done();
         rec(nyp, p);
         LK::load(sl + lown + LT::LB, 0, u);
-        hop_rec<1, EF, false, SP>(sum2, p, u);
+        hop_rec<1, EF, false, SP>(sum, p, u);
         rec(nym, p);
         LK::load(sl + lym, 0, u);
-        hop_rec<1, -EF, true, SP>(sum2, p, u);
+        hop_rec<1, -EF, true, SP>(sum, p, u);
+        pair_done();
         rec(nzp, p);
         LK::load(sl + lown + 2 * LT::LB, 0, u);
-        hop_rec<2, EF, false, SP>(sum2, p, u);
+        hop_rec<2, EF, false, SP>(sum, p, u);
         rec(nzm, p);
         LK::load(sl + lzm, 0, u);
-        hop_rec<2, -EF, true, SP>(sum2, p, u);
-        if constexpr (!SP::kScaled) {
-#pragma unroll
-            for (int j = 0; j < 12; ++j) acc[j / 3][j % 3] = cadd(acc[j / 3][j % 3], acc2[j / 3][j % 3]);
-        }
+        hop_rec<2, -EF, true, SP>(sum, p, u);
+        pair_done();
         // forward time hop psi(x, t + 1) with U_t(x, t); the same link carries the backward time
         // hop of slice t + 1, U_t(x, t)^dagger h(psi(x, t))
         LK::load(sl + lown + 3 * LT::LB, 0, u);
         p.set(Qw, Qs);
-        hop_rec<3, EF, false, SP>(acc, p, u);
+        if constexpr (PAIR) reconstruct_fma<3, -EF, SP::kScaled>(two, chi_b, chi_s);
+        hop_rec<3, EF, false, SP>(sum, p, u);
+        pair_done();
         rec(own, p);   // the centre psi(x, t), as staged
         if constexpr (KIND != GRID_HOP) {
             // D = (4 + m) - H/2
