@@ -43,9 +43,9 @@ TRAFFIC_FILES = {
     "dwf_24^4x12_f16s_L18": os.path.join(ROOT, "profiles", "traffic_dwf_f16s_L18_24x24x24x24_ls12.txt"),
 }
 ORACLE_CG_FILE = os.path.join(ROOT, "profiles", "oracle_cg_dwf_16x16x16x16_ls16.txt")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1512_03487_amd", "csrc", f) for f in ("dhop.hip", "device.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1512_03487_amd", "csrc", f) for f in ("dhop.hip", "tile.hip", "plane.hip", "device.h")]
 HEAD_DIMS = (32, 32, 32, 32)
-HEAD_KERNEL = "k_dhop_dir<SpF32, LkF32<3>, hop>"
+HEAD_KERNEL = "k_dhop_tile<SpF32, LkF32<3>, hop>"
 
 
 def progress(msg: str) -> None:
@@ -872,10 +872,10 @@ def dwf_config5(calibrate_copy=False):
     bytes: psi and out once per 5D site, the links once per 4D site)."""
     import torch
     out = {"workload": "domain-wall operator M, 24^4 x Ls = 12, M5 = 1.8, mf = 0.01, Haar links, Gaussian spinor"}
-    for name, prec, fmt, kern in (("f32", "f32", "L18", "k_dhop_walk2<SpF32, LkF32<3>, false, GRID_DWF, 0>"),
-                                  ("f16s_L12", "f16s", "L12", "k_dhop_walk2<SpF16S, LkF16<2>, false, GRID_DWF, 0>"),
-                                  ("f16s_L18", "f16s", "L18", "k_dhop_walk2<SpF16S, LkF16<3>, false, GRID_DWF, 0>"),
-                                  ("f32_L12", "f32", "L12", "k_dhop_walk2<SpF32, LkF32<2>, false, GRID_DWF, 0>")):
+    for name, prec, fmt, kern in (("f32", "f32", "L18", "k_dhop_plane<SpF32, LkF32<3>, false, GRID_DWF, 0>"),
+                                  ("f16s_L12", "f16s", "L12", "k_dhop_plane<SpF16S, LkF16<2>, false, GRID_DWF, 0>"),
+                                  ("f16s_L18", "f16s", "L18", "k_dhop_plane<SpF16S, LkF16<3>, false, GRID_DWF, 0>"),
+                                  ("f32_L12", "f32", "L12", "k_dhop_plane<SpF32, LkF32<2>, false, GRID_DWF, 0>")):
         r = leg((24, 24, 24, 24), prec, fmt, "dwf", 12, 20, 3)
         key = f"dwf_24^4x12_{name}"
         traffic = measured_traffic(key) if key in TRAFFIC_FILES else None

@@ -1207,7 +1207,8 @@ static hipError_t launch_walk_cb(const DhopArgs &a) {
 }
 
 // Schedules: the plane walk (plane.hip) for the plain operators on 5D FP32 and FP16-storage fields
-// its tiles divide and its checkerboard form (plane_cb.hip) for Ls = 16; the tiled walk (tile.hip) for
+// its tiles divide, its checkerboard form (plane_cb.hip) for Ls = 16 and its form for large 5D FP64
+// fields (plane64.hip); the tiled walk (tile.hip) for
 // 4D FP16-storage and large FP32 fields; column walks for the other FP16-storage and 5D FP32 fields
 // (full lattice, or checkerboard fields in the even-odd form); direction-parallel otherwise (measured
 // faster there). The full-lattice walk also takes the custom form with a separate y and beta = -1/2

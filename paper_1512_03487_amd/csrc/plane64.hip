@@ -3,8 +3,9 @@
 // As k_dhop_plane, a block owns a 4 x 4 tile of (x, y) columns at one z with all their s (16 Ls threads, a
 // multiple of 64) and walks slices of t: own records, the tile's faces and the links go through LDS, the z
 // neighbours are read straight from memory, psi(x, t + 1) is the next slice's own record, the backward
-// t-hop is carried in registers, and the finished records leave through LDS. An FP64 block takes 62 to 112 KB of LDS, so a SIMD holds one wavefront and its
-// registers hold the next slice's own records, faces and links while this slice's hops run.
+// t-hop is carried in registers, and the finished records leave through LDS. A block takes 37 (Ls = 4) to
+// 111 KB of LDS, so a SIMD holds one wavefront, and its registers hold the next slice's own records, faces
+// and links while this slice's hops run.
 //
 // Why. The direction-parallel kernel spends 5100 vector instructions per 64 sites (eight wavefronts
 // decode every site, 12 of 16 lanes reduce), 69 % of its time at 16^4 x 8, and requests 14 lines of 128 bytes
