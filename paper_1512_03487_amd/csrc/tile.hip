@@ -416,17 +416,22 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
 // Tiles: 8 x 8 x 4 (256 threads) for FP16 storage, 8 x 8 x 2 for FP32, whose links and records fill the
 // LDS (76 KB; 8 x 8 x 4 takes 134 KB and one block per CU: 32^4 18-real 108 against 110 us, 12-real 105 against
 // 101, 32^3 x 16 51 and 53 against 50 and 51). Two blocks fit a CU. Blocks along t: the count with the least
-// (slices of the longest + 0.7) x (0.5 + m) summed over the rounds of m <= 2 blocks a CU runs at a
-// time. Measured, nseg = 1 / 2 / 4 / 6 / 8 / 12 / 16, 12-real links: FP16 storage 32^4 116 / 64 / 55 / 62 / 59 / 65 /
-// 62 us, 24^4 87 / 47 / 28 / 30 / 25 / 26 / 29 us; FP32 32^4 141 / 101 / 104 / 117 / 114 / 128 / 134 us.
+// (slices of the longest + start) x the sum over the rounds of blocks a CU runs at a time, 2.5 for two and
+// `alone` for one; start and alone as measured, FP32's longer prefetch weighing more. nseg = 1 / 2 / 4 / 6 / 8 /
+// 12 / 16, 12-real links: FP16 storage 32^4 116 / 64 / 55 / 62 / 59 / 65 / 62 us, 24^4 87 / 47 / 28 / 30 / 25 / 26 /
+// 29; FP32 32^4 141 / 101 / 104 / 117 / 114 / 128 / 134 us. FP16 storage, two blocks of one slice against one of two:
+// 16 x 24 x 12 x 28 nseg 28 / 14 10.6 / 11.7 us, 16^2 x 20 x 24 nseg 24 / 12 10.6 / 11.5; three of one against two of
+// two: 24^2 x 20 x 16 nseg 16 / 8 17.3 / 18.8 us.
 constexpr int kTX = 8, kTY = 8;
 template <class SP>
 constexpr int kTZ = SP::kScaled ? 4 : 2;
 
 static int tile_z(const DhopArgs &a) { return a.prec == GRID_F16S ? kTZ<SpF16S> : kTZ<SpF32>; }
 
-static TileDev tile_dev(const DhopArgs &a) {
+// share: the slices of an evenly spread lattice over those the model charges (at least one).
+static TileDev tile_dev(const DhopArgs &a, double *share = nullptr) {
     const GeomDev &g = a.g;
+    const double start = a.prec == GRID_F16S ? 0.4 : 0.7, alone = a.prec == GRID_F16S ? 1.5 : 1.8;
     TileDev td;
     td.ntx = g.L[0] / kTX;
     td.nty = g.L[1] / kTY;
@@ -435,30 +440,31 @@ static TileDev tile_dev(const DhopArgs &a) {
     double best = 0.0;
     for (int n = 1; n <= g.L[3]; ++n) {
         const long m = (ntiles * n + 255) / 256, rem = m % 2;
-        const double cost = ((g.L[3] + n - 1) / n + 0.7) * ((m / 2) * 2.5 + (rem ? 1.5 : 0.0));
+        const double cost = ((g.L[3] + n - 1) / n + start) * ((m / 2) * 2.5 + (rem ? alone : 0.0));
         if (n == 1 || cost < best) {
             best = cost;
             td.nseg = n;
         }
     }
+    if (share) *share = static_cast<double>(ntiles) * g.L[3] / 256.0 * 1.25 / best;
     return td;
 }
 
 // 4D fields the tile divides: all in FP16 storage (32^4: 55 us, the column walk 93, the direction-
-// parallel kernel 132); in FP32 from 500000 sites on where the blocks keep the CUs evenly busy, the
-// mean number of slices of a CU at least 0.93 (12-real: 0.95) of the largest. Tile against the
-// direction-parallel kernel, 18-real / 12-real: 32^4 110 / 101 and 145 / 126 us, 40^4 254 / 233 and 358 / 322, 32^3 x
-// 16 50 / 51 and 59 / 53, 56 x 32 x 24^2 (0.98) 116 / 105 and 141 / 121, 40^2 x 24^2 (0.94) 109 / 102 and 125 / 96,
-// 32^2 x 24^2 (0.90) 68 / 65 and 66 / 61, 24^4 (331776 sites, which the caches hold) 38 / 39 and 35 / 34.
+// parallel kernel 132); in FP32 from 500000 sites on (24^4, 331776 sites, which the caches hold, 38 / 39 us
+// here with 18- / 12-real links, 35 / 34 there) where the blocks keep the CUs evenly busy: a share of at least
+// 0.78 (18-real) or 0.815 (12-real). Direction-parallel / tile from memory, 18-real and 12-real, by share:
+// 56 x 32 x 24^2 (0.91) 142 / 125, 128 / 110 us, 32 x 24 x 28 x 26 (0.88) 80 / 65, 73 / 61, 40^2 x 24^2 (0.82) 128 / 117,
+// 116 / 108, 32^2 x 20 x 28 (0.82) 82 / 69, 74 / 65, 32^2 x 24^2 (0.81) 87 / 83, 75 / 76, 24^2 x 32 x 30 (0.79) 76 / 67,
+// 69 / 65.
 bool tile_applies(const DhopArgs &a) {
     if (a.custom || a.g.Ls != 1 || (a.kind != GRID_HOP && a.kind != GRID_WILSON)) return false;
     if (a.prec != GRID_F16S && a.prec != GRID_F32) return false;
     if (a.g.L[0] % kTX || a.g.L[1] % kTY || a.g.L[2] % tile_z(a) || !offsets32(a.g.vol / a.g.L[3], 288)) return false;
     if (a.prec == GRID_F16S) return true;
-    const TileDev td = tile_dev(a);
-    const double ntiles = static_cast<double>(td.ntx) * td.nty * td.ntz;
-    const double most = ceil(ntiles * td.nseg / 256.0) * ((a.g.L[3] + td.nseg - 1) / td.nseg);
-    return a.g.n5 >= 500000 && ntiles * a.g.L[3] / 256.0 >= (a.link_fmt == GRID_L12 ? 0.95 : 0.93) * most;
+    double share;
+    tile_dev(a, &share);
+    return a.g.n5 >= 500000 && share >= (a.link_fmt == GRID_L12 ? 0.815 : 0.78);
 }
 
 long tile_blocks(const DhopArgs &a) {
