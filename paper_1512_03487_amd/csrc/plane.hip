@@ -1,7 +1,7 @@
 // Plane walk of the hopping operator on 5D fields (FP32 and FP16 storage, gfx950).
 //
 // A block owns a TX x TY tile of (x, y) columns at one z with all their s (one thread per 5D
-// column, s fastest, TX TY Ls <= 256 threads) and walks T time slices. Per slice its own records,
+// column, s fastest, TX TY Ls <= 384 threads) and walks T time slices. Per slice its own records,
 // the tile's four faces and every link the slice's hops use go through LDS, so the four x and y
 // hops, the fifth-dimension hop and the diagonal read LDS; the two z neighbours are read straight
 // from memory; psi(x, t + 1) is the next slice's own record and the backward t-hop is carried in
@@ -53,7 +53,7 @@ static size_t plane_lds_bytes(const PlaneDev &d, int Ls, int chunks, bool scaled
 // Registers: three wavefronts per SIMD, two for the Moebius operators with FP32 records in LDS, of
 // which two blocks fit a CU in any case (their 17 to 31 spilled registers at three).
 template <class SP, class LK, bool DAG, int KIND, int FUSE>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(384)
 __attribute__((amdgpu_waves_per_eu(KIND == GRID_MOBIUS && !(SP::kScaled && DAG) ? 2 : 3)))
 k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const float *__restrict__ psi_scale, void *out,
              float *out_scale, GeomDev g, PlaneDev pd, double diag, double mf, double cs, double b5, double c5,
@@ -409,7 +409,7 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     }
     if constexpr (FUSE != kFuseNone) {
         n2 = wave_sum64(n2);
-        __shared__ double fred[4];
+        __shared__ double fred[6];
         if ((td & 63) == 0) fred[td >> 6] = n2;
         __syncthreads();
         if (td == 0) {
@@ -420,10 +420,11 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     }
 }
 
-// Tile: 4 x 4 columns for Ls = 12 and 16, 8 x 4 (or 4 x 8) for Ls = 8, so that a block has 192 or
-// 256 threads, the halo no more columns than the tile and a slice's links no more than the threads.
+// Tile: 4 x 4 columns for Ls = 12 to 24, 8 x 4 (or 4 x 8) for Ls = 8, so that a block has 192 to
+// 384 threads, the halo no more columns than the tile and a slice's links no more than the threads.
+// (Ls = 28 would leave one block to a CU in FP32.)
 static bool plane_tile(const GeomDev &g, PlaneDev *d) {
-    if (g.Ls == 12 || g.Ls == 16) {
+    if (g.Ls % 4 == 0 && g.Ls >= 12 && g.Ls <= 24) {
         d->ltx = d->lty = 2;
     } else if (g.Ls == 8) {
         d->ltx = g.L[0] % 8 == 0 ? 3 : 2;
@@ -467,9 +468,15 @@ static PlaneDev plane_dev(const GeomDev &g, bool scaled) {
 // Below these sizes the column walk is faster (its wavefronts wait for nothing but their own loads):
 // FP32 8^3 x 32 x 8 (131072 sites) 14.8 against 16.1 us here, 12^3 x 8 x 16 (221184) 25.7 against 21.7;
 // FP16 storage 12^4 x 12 (248832) 17.9 against 20.6 us, 12^4 x 16 (331776) 23.2 against 21.8.
+// Ls = 20 and 24 in FP32 only: 16^4 x 20 120.6 against 100.1 us here, 16^4 x 24 147.1 against 113.0, 12^4 x 24
+// 49.6 against 43.8, 12^2 x 13 x 9 x 24 (404352 sites) 42.9 against 41.0, 12^2 x 10 x 8 x 20 (230400) 52.9 against 59.1
+// (M^dagger M); FP16 storage, whose larger blocks leave a CU with
+// fewer wavefronts than the column walk's, 16^4 x 20 78.8 against 89.3 us, 16^4 x 24 94.7 against 92.7, 12^4 x 24
+// 33.4 against 37.9.
 bool plane_applies(const DhopArgs &a) {
     PlaneDev d;
-    const int least = a.prec == GRID_F16S ? 300000 : 160000;
+    const int least = a.prec == GRID_F16S ? 300000 : a.g.Ls > 16 ? 400000 : 160000;
+    if (a.g.Ls > 16 && a.prec != GRID_F32) return false;
     const bool kind = a.kind == GRID_HOP || a.kind == GRID_DWF || (a.kind == GRID_MOBIUS && a.g.Ls == 16);
     return !a.custom && kind && (a.prec == GRID_F32 || a.prec == GRID_F16S) && a.g.n5 >= least && plane_tile(a.g, &d) &&
            offsets32(a.g.n5 / a.g.L[3], 96);
