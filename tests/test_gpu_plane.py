@@ -1,5 +1,5 @@
 """GPU parity of the plane walk (5D FP32 / FP16-storage fields with Ls = 8, 12 or 16, at least 160000
-and 300000 sites; FP32 with Ls = 20 or 24, at least 200000; on lattices whose x and y extents its
+and 300000 sites; FP32 with Ls = 20 or 24, at least 400000; on lattices whose x and y extents its
 tiles divide) at the sizes where it can go wrong: one tile per direction (every face wraps), odd numbers of planes and slices, tiles in the
 interior, walks of several slices and of one, and lattices on either side of its limits.
 
@@ -42,7 +42,7 @@ def _check(got, ref, prec, what):
 # column walk's.
 SHAPES = [((4, 4, 41, 20), 16), ((4, 4, 79, 16), 16), ((8, 4, 71, 11), 8), ((8, 4, 121, 10), 8), ((4, 8, 131, 9), 8),
           ((12, 8, 23, 12), 12), ((8, 16, 17, 18), 8), ((16, 12, 8, 13), 16), ((6, 4, 41, 26), 12), ((4, 4, 32, 32), 20),
-          ((4, 8, 25, 11), 24), ((12, 8, 11, 8), 24)]
+          ((4, 4, 41, 31), 20), ((4, 8, 41, 13), 24), ((12, 8, 16, 11), 24)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -59,7 +59,7 @@ def test_plane_parity(gpu, shape, prec, fmt):
 
 
 @pytest.mark.parametrize("sloppy", ["f32", "f16s"])
-@pytest.mark.parametrize("shape", [((8, 12, 26, 12), 12), ((8, 4, 121, 10), 8), ((4, 8, 26, 11), 24)])
+@pytest.mark.parametrize("shape", [((8, 12, 26, 12), 12), ((8, 4, 121, 10), 8), ((4, 8, 41, 13), 24)])
 def test_plane_fused_epilogues(gpu, sloppy, shape):
     """Mixed-precision CG (the norm and r-update epilogues) to a small FP64 residual."""
     from tests.gpu_util import dev, host, rel
