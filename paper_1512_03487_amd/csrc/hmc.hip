@@ -258,6 +258,18 @@ k_link_exp(void *U, const void *__restrict__ P, double eps, long nlinks) {
         nrm *= 0.5;
         ++sq;
     }
+    bool minus1 = true;   // see below
+    if (sq > 0) {
+        double h2 = 0.0;   // |P + P^dagger|^2
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const double hr = X[i][j].r + X[j][i].r, hi = X[i][j].i - X[j][i].i;
+                h2 += hr * hr + hi * hi;
+            }
+        minus1 = !(fabs(eps) * sqrt(h2) > 1.0);
+    }
     const double sc = eps * ldexp(1.0, -sq);
 #pragma unroll
     for (int k = 0; k < 9; ++k) X[k / 3][k % 3] = cscale(sc, X[k / 3][k % 3]);
@@ -288,17 +300,28 @@ k_link_exp(void *U, const void *__restrict__ P, double eps, long nlinks) {
         if (k % 4 == 0) x = cadd(x, e0);
         E[k / 3][k % 3] = x;
     }
-    // E = exp - 1 throughout, (1 + E)^2 - 1 = 2 E + E E and U + E U: the products' roundings are relative to
-    // the small E (leapfrog at 16^4 off by 1.6e-16; with the unit added before the product 1.9e-16)
+    // For momenta in su(3) E = exp - 1 throughout, (1 + E)^2 - 1 = 2 E + E E and U + E U: the products'
+    // roundings are relative to the small E (leapfrog at 16^4 off by 1.6e-16; with the unit added before the
+    // product 1.9e-16). A P with a Hermitian part may contract, exp(X) far below 1, which U + E U would
+    // leave as a difference of numbers of order 1 (exp(-10) off by 2e-12, exp(-40) wholly lost): there (the
+    // Hermitian part of eps P above 1/2) the unit is added first and exp itself is squared (4e-15, 2e-14).
+    if (!minus1) {
+#pragma unroll
+        for (int k = 0; k < 9; k += 4) E[k / 3][k % 3].r += 1.0;
+    }
     for (int k = 0; k < sq; ++k) {
         mm<false, false>(E, E, T);
 #pragma unroll
-        for (int j = 0; j < 9; ++j) E[j / 3][j % 3] = cadd(cadd(E[j / 3][j % 3], E[j / 3][j % 3]), T[j / 3][j % 3]);
+        for (int j = 0; j < 9; ++j) {
+            const Cx<double> e = E[j / 3][j % 3], x = T[j / 3][j % 3];
+            E[j / 3][j % 3] = minus1 ? cadd(cadd(e, e), x) : x;
+        }
     }
     link_take(fu, tmp, u);
     mm<false, false>(E, u, T);
 #pragma unroll
-    for (int j = 0; j < 9; ++j) T[j / 3][j % 3] = cadd(u[j / 3][j % 3], T[j / 3][j % 3]);
+    for (int j = 0; j < 9; ++j)
+        if (minus1) T[j / 3][j % 3] = cadd(u[j / 3][j % 3], T[j / 3][j % 3]);
     link_leave(T, tmp);
     chunk_t *out = static_cast<chunk_t *>(U);
 #pragma unroll
