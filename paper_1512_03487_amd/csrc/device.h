@@ -373,7 +373,8 @@ __device__ __forceinline__ double stored_n2<SpF16S>(Cx<float> v, bool live) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Link storage. `link` = site * 4 + mu. Loads fill u[3][3] (row 2 rebuilt for 12-real links).
+// Link storage. `link` = site * 4 + mu. Loads fill u[3][3] (row 2 rebuilt for 12-real links) by reads of
+// kAlign bytes, which `base` has to be aligned to.
 // ------------------------------------------------------------------------------------------
 
 template <typename C>
@@ -421,7 +422,7 @@ template <int ROWS>
 struct LkF64 {
     using C = double;
     static constexpr int kRows = ROWS;
-    static constexpr int kBytes = ROWS * 3 * 16;
+    static constexpr int kBytes = ROWS * 3 * 16, kAlign = 16;
     __device__ __forceinline__ static void load(const void *base, size_t link, Cx<C> u[3][3]) {
         const double2 *q = reinterpret_cast<const double2 *>(base) + link * (ROWS * 3);
 #pragma unroll
@@ -448,7 +449,7 @@ template <int ROWS>
 struct LkF32 {
     using C = float;
     static constexpr int kRows = ROWS;
-    static constexpr int kBytes = ROWS * 3 * 8;
+    static constexpr int kBytes = ROWS * 3 * 8, kAlign = ROWS == 2 ? 16 : 8;
     __device__ __forceinline__ static void load(const void *base, size_t link, Cx<C> u[3][3]) {
         if (ROWS == 2) {
             const float4 *q = reinterpret_cast<const float4 *>(base) + link * 3;
@@ -474,7 +475,7 @@ template <int ROWS>
 struct LkF16 {
     using C = float;
     static constexpr int kRows = ROWS;
-    static constexpr int kBytes = ROWS * 3 * 4;
+    static constexpr int kBytes = ROWS * 3 * 4, kAlign = ROWS == 2 ? 8 : 4;
     __device__ __forceinline__ static void load(const void *base, size_t link, Cx<C> u[3][3]) {
         if (ROWS == 2) {
             const uint2 *q = reinterpret_cast<const uint2 *>(base) + link * 3;

@@ -308,7 +308,7 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
             if constexpr (MOBA) raw = centre;
         };
         // Own record first: the t-hops need no other load.
-        uint32_t wl[LK::kBytes / 4];
+        alignas(16) char wl[LK::kBytes];
         auto link_load = [&]() {
             const char *l = static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes) +
                             static_cast<size_t>(ug) * LK::kBytes;

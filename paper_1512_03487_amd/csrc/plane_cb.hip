@@ -276,7 +276,7 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
         const int tt = t0 + k;
         const int b = (b0 + tt) & 1;
         Rec<SP> own, hr, yr;
-        uint32_t wl[LK::kBytes / 4];
+        alignas(16) char wl[LK::kBytes];
         auto others = [&]() {   // halo record and link
             if (c < NH) direct(psi, psi_scale, tt, (hb0 + tt) & 1 ? hq1 : hq0, hr);
             const char *l = static_cast<const char *>(U) + static_cast<size_t>(slice(tt)) * V3 * (4 * LK::kBytes) +

@@ -105,7 +105,10 @@ __device__ __forceinline__ int tile_chunk_offset(const GeomDev &g, int x0, int y
 }
 
 // Links of a tile in LDS: a site's four links as stored and eight bytes of padding (the reads of a
-// wavefront, one link per lane at this pitch, then spread over all banks), the face links after them.
+// wavefront, one link per lane at this pitch, then spread over all banks), the face links after them. The
+// pitch leaves a link aligned to its unit of eight or four bytes, not to the 16 that a 12-real FP32 link is
+// read by from memory: get() reads units (16-byte reads there are undefined, and where the hardware allows
+// them slower: 32^4 98 to 102 us, in units 89 to 92).
 template <class LK>
 struct LinkTile {
     static constexpr int LB = LK::kBytes;
@@ -115,6 +118,21 @@ struct LinkTile {
     static constexpr int kUnits = LB / kUnit;
     typedef unsigned int u2v __attribute__((ext_vector_type(2)));
     using T = std::conditional_t<kUnit == 8, u2v, uint32_t>;
+    static_assert(kPitch % kUnit == 0 && LB % kUnit == 0 && kUnit % sizeof(T) == 0, "links aligned to their unit");
+    // the link at sl + at (a multiple of kUnit)
+    __device__ __forceinline__ static void get(const char *sl, int at, Cx<typename LK::C> u[3][3]) {
+        if constexpr (LK::kAlign <= kUnit) {
+            LK::load(sl + at, 0, u);
+        } else {
+            alignas(LK::kAlign) char w[LB];
+#pragma unroll
+            for (int k = 0; k < kUnits; ++k) {
+                const T v = reinterpret_cast<const T *>(sl + at)[k];
+                __builtin_memcpy(w + k * kUnit, &v, kUnit);
+            }
+            LK::load(w, 0, u);
+        }
+    }
 };
 
 template <class SP, class LK, bool DAG, int KIND, int FUSE, int TX, int TY, int TZ>
@@ -327,29 +345,29 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
         else
             reconstruct_fma<3, -EF, SP::kScaled>(acc, chi_b, chi_s);
         rec(nxp, p);
-        LK::load(sl + lown, 0, u);
+        LT::get(sl, lown, u);
         hop_rec<0, EF, false, SP>(sum, p, u);
         rec(nxm, p);
-        LK::load(sl + lxm, 0, u);
+        LT::get(sl, lxm, u);
         hop_rec<0, -EF, true, SP>(sum, p, u);
         pair_done();
         rec(nyp, p);
-        LK::load(sl + lown + LT::LB, 0, u);
+        LT::get(sl, lown + LT::LB, u);
         hop_rec<1, EF, false, SP>(sum, p, u);
         rec(nym, p);
-        LK::load(sl + lym, 0, u);
+        LT::get(sl, lym, u);
         hop_rec<1, -EF, true, SP>(sum, p, u);
         pair_done();
         rec(nzp, p);
-        LK::load(sl + lown + 2 * LT::LB, 0, u);
+        LT::get(sl, lown + 2 * LT::LB, u);
         hop_rec<2, EF, false, SP>(sum, p, u);
         rec(nzm, p);
-        LK::load(sl + lzm, 0, u);
+        LT::get(sl, lzm, u);
         hop_rec<2, -EF, true, SP>(sum, p, u);
         pair_done();
         // forward time hop psi(x, t + 1) with U_t(x, t); the same link carries the backward time
         // hop of slice t + 1, U_t(x, t)^dagger h(psi(x, t))
-        LK::load(sl + lown + 3 * LT::LB, 0, u);
+        LT::get(sl, lown + 3 * LT::LB, u);
         p.set(Qw, Qs);
         if constexpr (PAIR) reconstruct_fma<3, -EF, SP::kScaled>(two, chi_b, chi_s);
         hop_rec<3, EF, false, SP>(sum, p, u);
