@@ -913,6 +913,7 @@ struct Rec<SpF32> {
     Cx<float> p[4][3];
     __device__ __forceinline__ void set(const uint4 *w, float) { SpF32::unpack(w, 1.0f, p); }
     __device__ __forceinline__ float scale() const { return 1.0f; }
+    __device__ __forceinline__ Cx<C> at(int j) const { return p[j / 3][j % 3]; }   // complex j of psi
     __device__ __forceinline__ void renew() {}
     template <int MU, int E>
     __device__ __forceinline__ void proj(Cx<C> h[2][3]) const {
@@ -954,6 +955,7 @@ struct Rec<SpF16S> {
         s = sc;
     }
     __device__ __forceinline__ float scale() const { return s; }
+    __device__ __forceinline__ Cx<C> at(int j) const { return {half_lo(w[j]) * s, half_hi(w[j]) * s}; }
     // hides the codes from the compiler, which would keep 24 conversions for a record's second use
     __device__ __forceinline__ void renew() {
 #pragma unroll
