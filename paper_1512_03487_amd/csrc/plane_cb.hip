@@ -77,16 +77,22 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
     const int zpo = (z == Lz - 1 ? 1 - Lz : 1) * plane * Ls, zmo = (z == 0 ? Lz - 1 : -1) * plane * Ls;
     const int t0 = seg * Lt / pd.nseg, T = (seg + 1) * Lt / pd.nseg - t0;
     constexpr int EF = DAG ? +1 : -1;
-    // wall factors of s + 1 and s - 1; y's part of the sum is divided by beta, which scales it at the end
-    const float wp = (s == Ls - 1) ? static_cast<float>(-mf) : 1.0f, wm = (s == 0) ? static_cast<float>(-mf) : 1.0f;
-    const float bt = static_cast<float>(beta);
-    [[maybe_unused]] const float dgb = static_cast<float>(diag) / bt, csb = -static_cast<float>(cs) / bt;
-    [[maybe_unused]] const float mb5 = static_cast<float>(b5), mc5 = static_cast<float>(c5);
-
     // FP32 records are stored through LDS (wave_store; 16^4 x 16 H 36 -> 33 us, 24^4 x 16 204 -> 184), for which
     // out(t - 1) is finished before slice t's records go there; FP16-storage ones, at half the pitch, are
     // as fast stored by their lane (28 against 29 us), and their LDS writes need not wait.
     constexpr bool STAGE = !SP::kScaled;
+    // out = diag y - cs S y + beta H psi. y's part comes after the hops: before them, as diag y / beta and larger
+    // than they are, it has each of them rounded at its size (domain wall in FP32, beta = -1/4: error 7.8e-8 of the
+    // result; 5.1e-8 so, the column walk's). YEND: it is added to the finished sum. In FP32 that exposes the load
+    // of y (46 -> 52 us at 16^4 x 16, and spills where it is issued before the t-hop): there it joins beta times
+    // the seven hops of the slice, and the last hop is added times beta (47 us).
+    constexpr bool YEND = HASY && (MOBA || !STAGE), YMID = HASY && !YEND;
+    // wall factors of s + 1 and s - 1
+    const float wp = (s == Ls - 1) ? static_cast<float>(-mf) : 1.0f, wm = (s == 0) ? static_cast<float>(-mf) : 1.0f;
+    const float bt = static_cast<float>(beta);
+    [[maybe_unused]] const float dg = static_cast<float>(diag), csm = -static_cast<float>(cs);
+    [[maybe_unused]] const float mb5 = static_cast<float>(b5), mc5 = static_cast<float>(c5);
+
     // Byte offsets, within a slice, of this thread's stores: chunks j 64 + lane of the wavefront's records
     constexpr int CM = SP::kChunks;
     [[maybe_unused]] unsigned og[CM];
@@ -174,8 +180,8 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
         if constexpr (MOBF) {
 #pragma unroll
             for (int j = 0; j < 12; ++j) h.p[j / 3][j % 3] = {0.f, 0.f};
-            r.axpy(h.p, mb5);
             column_shift_axpy<false>(r, h.p, mc5 * wp, mc5 * wm);
+            r.axpy(h.p, mb5);
         } else {
             h = r;
         }
@@ -210,10 +216,26 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
         p.set(w, SC ? rsc[r] : 1.0f);
     };
     [[maybe_unused]] double n2 = 0.0;   // fused epilogue: this thread's |out|^2
-    // out(tt) from the finished sum (and y, for the Moebius adjoint)
-    auto finish = [&](int tt, [[maybe_unused]] const Rec<SP> &raw) {
+    auto scale_sum = [&]() {
 #pragma unroll
         for (int j = 0; j < 12; ++j) A[j / 3][j % 3] = {bt * A[j / 3][j % 3].r, bt * A[j / 3][j % 3].i};
+    };
+    // the forward t-hop of the slice before, with psi(x, tt) in p
+    auto last_hop = [&]() {
+        if constexpr (YMID) {
+            Cx<float> h[2][3], chi[2][3];
+            p.template proj<3, EF>(h);
+            su3_mfma<false>(utf, h, chi);
+            reconstruct_fma<3, EF, true>(A, chi, bt);
+            pin(A);
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            hop_mfma<3, EF, false, SL>(A, p, utf);
+        }
+    };
+    // out(tt) from the finished sum (and with YEND y)
+    auto finish = [&](int tt, [[maybe_unused]] const Rec<SP> &raw) {
+        if constexpr (!YMID) scale_sum();
         if constexpr (MOBA) {
             // h = A: v = c5 h - cs y, out = diag y + b5 h + S^dagger v (no y for kMobHop and kMobHopInv)
             Rec<SpF32> v;
@@ -224,10 +246,13 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
                 a = {mb5 * a.r, mb5 * a.i};
             }
             if constexpr (HASY) {
-                raw.axpy(v.p, -static_cast<float>(cs));
-                raw.axpy(A, static_cast<float>(diag));
+                raw.axpy(v.p, csm);
+                raw.axpy(A, dg);
             }
             column_shift_axpy<true>(v, A, wp, wm);
+        } else if constexpr (YEND) {
+            raw.axpy(A, dg);
+            column_shift_axpy<DAG>(raw, A, csm * wp, csm * wm);
         }
         if constexpr (INV) column_m5inv_row<DAG>(A, s, static_cast<float>(1.0 / diag), static_cast<float>(mf));
         const size_t o = static_cast<size_t>(tt) * nq + q;
@@ -301,24 +326,21 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
             __builtin_amdgcn_sched_barrier(0);
         };
         direct(psi, psi_scale, tt, q, own);
-        if constexpr (HASY && MOBA && STAGE)
-            if (k > 0) direct(yv, y_scale, tt - 1, q, yr);
         if constexpr (!STAGE) others();
         hopped(own, p);
         if constexpr (!STAGE) {
             put_all();
-            if constexpr (HASY && !MOBA) direct(yv, y_scale, tt, q, yr);
-            if constexpr (HASY && MOBA)
+            if constexpr (YEND)
                 if (k > 0) direct(yv, y_scale, tt - 1, q, yr);
         }
         // finish out(tt - 1) with psi(x, tt) and start the sum of out(tt)
         if (k > 0) {
-            hop_mfma<3, EF, false, SL>(A, p, utf);
+            last_hop();
+            if constexpr (YEND && STAGE) direct(yv, y_scale, tt - 1, q, yr);
             finish(tt - 1, yr);
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (STAGE) others();   // not in registers beside the t-hop's
-        if constexpr (HASY && !MOBA && STAGE) direct(yv, y_scale, tt, q, yr);
         {
             Cx<float> chi[2][3];
             su3_mfma<true>(utb, hb, chi);
@@ -330,10 +352,6 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
             hs = p.scale();
         }
         if constexpr (STAGE) put_all();
-        if constexpr (HASY && !MOBA) {
-            yr.axpy(A, dgb);
-            column_shift_axpy<DAG>(yr, A, csb * wp, csb * wm);
-        }
         __syncthreads();
         Rec<SP> rz;
         direct(psi, psi_scale, tt, q + zpo, rz);   // in flight during the x hops
@@ -356,11 +374,18 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
         staged(nym);
         mat_row<true>(link(lym), u);
         hop_mfma<1, -EF, true, SL>(A, p, u);
+        // in flight during the last z hop (issued before the y hops it spills: 60 us)
+        if constexpr (YMID) direct(yv, y_scale, tt, q, yr);
         mat_row<true>(link(c * 8 + 6), u);
         {
             Rec<SL> pz;
             hopped(rz, pz);
             hop_mfma<2, -EF, true, SL>(A, pz, u);
+        }
+        if constexpr (YMID) {
+            scale_sum();
+            yr.axpy(A, dg);
+            column_shift_axpy<DAG>(yr, A, csm * wp, csm * wm);
         }
         // U_t at the output's site (forward t-hop of out(tt)) and at the input's (backward one of out(tt + 1))
         mat_row<false>(link(c * 8 + 3), utf);
@@ -373,8 +398,8 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
         direct(psi, psi_scale, tl == Lt - 1 ? 0 : tl + 1, q, r);
         hopped(r, p);
         Rec<SP> yr;
-        if constexpr (HASY && MOBA) direct(yv, y_scale, tl, q, yr);
-        hop_mfma<3, EF, false, SL>(A, p, utf);
+        if constexpr (YEND) direct(yv, y_scale, tl, q, yr);
+        last_hop();
         finish(tl, yr);
     }
     if constexpr (FUSE != kFuseNone) {
@@ -411,12 +436,10 @@ static PlaneCbDev plane_cb_dev(const GeomDev &g) {
 // Below these sizes (full lattice) the checkerboard column walk is as fast: FP32 8^3 x 16 x 16 (131072
 // sites) 10.4 us both, 12 x 8 x 12^2 x 16 (221184) 12.3 here against 12.8, 16 x 8 x 16^2 x 16 (524288) 22 against
 // 26; FP16 storage 12 x 8 x 12^2 x 16 11.3 us both, 16 x 8 x 16^2 x 16 15 both for H, 17 against 18 with y.
-// beta divides y's part of the sum: a beta far from 1 keeps the column walk.
 bool plane_cb_applies(const DhopArgs &a) {
     const int least = a.prec == GRID_F16S ? 400000 : 200000;
     return a.custom && a.cb >= 0 && a.kind != GRID_WILSON && (a.prec == GRID_F32 || a.prec == GRID_F16S) &&
-           a.g.Ls == kPcLs && a.g.n5 >= least && fabs(a.beta) >= 0x1p-20 && fabs(a.beta) <= 0x1p20 &&
-           plane_cb_dev(a.g).ltx != 0 && offsets32(a.g.n5 / a.g.L[3], 48);
+           a.g.Ls == kPcLs && a.g.n5 >= least && plane_cb_dev(a.g).ltx != 0 && offsets32(a.g.n5 / a.g.L[3], 48);
 }
 
 long plane_cb_blocks(const DhopArgs &a) {
