@@ -37,7 +37,7 @@ namespace gridmi {
 struct PlaneDev {
     int tx, ty;          // tile extents (powers of two)
     int ltx, lty;        // their logarithms
-    int T;               // time slices per block
+    int nseg;            // blocks along t: block i walks slices [i Lt / nseg, (i + 1) Lt / nseg)
 };
 
 // Halo columns of a tile: the -x, +x faces (ty each), then -y, +y (tx each).
@@ -86,7 +86,7 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
     const int col = z * plane + (y0 + cy) * Lx + x0 + cx;
     const int zpo = (z == Lz - 1 ? 1 - Lz : 1) * plane * Ls, zmo = (z == 0 ? Lz - 1 : -1) * plane * Ls;
     const int q = col * Ls + s;
-    const int t0 = seg * pd.T;
+    const int t0 = seg * Lt / pd.nseg, T = (seg + 1) * Lt / pd.nseg - t0;
     constexpr int EF = DAG ? +1 : -1;
     // H and the domain-wall M: out = beta (H psi + (diag psi - S psi) / beta), beta = 1 for H and -1/2 for M
     const float bt = KIND == GRID_HOP ? 1.0f : -0.5f;
@@ -293,7 +293,7 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
         utf = utb;
     }
 #pragma unroll 1
-    for (int k = 0; k < pd.T; ++k) {
+    for (int k = 0; k < T; ++k) {
         const int tt = t0 + k;
         // finishes out(tt - 1) with psi(x, tt) (p) and starts the sum of out(tt)
         auto t_hops = [&](const Rec<SP> &centre) {
@@ -405,7 +405,7 @@ k_dhop_plane(const void *__restrict__ U, const void *__restrict__ psi, const flo
         __syncthreads();   // the next slice overwrites what was read here
     }
     {
-        const int tl = t0 + pd.T - 1;
+        const int tl = t0 + T - 1;
         Rec<SP> r;
         direct(tl == Lt - 1 ? 0 : tl + 1, q, r);
         hopped(r, p);
@@ -442,13 +442,18 @@ static bool plane_tile(const GeomDev &g, PlaneDev *d) {
     return g.L[0] % d->tx == 0 && g.L[1] % d->ty == 0;
 }
 
-// Slices per block: the divisor T <= 8 of Lt with the least of (T + 1.5) x the sum over rounds of
-// (1.5 + blocks of the round on a CU). A walk's start and end cost about one and a half slices, and a
+// Blocks along t: of the counts that divide Lt into walks of T <= 8 slices the one with the least of (T + 1.5) x
+// the sum over rounds of (1.5 + blocks of the round on a CU). A walk's start and end cost about one and a half slices, and a
 // slice of one block takes, with m blocks on its CU, about as long as 1.5 + m (latency, then
 // throughput). Measured, T = 2 / 3 / 4 / 6 / 8 / 12 / 24: 24^4 x 12 FP16 storage 226 / 205 / 198 / 193 / 198 /
 // 197 / 201 us, FP32 371 / 339 / 339 / 336 / 348 / 340 / 371 us, 24^4 x 8 FP32 248 / 229 / 227 / 221 / 236 / 237 /
 // 239 us; T = 2 / 4 / 8 / 16: 16^4 x 16 FP32 93 / 85 / 80 / 89 us, 16^4 x 12 FP16 storage 45 / 39 / 45 / 58 us;
-// T = 1 / 2 / 3 / 4 / 6: 12^4 x 16 FP32 38 / 34 / 29 / 34 / 34 us.
+// T = 1 / 2 / 3 / 4 / 6: 12^4 x 16 FP32 38 / 34 / 29 / 34 / 34 us. A count that does not divide Lt, its longest walk for
+// T, is taken where that is well below: an Lt without such a divisor would leave walks of one slice, which read
+// three. Equal / unequal walks: 16^3 x 13 FP32 x 8 / 12 / 16 / 20 / 24 41 / 34, 56 / 48, 76 / 58, 127 / 89, 137 / 98 us (the
+// column walk 47, 67, 88, 108, 126), 24^3 x 23 x 12 344 / 261, FP16 storage 204 / 174; a little below is no gain: 20^4
+// FP32 x 12 / 16 / 24 (0.94 to 0.98 of the model) 133 / 137, 167 / 174, 296 / 319, 16^3 x 34 x 8 (0.78) 88 / 90; FP16 storage, whose one-slice walks cost less than
+// modelled, 16^3 x 13 x 12 (0.62) 35 / 38, 12^3 x 19 x 12 (0.60) 25 / 25, 16^3 x 13 x 16 (0.57) 43 / 40.
 static PlaneDev plane_dev(const GeomDev &g, bool scaled) {
     PlaneDev d{};
     if (!plane_tile(g, &d)) return d;
@@ -457,16 +462,23 @@ static PlaneDev plane_dev(const GeomDev &g, bool scaled) {
     const long by_lds = 128 / granules;   // 160 KB in granules of 1280 bytes
     const long per_cu = by_lds < 12 / waves ? by_lds : 12 / waves;   // three wavefronts per SIMD
     const long tiles = static_cast<long>(g.vol / g.L[3]) / (d.tx * d.ty);
-    double best = 0.0;
-    for (int T = 1; T <= 8 && T <= g.L[3]; ++T) {
-        if (g.L[3] % T) continue;
-        const long m = (tiles * (g.L[3] / T) + 255) / 256, rem = m % per_cu;
+    double even = 0.0, any = 0.0;   // costs of the best count that divides Lt, and of the best of all
+    int uneven = 0;
+    for (int n = g.L[3]; n >= 1; --n) {
+        const int T = (g.L[3] + n - 1) / n;
+        if (T > 8) break;
+        const long m = (tiles * n + 255) / 256, rem = m % per_cu;
         const double cost = (T + 1.5) * ((m / per_cu) * (1.5 + per_cu) + (rem ? 1.5 + rem : 0.0));
-        if (d.T == 0 || cost < best) {
-            best = cost;
-            d.T = T;
+        if (g.L[3] % n == 0 && (d.nseg == 0 || cost < even)) {
+            even = cost;
+            d.nseg = n;
+        }
+        if (uneven == 0 || cost < any) {
+            any = cost;
+            uneven = n;
         }
     }
+    if (any < (scaled ? 0.59 : 0.76) * even) d.nseg = uneven;
     return d;
 }
 
@@ -492,7 +504,7 @@ static bool plane_scaled(const DhopArgs &a) { return a.prec == GRID_F16S && !(a.
 
 long plane_blocks(const DhopArgs &a) {
     const PlaneDev d = plane_dev(a.g, plane_scaled(a));
-    return static_cast<long>(a.g.vol / a.g.L[3]) / (d.tx * d.ty) * (a.g.L[3] / d.T);
+    return static_cast<long>(a.g.vol / a.g.L[3]) / (d.tx * d.ty) * d.nseg;
 }
 
 template <class SP, class LK>

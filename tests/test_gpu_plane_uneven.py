@@ -1,0 +1,49 @@
+"""Plane walks of unequal length along t (time extents without a divisor up to eight, or with poor ones):
+every slice exactly once, to the parity bounds of the equal ones, and the fused epilogues' partial sums.
+
+Tolerances as in tests/test_gpu_plane.py: FP32 1e-6 and FP16 storage 2e-3 over the field, per component
+2^-16 and 2^-10 of the site's largest component.
+"""
+import numpy as np
+import pytest
+
+import oracle.oracle as O
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1e-6, "f16s": 2e-3}
+SITE_TOL = {"f32": 2.0 ** -16, "f16s": 2.0 ** -10}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _announce():
+    print("\n[gpu] test_gpu_plane_uneven", flush=True)
+
+
+# walks of 5 and 6 slices (11 in 2), 4 and 5 (13 in 3), 3 and 4 (31 in 8, 23 in 6), 6 and 7 (13 in 2)
+@pytest.mark.parametrize("dims,Ls", [((16, 16, 16, 11), 16), ((16, 16, 16, 13), 12), ((8, 8, 32, 31), 8), ((8, 8, 16, 23), 24),
+                                     ((16, 16, 16, 13), 20), ((16, 16, 16, 17), 8)])
+@pytest.mark.parametrize("prec,fmt", [("f32", "L18"), ("f16s", "L12")])
+def test_plane_uneven_parity(gpu, dims, Ls, prec, fmt):
+    import paper_1512_03487_amd as gm
+    from tests.gpu_util import as_prec, cached, host, rel
+    U, psi = cached("gauge", dims, 1, kind="haar"), cached("spinor", dims, 3, Ls=Ls)
+    Uk, pk, Ur, pr = as_prec(U, psi, prec, fmt)
+    for dag in (False, True):
+        got, ref = host(gm.dwf(Uk, pk, 1.8, 0.3, dag=dag)), O.dwf(Ur, pr, 1.8, 0.3, dag)
+        g, r = got.reshape(-1, 12), ref.reshape(-1, 12)
+        d = np.maximum(np.abs(g.real - r.real), np.abs(g.imag - r.imag)).max(axis=1)
+        s = np.maximum(np.abs(r.real), np.abs(r.imag)).max(axis=1)
+        assert rel(got, ref) <= TOL[prec] and float(np.max(d / s)) <= SITE_TOL[prec], (dims, Ls, dag)
+
+
+@pytest.mark.parametrize("sloppy", ["f32", "f16s"])
+def test_plane_uneven_in_the_mixed_solve(gpu, sloppy):
+    from paper_1512_03487_amd import fields as F
+    from tests.gpu_util import dev, host, rel
+    import paper_1512_03487_amd as gm
+    dims, Ls = (16, 8, 16, 11), 16
+    U, b = F.gauge_field(dims, seed=1, kind="haar"), F.spinor_field(dims, seed=3, Ls=Ls)
+    x, st = gm.cg(dev(U), dev(b), kind="dwf", M5=1.8, mf=0.1, tol=1e-10, sloppy=sloppy, check_every=4)
+    assert st["converged"]
+    assert rel(O.normal(O.Op.dwf(Ls, 1.8, 0.1), U, host(x)), b) <= 1.1e-10
