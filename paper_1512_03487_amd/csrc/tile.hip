@@ -473,12 +473,12 @@ static TileDev tile_dev(const DhopArgs &a, double *share = nullptr) {
 // third round for a part of one: H here / column walk 16 x 8 x 28 x 38 (2.1) 16.2 / 15.3 us, 24 x 16 x 20^2 (2.3) 16.8 /
 // 15.4, 24^3 x 13 (2.7) 18.6 / 16.8, 24^2 x 20 x 16 (2.8) 18.4 / 16.4, D 18.6 / 16.9, and beside that range 16^3 x 28 (1.75)
 // 11.9 / 12.1, 24^2 x 36 x 9 (2.85) 17.3 / 19.0, 24^3 x 15 (3.2) 19.4 / 21.1; with 18-real links 24^3 x 13 19.4 / 21.8.
-// FP32: from 500000 sites on (24^4, 331776 sites, which the caches hold, 38 / 39 us
-// here with 18- / 12-real links, 35 / 34 there) where the blocks keep the CUs evenly busy: a share of at least
-// 0.78 (18-real) or 0.815 (12-real). Direction-parallel / tile from memory, 18-real and 12-real, by share:
-// 56 x 32 x 24^2 (0.91) 142 / 125, 128 / 110 us, 32 x 24 x 28 x 26 (0.88) 80 / 65, 73 / 61, 40^2 x 24^2 (0.82) 128 / 117,
-// 116 / 108, 32^2 x 20 x 28 (0.82) 82 / 69, 74 / 65, 32^2 x 24^2 (0.81) 87 / 83, 75 / 76, 24^2 x 32 x 30 (0.79) 76 / 67,
-// 69 / 65.
+// FP32: from 500000 sites on (24^4, 331776 sites, which the caches hold, 38 / 39 us here with 18- / 12-real links,
+// 35 / 34 there) where the blocks keep the CUs evenly busy: a share of at least 0.78 (18-real) or 0.70 (12-real).
+// Direction-parallel / tile from memory, H with 18-real and 12-real links, by share: 56 x 32 x 24^2 (0.91) 137 / 125,
+// 126 / 104 us, 32 x 24 x 28 x 26 (0.88) 78 / 65, 69 / 55, 40^2 x 24^2 (0.82) 123 / 117, 110 / 100, 32^2 x 20 x 28 (0.82) 80 / 69,
+// 71 / 58, 32^2 x 24^2 (0.81) 82 / 83, 71 / 70 (D 12-real 76 / 71), 24^2 x 32 x 30 (0.79) 73 / 67, 66 / 57, 16 x 48 x 30 x 28
+// (0.77) 87 / 89, 78 / 76, 48 x 16 x 30 x 27 (0.74) 87 / 88, 77 / 76, 56 x 48 x 26 x 9 (0.70) 93 / 95, 82 / 82.
 bool tile_applies(const DhopArgs &a) {
     if (a.custom || a.g.Ls != 1 || (a.kind != GRID_HOP && a.kind != GRID_WILSON)) return false;
     if (a.prec != GRID_F16S && a.prec != GRID_F32) return false;
@@ -487,9 +487,10 @@ bool tile_applies(const DhopArgs &a) {
         const double per_cu = static_cast<double>(a.g.vol) / (kTX * kTY * kTZ<SpF16S> * 256.0);
         return a.link_fmt == GRID_L18 || per_cu <= 2.0 || per_cu >= 2.83;
     }
+    if (a.g.n5 < 500000) return false;
     double share;
     tile_dev(a, &share);
-    return a.g.n5 >= 500000 && share >= (a.link_fmt == GRID_L12 ? 0.815 : 0.78);
+    return share >= (a.link_fmt == GRID_L12 ? 0.70 : 0.78);
 }
 
 long tile_blocks(const DhopArgs &a) {
