@@ -414,9 +414,11 @@ k_dhop_plane_cb(const void *__restrict__ U, const void *__restrict__ psi, const 
 // Tile 4 x 4, or 2 x 8 where only that divides (xh, y). Blocks along t: the count with the least (slices
 // of the longest + 0.5) x (1.5 + m), m blocks on a CU (a walk's start and end cost about half a slice;
 // one block's slice takes, with m of them on a CU, about as long as 1.5 + m), or beyond the three that
-// fit a CU x (1 + 1.5 m). Measured, nseg = 1 / 2 / 3 / 4 / 6 / 8 / 12 / 16: FP32 16^4 66 / 43 / 44 / 36 / 39 / 39 /
-// 44 / 42 us, 24^4 211 / 224 / 215 / 204 / 197 / 200 / 213 / 219 us, 16 x 8^2 x 16 63 / 35 / 28 / 20 / 18 / 14 /
-// 16 / 13 us; FP16 storage 16^4 55 / 33 / 34 / 25 / 26 / 25 / 30 / 28 us.
+// fit a CU x (1 + 1.5 m), and no less than 6.5: a fourth block on a few CUs waits for a slot on each of them.
+// Measured, nseg = 2 / 3 / 4 / 6 / 8 / 12 / 16: FP32 H 16^4 40 / 40 / 32 / 35 / 39 / 43 / 43 us, 24^4 206 / 186 / 189 / 180 / 183 /
+// 198 / 209 us; FP16 storage 16^4 32 / 33 / 25 / 26 / 25 / 30 / 28 us; a fourth block on few: nseg = 2 / 4 / 5 / 7 / 14 at 16^3 x 14
+// FP32 36 / 31 / 32 / 36 / 38, FP16 storage 29 / 25 / 26 / 25 / 26 (7 would be 3.5 a CU); 6 / 11 / 22 at 12 x 8 x 12 x 22 FP32
+// 22 / 18 / 20, FP16 storage 18.1 / 15.1 / 15.9 (22: 3.1).
 static PlaneCbDev plane_cb_dev(const GeomDev &g) {
     PlaneCbDev d{};
     d.ltx = (g.L[0] % 8 == 0 && g.L[1] % 4 == 0) ? 2 : (g.L[0] % 4 == 0 && g.L[1] % 8 == 0) ? 1 : 0;
@@ -424,7 +426,7 @@ static PlaneCbDev plane_cb_dev(const GeomDev &g) {
     double best = 0.0;
     for (int n = 1; n <= g.L[3]; ++n) {
         const double m = tiles * n / 256.0, t = (g.L[3] + n - 1) / n + 0.5;
-        const double cost = t * (m <= 3.0 ? 1.5 + ceil(m) : 1.0 + 1.5 * m);
+        const double cost = t * (m <= 3.0 ? 1.5 + ceil(m) : fmax(6.5, 1.0 + 1.5 * m));
         if (n == 1 || cost < best) {
             best = cost;
             d.nseg = n;
