@@ -80,6 +80,13 @@ bool walk_mobius_applies(const DhopArgs &a);
 // Whether n records or sites of `bytes` (a time slice's records or links) have 32-bit byte offsets, as
 // the tiled schedules form them.
 inline bool offsets32(long n, long bytes) { return n <= 0xffffffffL / bytes; }
+// The counts n of blocks along t that a schedule has to weigh, ascending from 1 to Lt: the least n of every
+// length ceil(Lt / n) of the longest walk (more blocks of that length cost more). About 2 sqrt(Lt) of them; all Lt
+// took 6 to 8 us of a launch's host time at Lt = 2047.
+inline int next_walk_count(int Lt, int n) {
+    const int T = (Lt + n - 1) / n;
+    return T == 1 ? Lt + 1 : (Lt + T - 2) / (T - 1);
+}
 // Tiled time-walk schedule (tile.hip): full-lattice 4D FP16-storage and large FP32 fields
 // whose x, y, z extents the tile divides.
 bool tile_applies(const DhopArgs &a);

@@ -442,18 +442,17 @@ static bool plane_tile(const GeomDev &g, PlaneDev *d) {
     return g.L[0] % d->tx == 0 && g.L[1] % d->ty == 0;
 }
 
-// Blocks along t: of the counts that divide Lt into walks of T <= 8 slices the one with the least of (T + 1.5) x
-// the sum over rounds of (1.5 + blocks of the round on a CU). A walk's start and end cost about one and a half slices, and a
-// slice of one block takes, with m blocks on its CU, about as long as 1.5 + m (latency, then
-// throughput). Measured, T = 2 / 3 / 4 / 6 / 8 / 12 / 24: 24^4 x 12 FP16 storage 226 / 205 / 198 / 193 / 198 /
-// 197 / 201 us, FP32 371 / 339 / 339 / 336 / 348 / 340 / 371 us, 24^4 x 8 FP32 248 / 229 / 227 / 221 / 236 / 237 /
-// 239 us; T = 2 / 4 / 8 / 16: 16^4 x 16 FP32 93 / 85 / 80 / 89 us, 16^4 x 12 FP16 storage 45 / 39 / 45 / 58 us;
-// T = 1 / 2 / 3 / 4 / 6: 12^4 x 16 FP32 38 / 34 / 29 / 34 / 34 us. A count that does not divide Lt, its longest walk for
-// T, is taken where that is well below: an Lt without such a divisor would leave walks of one slice, which read
-// three. Equal / unequal walks: 16^3 x 13 FP32 x 8 / 12 / 16 / 20 / 24 41 / 34, 56 / 48, 76 / 58, 127 / 89, 137 / 98 us (the
-// column walk 47, 67, 88, 108, 126), 24^3 x 23 x 12 344 / 261, FP16 storage 204 / 174; a little below is no gain: 20^4
-// FP32 x 12 / 16 / 24 (0.94 to 0.98 of the model) 133 / 137, 167 / 174, 296 / 319, 16^3 x 34 x 8 (0.78) 88 / 90; FP16 storage, whose one-slice walks cost less than
-// modelled, 16^3 x 13 x 12 (0.62) 35 / 38, 12^3 x 19 x 12 (0.60) 25 / 25, 16^3 x 13 x 16 (0.57) 43 / 40.
+// Blocks along t: the count with the least (T + start) x the sum over rounds of (a + blocks of the round on a CU),
+// T slices the longest walk. A walk's start and end cost FP32 records 1.2 slices, codes 0.4, and a slice of one
+// block takes, with m blocks on its CU, about as long as a + m (latency, then throughput; a = 2, for the five or six
+// wavefronts of Ls = 20 and 24 0.25, and for codes 1). Walks are of
+// at most 8 slices, in FP32 of 13 where all blocks run in one round (longer ones lose the reuse between
+// neighbouring blocks: 24^4 x 16 T = 6 / 8 / 12 355 / 390 / 384 us); a count that does not divide Lt has to be a tenth better.
+// Measured, T = 1 / 2 / 3 / 4 / 6 / 8 / 12: 24^4 x 12 FP32 362 / 297 / 270 / 274 / 273 / 288 / 286 us, FP16 storage 223 / 187 / 179 / 182 /
+// 178 / 185 / 182; 16^4 x 16 FP32 T = 1 / 2 / 4 / 8 90 / 77 / 69 / 64, 16^4 x 12 FP16 storage 42 / 39 / 37 / 43; 16^3 x 13 x 24 FP32
+// T = 1 / 2 / 4 / 7 / 13 138 / 115 / 114 / 98 / 88 (the column walk 126), 20 x 12 x 21 x 5 x 12 FP16 storage T = 1 / 2 / 5 25 / 21 / 28
+// (column walk 21.5), 8 x 24 x 19 x 14 x 12 T = 2 / 7 34 / 38 (35). Over 220 shapes with every count timed the choice is
+// 0.9 % from the best.
 static PlaneDev plane_dev(const GeomDev &g, bool scaled) {
     PlaneDev d{};
     if (!plane_tile(g, &d)) return d;
@@ -462,23 +461,18 @@ static PlaneDev plane_dev(const GeomDev &g, bool scaled) {
     const long by_lds = 128 / granules;   // 160 KB in granules of 1280 bytes
     const long per_cu = by_lds < 12 / waves ? by_lds : 12 / waves;   // three wavefronts per SIMD
     const long tiles = static_cast<long>(g.vol / g.L[3]) / (d.tx * d.ty);
-    double even = 0.0, any = 0.0;   // costs of the best count that divides Lt, and of the best of all
-    int uneven = 0;
-    for (int n = g.L[3]; n >= 1; --n) {
-        const int T = (g.L[3] + n - 1) / n;
-        if (T > 8) break;
+    const double start = scaled ? 0.4 : 1.2, a = scaled ? 1.0 : g.Ls > 16 ? 0.25 : 2.0;
+    double best = 0.0;
+    for (int len = 1; len <= (scaled ? 8 : 13) && len <= g.L[3]; ++len) {
+        const int n = (g.L[3] + len - 1) / len, T = (g.L[3] + n - 1) / n;
         const long m = (tiles * n + 255) / 256, rem = m % per_cu;
-        const double cost = (T + 1.5) * ((m / per_cu) * (1.5 + per_cu) + (rem ? 1.5 + rem : 0.0));
-        if (g.L[3] % n == 0 && (d.nseg == 0 || cost < even)) {
-            even = cost;
+        if (T > 8 && m > per_cu) continue;
+        const double cost = (T + start) * ((m / per_cu) * (a + per_cu) + (rem ? a + rem : 0.0)) * (g.L[3] % n ? 1.1 : 1.0);
+        if (d.nseg == 0 || cost < best) {
+            best = cost;
             d.nseg = n;
         }
-        if (uneven == 0 || cost < any) {
-            any = cost;
-            uneven = n;
-        }
     }
-    if (any < (scaled ? 0.59 : 0.76) * even) d.nseg = uneven;
     return d;
 }
 

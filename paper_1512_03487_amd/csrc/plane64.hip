@@ -287,7 +287,7 @@ static int plane64_nseg(const GeomDev &g, double *even) {
     const long tiles = static_cast<long>(g.vol / g.L[3]) / kP6Cols;
     long best = 0;
     int nseg = 1;
-    for (int n = 1; n <= g.L[3]; ++n) {
+    for (int n = 1; n <= g.L[3]; n = next_walk_count(g.L[3], n)) {
         const long T = (g.L[3] + n - 1) / n, rounds = (tiles * n + slots - 1) / slots, cost = (T + 1) * rounds;
         if (n == 1 || cost < best) {
             best = cost;

@@ -424,7 +424,7 @@ static PlaneCbDev plane_cb_dev(const GeomDev &g) {
     d.ltx = (g.L[0] % 8 == 0 && g.L[1] % 4 == 0) ? 2 : (g.L[0] % 4 == 0 && g.L[1] % 8 == 0) ? 1 : 0;
     const long tiles = static_cast<long>(g.vol / g.L[3]) / 2 / kPcCols;
     double best = 0.0;
-    for (int n = 1; n <= g.L[3]; ++n) {
+    for (int n = 1; n <= g.L[3]; n = next_walk_count(g.L[3], n)) {
         const double m = tiles * n / 256.0, t = (g.L[3] + n - 1) / n + 0.5;
         const double cost = t * (m <= 3.0 ? 1.5 + ceil(m) : fmax(6.5, 1.0 + 1.5 * m));
         if (n == 1 || cost < best) {

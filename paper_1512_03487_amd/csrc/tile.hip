@@ -456,7 +456,7 @@ static TileDev tile_dev(const DhopArgs &a, double *share = nullptr) {
     td.ntz = g.L[2] / tile_z(a);
     const long ntiles = static_cast<long>(td.ntx) * td.nty * td.ntz;
     double best = 0.0;
-    for (int n = 1; n <= g.L[3]; ++n) {
+    for (int n = 1; n <= g.L[3]; n = next_walk_count(g.L[3], n)) {
         const long m = (ntiles * n + 255) / 256, rem = m % 2;
         const double cost = ((g.L[3] + n - 1) / n + start) * ((m / 2) * 2.5 + (rem ? alone : 0.0));
         if (n == 1 || cost < best) {

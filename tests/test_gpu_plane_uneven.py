@@ -20,7 +20,8 @@ def _announce():
     print("\n[gpu] test_gpu_plane_uneven", flush=True)
 
 
-# walks of 5 and 6 slices (11 in 2), 4 and 5 (13 in 3), 3 and 4 (31 in 8, 23 in 6), 6 and 7 (13 in 2)
+# FP32 / FP16 storage: 11 slices in 2 / 3 walks, 13 in 3 / 7, 31 in 8, 23 in 4 (column walk), 13 in 1 (the longest
+# walk), 17 in 4 / 6
 @pytest.mark.parametrize("dims,Ls", [((16, 16, 16, 11), 16), ((16, 16, 16, 13), 12), ((8, 8, 32, 31), 8), ((8, 8, 16, 23), 24),
                                      ((16, 16, 16, 13), 20), ((16, 16, 16, 17), 8)])
 @pytest.mark.parametrize("prec,fmt", [("f32", "L18"), ("f16s", "L12")])
