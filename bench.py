@@ -43,7 +43,8 @@ TRAFFIC_FILES = {
     "dwf_24^4x12_f16s_L18": os.path.join(ROOT, "profiles", "traffic_dwf_f16s_L18_24x24x24x24_ls12.txt"),
 }
 ORACLE_CG_FILE = os.path.join(ROOT, "profiles", "oracle_cg_dwf_16x16x16x16_ls16.txt")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1512_03487_amd", "csrc", f) for f in ("dhop.hip", "tile.hip", "plane.hip", "device.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1512_03487_amd", "csrc", f)
+                  for f in ("dhop.hip", "tile.hip", "plane.hip", "plane_cb.hip", "plane64.hip", "device.h")]
 HEAD_DIMS = (32, 32, 32, 32)
 HEAD_KERNEL = "k_dhop_tile<SpF32, LkF32<3>, hop>"
 

@@ -706,9 +706,9 @@ __device__ __forceinline__ void gather(const void *__restrict__ base, const floa
     stage<SP>(f, lds, p);
 }
 
-// Stores the records A of a wavefront's lanes, consecutive ones (this lane's is rec, idle lanes counting on; live lanes come first).
-// FP32 records go through the wavefront's staging area so that consecutive lanes write consecutive
-// 16 bytes: stored by their lanes, 16 bytes at a time at 96-byte pitch, each piece is a request to the
+// Stores the records A of a wavefront's lanes, consecutive ones (this lane's is rec, idle lanes counting on; live
+// lanes come first). FP32 records go through the wavefront's staging area so that consecutive lanes write
+// consecutive 16 bytes: stored by their lanes, 16 bytes at a time at 96-byte pitch, each piece is a request to the
 // L2 by itself. (FP16-storage records are as fast stored by their lanes.) Returns |A|^2 as stored with N2.
 template <class SP, bool N2>
 __device__ __forceinline__ double store_run(chunk_t *lds, void *out, float *out_scale, size_t rec, bool live,

@@ -8,21 +8,24 @@
 // registers, as in the column walks. The finished records of a slice leave through LDS (wave_store)
 // before the next slice's take their place there.
 //
-// Why. A CU keeps about 56 vector-L1 misses in flight (requests x latency / time, the same in every
-// schedule measured, a plain copy included), so the time goes with the number of 128-byte lines a
-// site requests times their latency: 6.9 lines in the same-step column walk, which fetches a record
-// for each of its uses, and 4.0 here (FP32, 24^4 x 12; FP16 storage 3.9 and 2.4); and stores of 16 bytes per
-// lane at the record's pitch send 24 million requests to the L2 there, more than the 16.6 million reads,
-// against 6 million through LDS. Same-step walk / this kernel without / with the stores through LDS:
-// 24^4 x 12 FP32 376 / 335 / 272 us from memory, in cache 320 -> 279, FP16 storage 190 -> 185; 16^4 x 16 FP32
-// 105 / 72 / 60 us, FP16 storage 59 / 48 / 46; 16^4 x 8 FP32 40 -> 31 us. Moebius (16^4 x 16): FP32 M 107 (column
-// walk) / 70 / 66 us, FP16 storage 90 / 54 / 56 us: B is applied once to each of the four records a site
-// loads instead of to all eight it hops. What remains is the latency of the lines that miss the L2: at
-// this size a step of the blocks an XCD holds moves as much as its L2, so the z neighbours are mostly
-// fetched again.
+// Why. The column walks are bound by the number of 128-byte lines a site requests times their latency (a CU
+// kept about 56 vector-L1 misses in flight in each of them and in a plain copy): 6.9 lines in the same-step walk,
+// which fetches a record for each of its uses, and 3.75 here (FP32, 24^4 x 12; FP16 storage 3.9 and 2.1); and stores
+// of 16 bytes per lane at the record's pitch send 24 million requests to the L2 there, more than the 14.9 million
+// reads, against 6 million through LDS. Same-step walk / this kernel without / with the stores through LDS:
+// 24^4 x 12 FP32 376 / 335 / 272 us from memory, in cache 320 -> 279, FP16 storage 190 -> 185 (now 177); 16^4 x 16
+// FP32 105 / 72 / 60 us, FP16 storage 59 / 48 / 46; 16^4 x 8 FP32 40 -> 31 us. Moebius: B is applied once to each of the
+// four records a site loads instead of to all eight it hops; M at 16^4 x 16 from memory, column walk / this kernel:
+// FP32 108 / 74 us, FP16 storage 91 / 57 (its stores through LDS or by their lanes: the same within 1 % at 16^4,
+// 24^4, 12^3 x 24 and 20 x 16 x 24 x 14).
+// What bounds it now is the bytes that cross the fabric: 24^4 x 12 FP32 reads 1426 MB and writes 385 in 270 us,
+// 6.7 TB/s, where a large copy reaches 5.4, and the mean latency of a read is 844 cycles, 447 to 477 in the kernels
+// bound by requests. 2.98 times the compulsory bytes are read: a step of the blocks an XCD holds moves as
+// much as its L2, so the z neighbours are mostly fetched again.
 // Tried and not kept: the next slice's loads in registers during the hops (345 against 325 us in
-// FP32, registers spill), streaming stores (580 us), tiles ordered over 2 x 2 x 2 XCD domains (+- 2 %),
-// tiles of two z planes (a quarter fewer requests, but one block per CU: 352 against 307 us).
+// FP32, registers spill), streaming stores (580 us), tiles of two z planes (a quarter fewer requests, but
+// one block per CU: 352 against 307 us); tiles ordered over 2 x 2 x 2 XCD domains (+- 2 %, in the first version of
+// this kernel, which its stores bound: no finding about the present one).
 //
 // The SU(3) products run on the matrix cores: the four lanes of a v_mfma_f32_4x4x1 block are four s
 // of one 4D site and share its link (su3_mfma), which needs Ls to be a multiple of four. A lane then
@@ -442,17 +445,17 @@ static bool plane_tile(const GeomDev &g, PlaneDev *d) {
     return g.L[0] % d->tx == 0 && g.L[1] % d->ty == 0;
 }
 
-// Blocks along t: the count with the least (T + start) x the sum over rounds of (a + blocks of the round on a CU),
-// T slices the longest walk. A walk's start and end cost FP32 records 1.2 slices, codes 0.4, and a slice of one
-// block takes, with m blocks on its CU, about as long as a + m (latency, then throughput; a = 2, for the five or six
-// wavefronts of Ls = 20 and 24 0.25, and for codes 1). Walks are of
-// at most 8 slices, in FP32 of 13 where all blocks run in one round (longer ones lose the reuse between
-// neighbouring blocks: 24^4 x 16 T = 6 / 8 / 12 355 / 390 / 384 us); a count that does not divide Lt has to be a tenth better.
-// Measured, T = 1 / 2 / 3 / 4 / 6 / 8 / 12: 24^4 x 12 FP32 362 / 297 / 270 / 274 / 273 / 288 / 286 us, FP16 storage 223 / 187 / 179 / 182 /
-// 178 / 185 / 182; 16^4 x 16 FP32 T = 1 / 2 / 4 / 8 90 / 77 / 69 / 64, 16^4 x 12 FP16 storage 42 / 39 / 37 / 43; 16^3 x 13 x 24 FP32
-// T = 1 / 2 / 4 / 7 / 13 138 / 115 / 114 / 98 / 88 (the column walk 126), 20 x 12 x 21 x 5 x 12 FP16 storage T = 1 / 2 / 5 25 / 21 / 28
-// (column walk 21.5), 8 x 24 x 19 x 14 x 12 T = 2 / 7 34 / 38 (35). Over 220 shapes with every count timed the choice is
-// 0.9 % from the best.
+// Blocks along t: the count with the least (T + start) x the sum over rounds of (a + blocks of the round on a
+// CU), T slices the longest walk. A walk's start and end cost FP32 records 1.2 slices, codes 0.4, and a slice of one
+// block takes, with m blocks on its CU, about as long as a + m (latency, then throughput; a = 2, for the five or
+// six wavefronts of Ls = 20 and 24 0.25, and for codes 1). Walks are of at most 8 slices, in FP32 of 13 where all
+// blocks run in one round (longer ones lose the reuse between neighbouring blocks: 24^4 x 16 T = 6 / 8 / 12
+// 355 / 390 / 384 us); a count that does not divide Lt has to be a tenth better.
+// Measured, T = 1 / 2 / 3 / 4 / 6 / 8 / 12: 24^4 x 12 FP32 362 / 297 / 270 / 274 / 273 / 288 / 286 us, FP16 storage
+// 223 / 187 / 179 / 182 / 178 / 185 / 182; T = 1 / 2 / 4 / 8: 16^4 x 16 FP32 90 / 77 / 69 / 64, 16^4 x 12 FP16 storage
+// 42 / 39 / 37 / 43; 16^3 x 13 x 24 FP32 T = 1 / 2 / 4 / 7 / 13 138 / 115 / 114 / 98 / 88 (the column walk 126), 20 x 12 x 21 x 5 x 12
+// FP16 storage T = 1 / 2 / 5 25 / 21 / 28 (column walk 21.5), 8 x 24 x 19 x 14 x 12 T = 2 / 7 34 / 38 (35). Over 220 shapes
+// with every count timed the choice is 0.9 % from the best.
 static PlaneDev plane_dev(const GeomDev &g, bool scaled) {
     PlaneDev d{};
     if (!plane_tile(g, &d)) return d;

@@ -12,10 +12,11 @@
 //    at the input sites), so they go through LDS once for the 16 s that share them.
 // A site fetches 4.75 records per slice in place of eight, and y: what S and (d - S)^-1 move along the
 // fifth dimension goes across the DPP row (column_m5inv_row: four steps of doubling in place of 96
-// LDS reads). As in the full-field walk the time goes with the 128-byte lines requested: checkerboard
-// column walk against this kernel, 16^4 x 16, FP16 storage: (d - S)^-1 H 45.7 -> 27.7 us, M with |out|^2
-// 34.6 -> 30 us, M^dagger with r - alpha (...) 38 -> 32 us; FP32 H 48 -> 33 us, with y 57 -> 40 us; 24^4 x 16 H
-// FP32 275 -> 184 us, FP16 storage 137 -> 106 us. The even-odd domain-wall solve at 16^4 x 16: 50.1 -> 40.7 ms.
+// LDS reads). The time goes with the 128-byte lines requested. Checkerboard column walk against this kernel,
+// 16^4 x 16 in cache, FP16 storage: (d - S)^-1 H 45.7 -> 27.7 us, M with |out|^2 34.6 -> 30 us, M^dagger with
+// r - alpha (...) 38 -> 32 us; FP32 H 48 -> 33 us, with y 57 -> 40 us. From memory H and with y: 16^4 x 16 FP32 52 -> 38,
+// 64 -> 47 us, FP16 storage 31 -> 25, 39 -> 28; 24^4 x 16 FP32 278 -> 187, 313 -> 235, FP16 storage 147 -> 109, 192 -> 130. The
+// even-odd domain-wall solve at 16^4 x 16: 50.1 -> 40.4 ms.
 // Tried and not kept: four wavefronts per SIMD (24 to 48 registers spilled: 38 against 28 us).
 #include <math.h>
 

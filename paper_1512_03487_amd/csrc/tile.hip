@@ -21,8 +21,8 @@
 // slice, touched the same cache lines (24-byte links of four directions at 96-byte pitch) each time:
 // 12-real 32^4 70 -> 62 us from memory, 58 -> 55 in cache, 18-real 72 -> 56, 24^4 x 18-real 30 -> 26; before
 // that the records' conversion and scaling ahead of the projection, and a last round of blocks a third
-// full: 75.5 -> 70 us, 18-real 79 -> 72. FP32: 32^4 138 (direction-parallel) -> 107 us from memory, whose
-// bytes take 99 us.
+// full: 75.5 -> 70 us, 18-real 79 -> 72. FP32: 32^4 143 (direction-parallel) -> 108 us from memory, whose
+// bytes take 99 us, with 12-real links 126 -> 90.
 //
 // Per site: 8 x (12 + 132) + 7 x 24 = 1320 flops, the convention of the flop counts quoted for
 // this operator.
@@ -432,14 +432,14 @@ k_dhop_tile(const void *__restrict__ U, const void *__restrict__ psi, const floa
 }
 
 // Tiles: 8 x 8 x 4 (256 threads) for FP16 storage, 8 x 8 x 2 for FP32, whose links and records fill the
-// LDS (76 KB; 8 x 8 x 4 takes 134 KB and one block per CU: 32^4 18-real 108 against 110 us, 12-real 105 against
-// 101, 32^3 x 16 51 and 53 against 50 and 51). Two blocks fit a CU. Blocks along t: the count with the least
-// (slices of the longest + start) x the sum over the rounds of blocks a CU runs at a time, 2.5 for two and
-// `alone` for one; start and alone as measured, FP32's longer prefetch weighing more. nseg = 1 / 2 / 4 / 6 / 8 /
-// 12 / 16, 12-real links: FP16 storage 32^4 116 / 64 / 55 / 62 / 59 / 65 / 62 us, 24^4 87 / 47 / 28 / 30 / 25 / 26 /
-// 29; FP32 32^4 141 / 101 / 104 / 117 / 114 / 128 / 134 us. FP16 storage, two blocks of one slice against one of two:
-// 16 x 24 x 12 x 28 nseg 28 / 14 10.6 / 11.7 us, 16^2 x 20 x 24 nseg 24 / 12 10.6 / 11.5; three of one against two of
-// two: 24^2 x 20 x 16 nseg 16 / 8 17.3 / 18.8 us.
+// LDS (76 KB; 8 x 8 x 4 takes 134 KB, with 12-real links 104, and one block per CU: 32^4 18-real 115 against 108 us,
+// 12-real 100 against 90, 32^3 x 16 63 and 54 against 59 and 50). Two blocks fit a CU. Blocks along t: the count with
+// the least (slices of the longest + start) x the sum over the rounds of blocks a CU runs at a time, 2.5 for two
+// and `alone` for one; start and alone as measured, FP32's longer prefetch weighing more. 12-real links: FP16 storage,
+// nseg = 1 / 2 / 4 / 6 / 8 / 12 / 16, 32^4 116 / 64 / 55 / 62 / 59 / 65 / 62 us, 24^4 87 / 47 / 28 / 30 / 25 / 26 / 29; FP32 32^4,
+// nseg = 1 / 2 / 4 / 6 / 8 / 16, 138 / 90 / 99 / 111 / 112 / 131 us, 18-real 143 / 108 / 121 / 128 / 130 / 158. FP16 storage, two
+// blocks of one slice against one of two: 16 x 24 x 12 x 28 nseg 28 / 14 10.6 / 11.7 us, 16^2 x 20 x 24 nseg 24 / 12
+// 10.6 / 11.5; three of one against two of two: 24^2 x 20 x 16 nseg 16 / 8 17.3 / 18.8 us.
 constexpr int kTX = 8, kTY = 8;
 template <class SP>
 constexpr int kTZ = SP::kScaled ? 4 : 2;
@@ -473,8 +473,8 @@ static TileDev tile_dev(const DhopArgs &a, double *share = nullptr) {
 // third round for a part of one: H here / column walk 16 x 8 x 28 x 38 (2.1) 16.2 / 15.3 us, 24 x 16 x 20^2 (2.3) 16.8 /
 // 15.4, 24^3 x 13 (2.7) 18.6 / 16.8, 24^2 x 20 x 16 (2.8) 18.4 / 16.4, D 18.6 / 16.9, and beside that range 16^3 x 28 (1.75)
 // 11.9 / 12.1, 24^2 x 36 x 9 (2.85) 17.3 / 19.0, 24^3 x 15 (3.2) 19.4 / 21.1; with 18-real links 24^3 x 13 19.4 / 21.8.
-// FP32: from 500000 sites on (24^4, 331776 sites, which the caches hold, 38 / 39 us here with 18- / 12-real links,
-// 35 / 34 there) where the blocks keep the CUs evenly busy: a share of at least 0.78 (18-real) or 0.70 (12-real).
+// FP32: from 500000 sites on (24^4, 331776 sites, which the caches hold, 12-real 35.4 us here, 34.7
+// direct) where the blocks keep the CUs evenly busy: a share of at least 0.78 (18-real) or 0.70 (12-real).
 // Direction-parallel / tile from memory, H with 18-real and 12-real links, by share: 56 x 32 x 24^2 (0.91) 137 / 125,
 // 126 / 104 us, 32 x 24 x 28 x 26 (0.88) 78 / 65, 69 / 55, 40^2 x 24^2 (0.82) 123 / 117, 110 / 100, 32^2 x 20 x 28 (0.82) 80 / 69,
 // 71 / 58, 32^2 x 24^2 (0.81) 82 / 83, 71 / 70 (D 12-real 76 / 71), 24^2 x 32 x 30 (0.79) 73 / 67, 66 / 57, 16 x 48 x 30 x 28

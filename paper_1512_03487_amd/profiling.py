@@ -49,7 +49,7 @@ def _calibration_copies(rows, counter, n=3):
 
 def kernel_source_hash(root):
     h = hashlib.sha256()
-    for f in ("dhop.hip", "tile.hip", "plane.hip", "device.h"):
+    for f in ("dhop.hip", "tile.hip", "plane.hip", "plane_cb.hip", "plane64.hip", "device.h"):
         with open(os.path.join(root, "paper_1512_03487_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
