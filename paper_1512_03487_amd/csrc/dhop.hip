@@ -1213,10 +1213,10 @@ static hipError_t launch_walk_cb(const DhopArgs &a) {
 
 // Schedules: the plane walk (plane.hip) for the plain operators on 5D FP32 and FP16-storage fields its tiles
 // divide, its checkerboard form (plane_cb.hip) for Ls = 16 and its form for large 5D FP64 fields (plane64.hip);
-// the tiled walk (tile.hip) for 4D FP16-storage fields, with 12-real links but for 2 to 2.83 slices of a block
-// per CU, and for large FP32 ones; column walks for the other FP16-storage and 5D FP32 fields (full lattice, or
-// checkerboard fields in the even-odd form); direction-parallel otherwise (measured faster there). The
-// full-lattice walk also takes the custom form with a separate y and beta = -1/2 (the Moebius operator's
+// the tiled walk (tile.hip) for 4D FP16-storage fields, with 12-real links but for 2 to 2.83 and 4 to 5 slices of
+// a block per CU, and for large FP32 ones; column walks for the other FP16-storage and 5D FP32 fields (full
+// lattice, or checkerboard fields in the even-odd form); direction-parallel otherwise (measured faster there).
+// The full-lattice walk also takes the custom form with a separate y and beta = -1/2 (the Moebius operator's
 // hopping pass).
 static bool walk_prec(const DhopArgs &a) { return a.prec == GRID_F16S || (a.prec == GRID_F32 && a.g.Ls > 1); }
 static bool use_walk(const DhopArgs &a) {

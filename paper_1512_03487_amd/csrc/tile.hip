@@ -472,7 +472,11 @@ static TileDev tile_dev(const DhopArgs &a, double *share = nullptr) {
 // 132), but with 12-real links not those of 2 to 2.83 slices of a block per CU, where two blocks on a CU take a
 // third round for a part of one: H here / column walk 16 x 8 x 28 x 38 (2.1) 16.2 / 15.3 us, 24 x 16 x 20^2 (2.3) 16.8 /
 // 15.4, 24^3 x 13 (2.7) 18.6 / 16.8, 24^2 x 20 x 16 (2.8) 18.4 / 16.4, D 18.6 / 16.9, and beside that range 16^3 x 28 (1.75)
-// 11.9 / 12.1, 24^2 x 36 x 9 (2.85) 17.3 / 19.0, 24^3 x 15 (3.2) 19.4 / 21.1; with 18-real links 24^3 x 13 19.4 / 21.8.
+// 11.9 / 12.1, 24^2 x 36 x 9 (2.85) 17.3 / 19.0, 24^3 x 15 (3.2) 19.4 / 21.1; nor, for the same reason, those of 4 to 5
+// in time slices of up to 15000 sites (larger ones slow the column walk): 8 x 24 x 36 x 38 (4.01) 23.9 / 22.1, 24 x 16
+// x 24 x 31 (4.4) 24.7 / 23.3, 32 x 24 x 12 x 34 (4.8) 25.0 / 24.0, 24 x 32 x 16 x 26 (4.9) 24.8 / 24.5, D 25.0 / 24.4, beside them
+// 40 x 16^2 x 24 (3.75) 20.0 / 20.7, 24 x 16 x 32 x 27 (5.06) 24.8 / 27.4, 48 x 16 x 36 x 10 (4.2, 27648 sites) 24.6 / 27.9;
+// with 18-real links 24^3 x 13 19.4 / 21.8.
 // FP32: from 500000 sites on (24^4, 331776 sites, which the caches hold, 12-real 35.4 us here, 34.7
 // direct) where the blocks keep the CUs evenly busy: a share of at least 0.78 (18-real) or 0.70 (12-real).
 // Direction-parallel / tile from memory, H with 18-real and 12-real links, by share: 56 x 32 x 24^2 (0.91) 137 / 125,
@@ -485,7 +489,9 @@ bool tile_applies(const DhopArgs &a) {
     if (a.g.L[0] % kTX || a.g.L[1] % kTY || a.g.L[2] % tile_z(a) || !offsets32(a.g.vol / a.g.L[3], 288)) return false;
     if (a.prec == GRID_F16S) {
         const double per_cu = static_cast<double>(a.g.vol) / (kTX * kTY * kTZ<SpF16S> * 256.0);
-        return a.link_fmt == GRID_L18 || per_cu <= 2.0 || per_cu >= 2.83;
+        const bool third_round =
+            (per_cu > 2.0 && per_cu < 2.83) || (per_cu > 4.0 && per_cu < 5.0 && a.g.vol / a.g.L[3] <= 15000);
+        return a.link_fmt == GRID_L18 || !third_round;
     }
     if (a.g.n5 < 500000) return false;
     double share;

@@ -43,3 +43,14 @@ def test_walk_4d_fused_epilogues_in_the_mixed_solve(gpu, dims):
     x, s = gm.cg(dev(U), dev(b), "wilson", mass=0.3, tol=1e-9, sloppy="f16s", link_fmt="L12")
     assert s["iterations"] <= 1.25 * s64["iterations"] + 10, (s["iterations"], s64["iterations"])
     assert rel(O.normal(O.Op.wilson(0.3), U, host(x)), b) <= 1.1e-9
+
+
+# blocks x Lt / 256: 4.0 (the tile), 4.06, 4.92, 5.06 (the tile), and 4.69 in slices of 15360 sites (the tile)
+@pytest.mark.parametrize("dims", [(16, 16, 32, 32), (16, 16, 16, 65), (8, 16, 40, 63), (16, 16, 16, 81), (24, 40, 16, 20)])
+@pytest.mark.parametrize("fmt", ["L18", "L12"])
+def test_walk_4d_parity_four_to_five_slices(gpu, dims, fmt):
+    test_walk_4d_parity(gpu, dims, fmt)
+
+
+def test_walk_4d_fused_epilogues_four_to_five_slices(gpu):
+    test_walk_4d_fused_epilogues_in_the_mixed_solve(gpu, (8, 16, 40, 63))
